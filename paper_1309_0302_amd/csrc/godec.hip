@@ -944,7 +944,7 @@ godec_status godec_get_S(godec_ctx* c, int64_t* idx_dev, void* val_dev, int64_t*
   }
   if (!idx_dev || !val_dev) return fail(GODEC_E_INVAL, "NULL output buffer");
   const Launch L = launch_of(c);
-  launch_sort_s(L, c->f64, c->s_idx[c->cur], c->s_val[c->cur], c->plan[c->cur], c->m * c->n,
+  launch_sort_s(L, c->f64, c->s_idx[c->cur], c->s_val[c->cur], &c->plan[c->cur]->nnz, c->m * c->n,
                 std::max<int64_t>(c->k, 1), c->bitmap, c->wpre, c->bsum, c->boff, idx_dev,
                 val_dev);
   SelPlan hp;

@@ -503,21 +503,30 @@ godec_status godec_batch_get_S(godec_batch* b, int32_t i, int64_t* idx_dev, void
   HIP_TRY(hipMemcpyAsync(&hs, b->tab[i].sel, sizeof(BSel), hipMemcpyDeviceToHost, b->stream));
   HIP_TRY(hipStreamSynchronize(b->stream));
   const int64_t nnz = hs.nnz_list[list];
-  std::vector<int64_t> idx(nnz);
-  std::vector<float> val(nnz);
   if (nnz > 0) {
-    HIP_TRY(hipMemcpy(idx.data(), b->tab[i].s_idx[list], sizeof(int64_t) * nnz, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(val.data(), b->tab[i].s_val[list], sizeof(float) * nnz, hipMemcpyDeviceToHost));
-  }
-  std::vector<int64_t> order(nnz);
-  for (int64_t e = 0; e < nnz; ++e) order[e] = e;
-  std::sort(order.begin(), order.end(), [&](int64_t x, int64_t y) { return idx[x] < idx[y]; });
-  std::vector<int64_t> si(nnz);
-  std::vector<float> sv(nnz);
-  for (int64_t e = 0; e < nnz; ++e) { si[e] = idx[order[e]]; sv[e] = val[order[e]]; }
-  if (nnz > 0) {
-    HIP_TRY(hipMemcpy(idx_dev, si.data(), sizeof(int64_t) * nnz, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(val_dev, sv.data(), sizeof(float) * nnz, hipMemcpyHostToDevice));
+    // The outputs may have pending work of the default stream on them (the
+    // caller's allocator reuses memory in that stream's order).
+    HIP_TRY(hipStreamSynchronize(nullptr));
+    // The index sort's scratch lies in the tie list, which is free between
+    // iterations (4 bytes for each of at least m n candidates and 768 more).
+    // Bound: the scattered list reads and writes.  On the device a list of
+    // 1.5e5 entries takes about 50 us; copied to the host, sorted there and
+    // copied back it took 4 ms.
+    const HostProb& h = b->hp[i];
+    const int64_t nwords = ceil_div(h.m * h.n, 32), nb = ceil_div(nwords, 1024);
+    Carver cv{(char*)b->tab[i].tie_idx};
+    uint32_t* bitmap = (uint32_t*)cv.take(sizeof(uint32_t) * nwords);
+    uint32_t* wpre = (uint32_t*)cv.take(sizeof(uint32_t) * nwords);
+    uint32_t* bsum = (uint32_t*)cv.take(sizeof(uint32_t) * nb);
+    unsigned long long* boff = (unsigned long long*)cv.take(sizeof(unsigned long long) * nb);
+    if (cv.off > sizeof(int32_t) * (size_t)((h.m + 3) * b->tab[i].rowcap))
+      return fail(GODEC_E_STATE, "index sort scratch exceeds the tie list");
+    launch_sort_s(Launch{b->stream, b->num_cu}, false, b->tab[i].s_idx[list],
+                  b->tab[i].s_val[list],
+                  reinterpret_cast<const long long*>(&b->tab[i].sel->nnz_list[list]), h.m * h.n,
+                  nnz, bitmap, wpre, bsum, boff, idx_dev, val_dev);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(b->stream));
   }
   *nnz_host = nnz;
   return GODEC_OK;

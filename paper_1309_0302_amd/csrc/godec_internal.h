@@ -226,8 +226,11 @@ void launch_update_d(const Launch& L, DType td, void* D, int64_t ldd, int64_t n,
 // doubles of scratch); *nonfinite |= 1 on a NaN/Inf entry.
 void launch_norm_check(const Launch& L, bool f64, const void* X, int64_t ldx,
                        int64_t m, int64_t n, double* out2, int* nonfinite, double* part);
+// An S list (*nnz <= kmax entries, distinct linear indices below mn, nnz on
+// the device) in ascending index order.  Scratch: bitmap and wpre of
+// ceil(mn / 32) words, bsum and boff of one entry per 1024 of those.
 void launch_sort_s(const Launch& L, bool f64, const int64_t* idx,
-                   const void* val, const SelPlan* plan, int64_t mn,
+                   const void* val, const long long* nnz, int64_t mn,
                    int64_t kmax, uint32_t* bitmap, uint32_t* wpre,
                    uint32_t* bsum, unsigned long long* boff, int64_t* out_idx,
                    void* out_val);

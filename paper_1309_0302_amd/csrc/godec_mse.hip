@@ -415,7 +415,7 @@ godec_status godec_mse_get_S(godec_mse* m, int64_t* idx_dev, void* val_dev, int6
   }
   if (!idx_dev || !val_dev) return fail(GODEC_E_INVAL, "NULL output buffer");
   const Launch L{m->stream, m->num_cu};
-  launch_sort_s(L, m->f64, m->s_idx[m->cur], m->s_val[m->cur], m->plan[m->cur], m->n * m->p,
+  launch_sort_s(L, m->f64, m->s_idx[m->cur], m->s_val[m->cur], &m->plan[m->cur]->nnz, m->n * m->p,
                 std::max<int64_t>(m->K, 1), m->bitmap, m->wpre, m->bsum, m->boff, idx_dev,
                 val_dev);
   SelPlan hp;

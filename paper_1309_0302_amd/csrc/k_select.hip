@@ -1620,10 +1620,10 @@ __global__ __launch_bounds__(256) void k_sum_fixed(const double* __restrict__ pa
 }
 
 // Ordered output of S: set bits of a bitmap over the linear indices, scan
-// the per-word popcounts, and scatter each entry to its rank.
-__global__ void k_bitmap_set(const int64_t* __restrict__ idx, const SelPlan* __restrict__ plan,
+// the per-word popcounts, and scatter each entry to its rank.  *nnz entries.
+__global__ void k_bitmap_set(const int64_t* __restrict__ idx, const long long* __restrict__ nnz,
                              uint32_t* __restrict__ bitmap) {
-  const long long cnt = plan->nnz;
+  const long long cnt = *nnz;
   for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < cnt;
        e += (long long)gridDim.x * 256) {
     const int64_t id = idx[e];
@@ -1677,12 +1677,12 @@ __global__ __launch_bounds__(1024) void k_bitmap_scan2(uint32_t* __restrict__ bs
 
 template <typename T>
 __global__ void k_bitmap_scatter(const int64_t* __restrict__ idx, const T* __restrict__ val,
-                                 const SelPlan* __restrict__ plan,
+                                 const long long* __restrict__ nnz,
                                  const uint32_t* __restrict__ bitmap,
                                  const uint32_t* __restrict__ wpre,
                                  const unsigned long long* __restrict__ boff,
                                  int64_t* __restrict__ out_idx, T* __restrict__ out_val) {
-  const long long cnt = plan->nnz;
+  const long long cnt = *nnz;
   for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < cnt;
        e += (long long)gridDim.x * 256) {
     const int64_t id = idx[e];
@@ -1890,7 +1890,7 @@ void launch_norm_check(const Launch& L, bool f64, const void* X, int64_t ldx, in
 }
 
 void launch_sort_s(const Launch& L, bool f64, const int64_t* idx, const void* val,
-                   const SelPlan* plan, int64_t mn, int64_t kmax, uint32_t* bitmap,
+                   const long long* nnz, int64_t mn, int64_t kmax, uint32_t* bitmap,
                    uint32_t* wpre, uint32_t* bsum, unsigned long long* boff,
                    int64_t* out_idx, void* out_val) {
   const int64_t nwords = (mn + 31) / 32;
@@ -1898,16 +1898,16 @@ void launch_sort_s(const Launch& L, bool f64, const int64_t* idx, const void* va
   hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(nwords, L.num_cu, 8)), dim3(256), 0, L.stream,
                      bitmap, nwords);
   const unsigned g = grid_for(kmax, L.num_cu, 4);
-  hipLaunchKernelGGL(k_bitmap_set, dim3(g), dim3(256), 0, L.stream, idx, plan, bitmap);
+  hipLaunchKernelGGL(k_bitmap_set, dim3(g), dim3(256), 0, L.stream, idx, nnz, bitmap);
   hipLaunchKernelGGL(k_bitmap_scan1, dim3((unsigned)nb), dim3(1024), 0, L.stream, bitmap,
                      nwords, wpre, bsum);
   hipLaunchKernelGGL(k_bitmap_scan2, dim3(1), dim3(1024), 0, L.stream, bsum, nb, boff);
   if (f64)
     hipLaunchKernelGGL(k_bitmap_scatter<double>, dim3(g), dim3(256), 0, L.stream, idx,
-                       (const double*)val, plan, bitmap, wpre, boff, out_idx, (double*)out_val);
+                       (const double*)val, nnz, bitmap, wpre, boff, out_idx, (double*)out_val);
   else
     hipLaunchKernelGGL(k_bitmap_scatter<float>, dim3(g), dim3(256), 0, L.stream, idx,
-                       (const float*)val, plan, bitmap, wpre, boff, out_idx, (float*)out_val);
+                       (const float*)val, nnz, bitmap, wpre, boff, out_idx, (float*)out_val);
 }
 
 }  // namespace godec
