@@ -66,7 +66,7 @@ struct godec_ctx {
   static constexpr int kA1Chunk = 4;
   const int64_t* support = nullptr;   // completion: fixed support of S
   int64_t support_nnz = 0;
-  int64_t* row_ptr = nullptr;         // completion: m x (ncb + 1) run starts (see init)
+  SupportWord* words = nullptr;       // completion: the support, word by word
   bool completion = false;
   bool f64;            // panel / residual type is double
   size_t ta;           // sizeof panel type
@@ -221,10 +221,9 @@ size_t carve(godec_ctx* c, void* base) {
   c->norm_x2 = (double*)cv.take(8);
   c->nonfinite = (int*)cv.take(8);
   c->s2part = (double*)cv.take((size_t)std::max(2 * kSelParts, kNormParts) * 8);
-  // completion: start of each (row, 256-column block) run of the support
-  c->row_ptr = c->completion
-                   ? (int64_t*)cv.take((size_t)m * ((c->n + 255) / 256 + 1) * 8)
-                   : nullptr;
+  c->words = c->completion
+                 ? (SupportWord*)cv.take(sizeof(SupportWord) * m * ((c->n + 63) / 64))
+                 : nullptr;
   return align_up(cv.off, 256);
 }
 
@@ -481,7 +480,8 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
     // D = X - S_{t-1} in FP32 for the refinement passes
     launch_init_d(L, F32, false, c->D, c->ldd, c->X, c->ldx, c->m, c->n, c->mpad);
     if (c->iters_done > 0)
-      launch_update_d(L, F32, c->D, c->ldd, c->n, c->s_idx[c->cur], c->s_val[c->cur],
+      launch_update_d(L, F32, c->D, c->ldd, c->n,
+                      c->completion ? c->support : c->s_idx[c->cur], c->s_val[c->cur],
                       c->s_x[c->cur], c->plan[c->cur], kk);
     c->d_native_valid = true;
   }
@@ -571,28 +571,17 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
       launch_update_d(L, BF16, c->D16, c->ldd, c->n, c->s_idx[prev], nullptr, c->s_x[prev],
                       c->plan[prev], kk);
   }
-  const bool fused_d = !c->completion;
-  if (fused_d) {
-    a.dwn = upd_native ? c->D : nullptr;
-    a.dw16 = mixed ? (uint16_t*)c->D16 : nullptr;
-    a.lddw = c->ldd;
-  }
+  // X - S on the new support is written by the sparse step itself
+  a.dwn = upd_native ? c->D : nullptr;
+  a.dw16 = mixed ? (uint16_t*)c->D16 : nullptr;
+  a.lddw = c->ldd;
   if (c->completion)
-    launch_fixed_support(L, c->f64, c->rp, c->X, c->ldx, c->UL, c->VL, c->m, c->n, c->support,
-                         c->row_ptr, c->support_nnz, c->s_idx[nxt], c->s_val[nxt],
-                         c->s_x[nxt], c->plan[nxt], (double*)c->hist);
+    launch_fixed_support(L, c->f64, c->rp, c->X, c->ldx, c->UL, c->VLt, c->ldd, c->m, c->n,
+                         c->words, c->support_nnz, c->s_val[nxt],
+                         mixed ? c->s_x[nxt] : nullptr, a.dwn, a.dw16, c->ldd, c->plan[nxt],
+                         (double*)c->hist);
   else
     launch_select(L, c->f64, c->rp, a);
-  // ---- D update, new support: X - S (written inside the selection; on a
-  // fixed support here) ----
-  if (!fused_d) {
-    if (upd_native)
-      launch_update_d(L, native, c->D, c->ldd, c->n, c->s_idx[nxt], c->s_val[nxt],
-                      c->s_x[nxt], c->plan[nxt], kk);
-    if (mixed)
-      launch_update_d(L, BF16, c->D16, c->ldd, c->n, c->s_idx[nxt], c->s_val[nxt],
-                      c->s_x[nxt], c->plan[nxt], kk);
-  }
   c->cur = nxt;
   c->iters_done += 1;
   HIP_TRY(hipGetLastError());
@@ -685,43 +674,6 @@ godec_status godec_init(godec_ctx** out, const void* X_dev, godec_dtype dtype, i
     c->completion = true;
     c->support = opts->support_dev;
     c->support_nnz = opts->support_nnz;
-    // one copy of the support to the host, on the context's stream: it is
-    // checked, then turned into the run starts below
-    std::vector<int64_t> h((size_t)c->support_nnz);
-    if (!h.empty()) {
-      hipError_t e = hipMemcpyAsync(h.data(), c->support, sizeof(int64_t) * h.size(),
-                                    hipMemcpyDeviceToHost, c->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-      if (e != hipSuccess) {
-        delete c;
-        return fail(GODEC_E_DEVICE, hipGetErrorString(e));
-      }
-      for (size_t q = 0; q < h.size(); ++q)
-        if (h[q] < 0 || h[q] >= m * n || (q > 0 && h[q] <= h[q - 1])) {
-          delete c;
-          return fail(GODEC_E_INVAL, "support must be strictly ascending in [0, m*n)");
-        }
-    }
-    // run starts of the sorted support: entry (i, cb) is the first support
-    // entry at or after (row i, column 256 cb); entry (i, ncb) is the first
-    // entry of row i + 1 (blocked CSR, ncb = ceil(n / 256))
-    const int64_t ncb = (n + 255) / 256;
-    std::vector<int64_t> rp((size_t)(m * (ncb + 1)), 0);
-    size_t pos = 0;
-    for (int64_t i = 0; i < m; ++i)
-      for (int64_t cb = 0; cb <= ncb; ++cb) {
-        const int64_t key = cb < ncb ? i * n + cb * 256 : (i + 1) * n;
-        while (pos < h.size() && h[pos] < key) ++pos;
-        rp[(size_t)(i * (ncb + 1) + cb)] = (int64_t)pos;
-      }
-    // the host table must outlive the copy: wait for it before returning
-    hipError_t e = hipMemcpyAsync(c->row_ptr, rp.data(), sizeof(int64_t) * rp.size(),
-                                  hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) {
-      delete c;
-      return fail(GODEC_E_DEVICE, hipGetErrorString(e));
-    }
   }
   c->a1_host.resize((size_t)n * r);
   if (opts && opts->a1_host)
@@ -772,13 +724,16 @@ godec_status godec_init(godec_ctx** out, const void* X_dev, godec_dtype dtype, i
   if (e == hipSuccess) e = hipMemsetAsync(c->UL, 0, (size_t)c->m * c->rp * c->ta, c->stream);
   if (e != hipSuccess) return cleanup(GODEC_E_DEVICE, hipGetErrorString(e));
   launch_norm_check(L, c->f64, X_dev, ldx, m, n, c->norm_x2, c->nonfinite, c->s2part);
+  if (c->completion)
+    launch_support_runs(L, c->support, c->support_nnz, m, n, c->words, c->nonfinite + 1);
   e = hipGetLastError();
   if (e != hipSuccess) return cleanup(GODEC_E_DEVICE, hipGetErrorString(e));
-  int bad = 0;
-  e = hipMemcpyAsync(&bad, c->nonfinite, sizeof(int), hipMemcpyDeviceToHost, c->stream);
+  int bad[2] = {0, 0};   // non-finite X, bad support
+  e = hipMemcpyAsync(bad, c->nonfinite, sizeof(bad), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return cleanup(GODEC_E_DEVICE, hipGetErrorString(e));
-  if (bad) return cleanup(GODEC_E_NUMERIC, "X contains NaN or Inf");
+  if (bad[1]) return cleanup(GODEC_E_INVAL, "support must be strictly ascending in [0, m*n)");
+  if (bad[0]) return cleanup(GODEC_E_NUMERIC, "X contains NaN or Inf");
   *out = c;
   return GODEC_OK;
 }
@@ -944,6 +899,18 @@ godec_status godec_get_S(godec_ctx* c, int64_t* idx_dev, void* val_dev, int64_t*
   }
   if (!idx_dev || !val_dev) return fail(GODEC_E_INVAL, "NULL output buffer");
   const Launch L = launch_of(c);
+  if (c->completion) {
+    // the list is the caller's ascending support, the values are in its order
+    if (c->support_nnz > 0) {
+      HIP_TRY(hipMemcpyAsync(idx_dev, c->support, sizeof(int64_t) * c->support_nnz,
+                             hipMemcpyDeviceToDevice, c->stream));
+      HIP_TRY(hipMemcpyAsync(val_dev, c->s_val[c->cur], c->ta * c->support_nnz,
+                             hipMemcpyDeviceToDevice, c->stream));
+    }
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    *nnz_host = c->support_nnz;
+    return GODEC_OK;
+  }
   launch_sort_s(L, c->f64, c->s_idx[c->cur], c->s_val[c->cur], &c->plan[c->cur]->nnz, c->m * c->n,
                 std::max<int64_t>(c->k, 1), c->bitmap, c->wpre, c->bsum, c->boff, idx_dev,
                 val_dev);

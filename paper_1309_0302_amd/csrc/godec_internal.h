@@ -456,16 +456,25 @@ void lf_pterm(const Launch& L, bool f64, int nb, int n, int r, const void* Zj, c
               const double* rtot, const void* cur, void* Vf, int w, int col);
 
 // ---- matrix completion (k_complete.hip) ----
-// S update on a fixed support (ascending; row_ptr: m x (ceil(n/256) + 1)
-// starts of its runs per row and 256-column block): lists
-// s_idx / s_val / s_x and plan (nnz, sum_r2, sum_sel2) as the selection
-// would leave them, in one pass over X.  scratch: at least
-// fixed_support_scratch_doubles() doubles.
+// A fixed support (ascending list) as the pass reads it, one record per row
+// and 64-column word (m ceil(n / 64) of them): its membership bits and the
+// list position of its first entry.  *bad |= 1 when the list is not strictly
+// ascending within [0, m n).
+struct alignas(16) SupportWord {
+  unsigned long long bits;
+  int64_t start;
+};
+void launch_support_runs(const Launch& L, const int64_t* support, int64_t nnz, int64_t m,
+                         int64_t n, SupportWord* words, int* bad);
+// S update on that support in one pass over X: s_val (and s_x, X at the
+// entries, when given) in list order, X - S into the working copies D and D16
+// (each optional), and the plan (nnz, sum_r2, sum_sel2, sum_obs2).  scratch:
+// at least fixed_support_scratch_doubles() doubles.
 void launch_fixed_support(const Launch& L, bool f64, int rp, const void* X, int64_t ldx,
-                          const void* UL, const void* VL, int64_t m, int64_t n,
-                          const int64_t* support, const int64_t* row_ptr, int64_t nnz,
-                          int64_t* s_idx, void* s_val, void* s_x, SelPlan* plan,
-                          double* scratch);
+                          const void* UL, const void* VLt, int64_t ldv, int64_t m, int64_t n,
+                          const SupportWord* words, int64_t nnz,
+                          void* s_val, void* s_x, void* D, uint16_t* D16, int64_t ldd,
+                          SelPlan* plan, double* scratch);
 int64_t fixed_support_scratch_doubles();
 
 // ---- GreBsmo (k_grebsmo.hip) ----

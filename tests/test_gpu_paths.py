@@ -45,3 +45,48 @@ def test_batch_list_in_index_order(m, n, k):
             assert torch.equal(u, v)
     b.close()
     c.close()
+
+
+# pieces of 16 rows x 64 columns, column blocks of 256: inside, at and past the
+# edges; empty, partial and full supports; D, D and its bf16 copy, FP64
+@pytest.mark.parametrize("prec", ["f32", "bf16", "f64"])
+@pytest.mark.parametrize("m,n,frac", [(1, 1, 1.0), (16, 64, 0.5), (17, 65, 0.3), (33, 321, 0.0),
+                                      (5, 300, 1.0), (70, 257, 0.05)])
+def test_fixed_support_pass(m, n, frac, prec):
+    """The list is the support with the residual the getter reports, and the
+    working copy the pass leaves is X - S: the next L update on it agrees
+    with the same update on X - S formed on the host (test bar: the FP32 or
+    FP64 rounding of one rank-1 update, 1e-5 or 1e-11; bf16 panels 2e-3)."""
+    from oracle.godec_ref import brp_power, rel_fro
+    from oracle.rng_ref import a1_gaussian
+    from paper_1309_0302_amd.binding import GoDec
+    rng = np.random.default_rng(m * 1000 + n)
+    dt = np.float64 if prec == "f64" else np.float32
+    X = (np.outer(rng.uniform(1, 2, m), rng.uniform(1, 2, n))
+         + 0.01 * rng.standard_normal((m, n))).astype(dt)
+    sup = np.sort(rng.permutation(m * n)[:int(round(frac * m * n))]).astype(np.int64)
+    sd = torch.from_numpy(sup).to("cuda:0")
+    gd = GoDec(torch.from_numpy(X).to("cuda:0"), 1, sup.size, 1, seed=3, support=sd,
+               prec=1 if prec == "bf16" else 0, refine_iters=1)
+    gd.step(1, 3)
+    idx, val = (t.cpu().numpy() for t in gd.S())
+    assert np.array_equal(idx, sup)
+    assert np.array_equal(val, gd.residual().cpu().numpy().ravel()[sup])
+    info = gd.info()
+    R = X.astype(np.float64) - gd.L_dense().cpu().numpy().astype(np.float64)
+    on = np.zeros(m * n, bool)
+    on[sup] = True
+    obs = np.sum(R.ravel()[~on] ** 2) / np.sum(X.astype(np.float64) ** 2)
+    assert abs(info["rel_err_sq"] - obs) <= 1e-6 * obs + 1e-13
+    D = X.astype(np.float64).ravel()
+    D[idx] -= val
+    A1 = a1_gaussian(3, n, 1)
+    for step, tol in ((2, {"f32": 1e-5, "bf16": 2e-3, "f64": 1e-11}[prec]),
+                      (3, {"f32": 1e-5, "bf16": 1e-5, "f64": 1e-11}[prec])):
+        gd.step(1, 3)
+        ref = brp_power(D.reshape(m, n), A1, 1).L
+        assert rel_fro(gd.L_dense().cpu().numpy().astype(np.float64), ref) <= tol
+        idx, val = (t.cpu().numpy() for t in gd.S())
+        D = X.astype(np.float64).ravel()
+        D[idx] -= val
+    gd.close()
