@@ -101,6 +101,11 @@ struct godec_ctx {
   // schedule
   int64_t nchunks, rows_per_chunk;
   int64_t kc_a, nct_a, rc_b, nch_b;   // MFMA tiling
+  // L update through A = D^T D (narrow matrices, k_gramform.hip)
+  bool gram_form = false;
+  int64_t gf_lda, gf_rows;
+  int gf_split;
+  double *gf_A = nullptr, *gf_Y[2] = {nullptr, nullptr}, *gf_Z = nullptr;
   // state
   int64_t iters_done = 0;
   // BF16_REFINE: the FP32 working copy D is only read by the refinement
@@ -161,6 +166,11 @@ PanelPlan godec_host::plan_sizes(int64_t m, int64_t n, int64_t k, int num_cu) {
 
 namespace {
 
+// Operations of the FP64 Gram that one panel pass of the general path pays
+// for: at 35 TFLOP/s 0.75e9 take 21 us, a pass on A takes 5-9 us, and a pass of
+// the general path 30-45 us (25 344 x 200, four passes: 190 us against 94).
+constexpr double kGfFlopsPerPass = 0.75e9;
+
 // Carve every buffer; returns the total size.  ctx may be a measuring dummy.
 size_t carve(godec_ctx* c, void* base) {
   Carver cv{(char*)base};
@@ -170,7 +180,7 @@ size_t carve(godec_ctx* c, void* base) {
   const int64_t mpad = c->mpad;
   c->D = cv.take((size_t)mpad * ldd * dsz);
   c->D16 = (c->prec == GODEC_PREC_BF16_REFINE) ? cv.take((size_t)mpad * ldd * 2) : nullptr;
-  if (!c->f64) {
+  if (!c->f64 && !c->gram_form) {
     c->Zt = cv.take((size_t)32 * ldd * 4);
     c->Wt = cv.take((size_t)32 * mpad * 4);
     c->Wtpart = (float*)cv.take((size_t)c->nct_a * 32 * mpad * 4);
@@ -184,13 +194,22 @@ size_t carve(godec_ctx* c, void* base) {
   c->a1_dev = c->redraw
                   ? (double*)cv.take((size_t)2 * godec_ctx::kA1Chunk * c->n * c->r * 8)
                   : nullptr;
-  c->P0 = cv.take((size_t)ldd * rp * ta);
-  c->P1 = cv.take((size_t)ldd * rp * ta);
   c->VL = cv.take((size_t)ldd * rp * ta);
   c->VLt = cv.take((size_t)ldd * rp * ta);
-  c->W = cv.take((size_t)m * rp * ta);
-  c->Zpart = c->f64 ? cv.take((size_t)c->nchunks * ldd * rp * ta) : nullptr;
-  c->Bp = cv.take((size_t)m * rp * ta);
+  if (c->gram_form) {
+    const size_t panel = (size_t)((c->n + 31) / 32 * 32) * rp * 8;
+    c->gf_A = (double*)cv.take((size_t)c->gf_lda * c->gf_lda * 8);
+    c->gf_Y[0] = (double*)cv.take(panel);
+    c->gf_Y[1] = (double*)cv.take(panel);
+    c->gf_Z = (double*)cv.take(panel);
+    c->P0 = c->P1 = c->W = c->Zpart = c->Bp = nullptr;
+  } else {
+    c->P0 = cv.take((size_t)ldd * rp * ta);
+    c->P1 = cv.take((size_t)ldd * rp * ta);
+    c->W = cv.take((size_t)m * rp * ta);
+    c->Zpart = c->f64 ? cv.take((size_t)c->nchunks * ldd * rp * ta) : nullptr;
+    c->Bp = cv.take((size_t)m * rp * ta);
+  }
   c->UL = cv.take((size_t)m * rp * ta);
   c->Kp = cv.take((size_t)rp * rp * ta);
   c->Gpart = (double*)cv.take((size_t)kGramSlots * rp * rp * 8);
@@ -262,6 +281,29 @@ godec_status validate(int64_t m, int64_t n, int32_t r, int64_t k, int32_t q,
   return GODEC_OK;
 }
 
+// Whether the L update goes through A = D^T D, and the tiling of that product.
+// The panel has to fit in LDS, and forming A (m n^2 multiply-adds in FP64)
+// has to cost less than the p + q panel passes it shortens.  The candidate
+// arrays of the sparse step, idle during the L update, hold the partial
+// tiles; a matrix too small for one tile there keeps the general path.
+void plan_gram_form(godec_ctx* c) {
+  c->gram_form = false;
+  const int64_t np = (c->n + kGfTile - 1) / kGfTile * kGfTile;
+  if (c->prec != GODEC_PREC_NATIVE || c->n > kGfMaxN || c->rp > 16 || np * c->rp > kGfMaxPanel)
+    return;
+  c->gf_lda = np;
+  const double flops = (double)c->m * (double)np * (double)(np + kGfTile);
+  if (flops > kGfFlopsPerPass * (c->p + c->q)) return;
+  const int64_t nt = np / kGfTile, ntile = nt * (nt + 1) / 2;
+  const int64_t fit = c->cap * (16 + 4 * (int64_t)c->ta) / (ntile * kGfTile * kGfTile * 8);
+  int64_t s = (512 + ntile - 1) / ntile;
+  s = std::min<int64_t>(std::min<int64_t>(s, c->mpad / kGfStep), fit);
+  if (s < 1) return;
+  c->gf_rows = ((c->mpad + s - 1) / s + kGfStep - 1) / kGfStep * kGfStep;
+  c->gf_split = (int)((c->mpad + c->gf_rows - 1) / c->gf_rows);
+  c->gram_form = true;
+}
+
 void fill_ctx_params(godec_ctx* c, int64_t m, int64_t n, int32_t r, int64_t k,
                      int32_t q, godec_dtype dtype, const godec_opts* o, int num_cu) {
   c->m = m; c->n = n; c->r = r; c->k = k; c->q = q; c->p = 2 * q + 1;
@@ -279,6 +321,7 @@ void fill_ctx_params(godec_ctx* c, int64_t m, int64_t n, int32_t r, int64_t k,
   c->kc_a = s.kc_a; c->nct_a = s.nct_a; c->rc_b = s.rc_b; c->nch_b = s.nch_b;
   c->completion = o && (o->support_dev != nullptr || o->support_nnz != 0);
   c->redraw = o && o->redraw_a1;
+  plan_gram_form(c);
 }
 
 // Counter-based SplitMix64 (Steele, Lea, Flood 2014): output i of the stream
@@ -469,13 +512,30 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
   const DType native = c->f64 ? F64 : F32;
   const bool mixed = c->prec == GODEC_PREC_BF16_REFINE;
   const bool refine = mixed && total > 0 && t >= total - c->refine_iters;
+  const int64_t kk = std::max<int64_t>(c->k, 1);
+  if (c->gram_form) {
+    GramForm g;
+    g.f64 = c->f64; g.rp = c->rp; g.r = c->r; g.p = c->p; g.q = c->q;
+    g.proj = c->lstep == 1; g.rank_tol = c->rank_tol;
+    g.m = c->m; g.n = c->n; g.mpad = c->mpad; g.ldd = c->ldd; g.D = c->D;
+    g.A1 = c->A1;
+    g.warm = c->warm && c->iters_done > 0 ? c->VL : nullptr;
+    g.ldA = c->gf_lda; g.nsplit = c->gf_split; g.rows_per = c->gf_rows; g.A = c->gf_A;
+    g.part = (double*)c->cand_idx;
+    for (int h = 0; h < 2; ++h) {
+      g.Y[h] = c->gf_Y[h];
+      g.G[h] = c->Gpart + (size_t)h * (kGfMaxN / 16) * c->rp * c->rp;
+    }
+    g.Zq = c->gf_Z; g.st = c->st; g.Kp = c->Kp;
+    g.VL = c->VL; g.VLt = c->VLt; g.UL = c->UL; g.ldv = c->ldd;
+    launch_gram_form(L, g);
+  } else {
   // ---- subspace chain: Q2 = orth((D^T D)^p A1), R2 tracked ----
   if (c->warm && c->iters_done > 0)
     HIP_TRY(hipMemcpyAsync(c->P0, c->VL, (size_t)c->ldd * c->rp * c->ta, hipMemcpyDeviceToDevice,
                            c->stream));   // Q2 of the last iteration (zero past r_eff)
   else
     launch_copy_panel(L, c->f64, c->rp, c->A1, c->n, c->ldd, c->r, c->st, c->P0);
-  const int64_t kk = std::max<int64_t>(c->k, 1);
   if (refine && !c->d_native_valid) {
     // D = X - S_{t-1} in FP32 for the refinement passes
     launch_init_d(L, F32, false, c->D, c->ldd, c->X, c->ldx, c->m, c->n, c->mpad);
@@ -529,10 +589,11 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
               c->rank_tol, c->q == 0 ? 1 : 0, c->Kp);
   launch_apply_small(L, c->f64, c->rp, c->Bp, c->m, c->Kp, c->UL);
   }
+  launch_transpose_panel(L, c->f64, c->VL, c->ldd, c->rp, c->VLt);
+  }
   // ---- sparse step ----
   const int prev = c->cur;
   const int nxt = c->cur ^ 1;
-  launch_transpose_panel(L, c->f64, c->VL, c->ldd, c->rp, c->VLt);
   SelectArgs a;
   a.X = c->X; a.ldx = c->ldx; a.UL = c->UL; a.VL = c->VL; a.m = c->m; a.n = c->n; a.k = c->k;
   a.VLt = c->VLt; a.ldv = c->ldd;

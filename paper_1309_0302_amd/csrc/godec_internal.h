@@ -455,6 +455,32 @@ void lf_qbar(const Launch& L, bool f64, int nb, int n, int r, const void* LtB, c
 void lf_pterm(const Launch& L, bool f64, int nb, int n, int r, const void* Zj, const double* rc,
               const double* rtot, const void* cur, void* Vf, int w, int col);
 
+// ---- L update of a narrow matrix through A = D^T D (k_gramform.hip) ----
+constexpr int kGfMaxN = 512;      // widest matrix
+constexpr int kGfMaxPanel = 5120; // most entries of a panel (FP64, in LDS)
+constexpr int kGfTile = 32;       // columns per side of a tile of A
+constexpr int kGfStep = 32;       // rows per step of the Gram (divides its row ranges)
+struct GramForm {
+  bool f64;
+  int rp, r, p, q;
+  bool proj;                 // projection form: U_L = D Q2
+  double rank_tol;
+  int64_t m, n, mpad, ldd;
+  const void* D;             // mpad x ldd, zero padded
+  const double* A1;          // n x r
+  const void* warm;          // start panel in place of A1 (type of X, RP columns), or null
+  int64_t ldA;               // n rounded up to 32
+  int nsplit;                // row ranges of the Gram and rows in each
+  int64_t rows_per;
+  double* A;                 // ldA x ldA
+  double* part;              // nsplit x (tiles of the lower triangle) x 1024
+  double *Y[2], *G[2], *Zq;  // panels of np x rp (np: n rounded up to 32); np/16 x rp x rp partials
+  SmallState* st;
+  void *Kp, *VL, *VLt, *UL;
+  int64_t ldv;
+};
+void launch_gram_form(const Launch& L, const GramForm& g);
+
 // ---- matrix completion (k_complete.hip) ----
 // A fixed support (ascending list) as the pass reads it, one record per row
 // and 64-column word (m ceil(n / 64) of them): its membership bits and the

@@ -90,3 +90,35 @@ def test_fixed_support_pass(m, n, frac, prec):
         D = X.astype(np.float64).ravel()
         D[idx] -= val
     gd.close()
+
+
+# the L update through A = D^T D: panel widths, 16- and 32-column edges of its
+# passes, the widest matrix and panel it takes and the first ones it leaves to
+# the general path, few and many rows, q = 0, 1, 2, both forms of the update
+@pytest.mark.parametrize("m,n,r,q,lstep", [
+    (40, 31, 1, 0, 0), (64, 32, 2, 1, 0), (65, 33, 3, 2, 0), (700, 200, 8, 1, 1),
+    (513, 256, 12, 2, 0), (400, 320, 16, 1, 0), (400, 321, 16, 1, 0), (90, 512, 8, 2, 0),
+    (90, 513, 8, 2, 0), (6000, 100, 5, 1, 0), (20, 300, 4, 1, 0), (33, 17, 2, 0, 1)])
+@pytest.mark.parametrize("dt,tol", [(np.float64, 1e-10), (np.float32, 1e-5)])
+def test_l_update_of_narrow_matrices(m, n, r, q, lstep, dt, tol):
+    """Two steps against the oracle's update on the library's own S (the bars
+    of the per-step parity tests)."""
+    from oracle import godec_ref as g
+    from oracle.rng_ref import a1_gaussian
+    from paper_1309_0302_amd.binding import GoDec
+    w = wl.tiny(m, n, r, seed=m + n, dtype=dt)
+    gd = GoDec(torch.from_numpy(w.X).to("cuda:0"), r, w.k, q, seed=9, lstep=lstep)
+    A1 = a1_gaussian(9, n, r)
+    X = w.X.astype(np.float64)
+    D = X.copy()
+    for _ in range(2):
+        gd.step(1)
+        ref = g.brp_projection(D, A1, q) if lstep else g.brp_power(D, A1, q)
+        assert g.rel_fro(gd.L_dense().cpu().numpy().astype(np.float64), ref.L) <= tol
+        UL, VL = (t.cpu().numpy().astype(np.float64) for t in gd.factors())
+        assert np.abs(VL.T @ VL - np.eye(r)).max() <= 10 * tol
+        idx, val = (t.cpu().numpy() for t in gd.S())
+        D = X.copy()
+        D.ravel()[idx] -= val
+    assert gd.info()["rank_eff"] == r
+    gd.close()
