@@ -597,7 +597,7 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
   SelectArgs a;
   a.X = c->X; a.ldx = c->ldx; a.UL = c->UL; a.VL = c->VL; a.m = c->m; a.n = c->n; a.k = c->k;
   a.VLt = c->VLt; a.ldv = c->ldd;
-  a.plan = c->plan[nxt]; a.hist = c->hist; a.counters = c->counters;
+  a.plan = c->plan[nxt]; a.next = c->plan[prev]; a.first = c->iters_done == 0; a.hist = c->hist; a.counters = c->counters;
   a.cand_idx = c->cand_idx; a.cand_val = c->cand_val; a.cand_x = c->cand_x; a.cap = c->cap;
   a.seg_count = c->seg_count;
   a.s_idx = c->s_idx[nxt]; a.s_val = c->s_val[nxt]; a.s_x = c->s_x[nxt];

@@ -22,7 +22,7 @@ constexpr int kMaxRP = 32;
 constexpr int kHistBits0 = 12;        // first radix digit of the key
 constexpr int kHistBits = 11;         // later digits
 constexpr int kHistBins = 1 << kHistBits0;
-constexpr int kHistReplicas = 8;      // global histogram copies (contention)
+constexpr int kHistReplicas = 2;      // global histogram copies (contention)
 constexpr int kMaxSeg = 4096;         // most candidate segments (waves of a full pass)
 // Fixed-order partial sums: one slot per block of a full selection pass
 // (kSelParts, at most kMaxSeg / 4 + 1 blocks), the same again for the
@@ -45,8 +45,7 @@ enum DType { F64 = 0, F32 = 1, BF16 = 2 };
 enum SelMode : int {
   SEL_HIST = 0,      // next full-data pass histograms the next digit
   SEL_COLLECT = 1,   // next full-data pass writes candidates >= bucket low
-  SEL_REFINE = 2,    // candidates hold the bucket; refine digits over them
-  SEL_FINAL = 3,     // threshold resolved, candidates hold everything needed
+  SEL_FINAL = 3,     // the candidates hold S: those above [blo, bhi] and part of that bin
   SEL_TIES = 4,      // threshold resolved but ties overflow the candidates:
                      // the next full pass collects the entries above it
   SEL_DONE = 5,      // S written by the index-ordered tie scan
@@ -63,6 +62,7 @@ struct SelPlan {
   long long nnz;               // entries of S written by compaction
   int pbits;                   // number of resolved key bits
   int kbits;                   // key width (31 for f32, 63 for f64)
+  unsigned long long blo, bhi; // at SEL_FINAL: keys of the bin holding the k-th key
   int mode;                    // SelMode
   int slow;                    // a slow exact path was used
   int overflow;                // candidate buffer overflowed
@@ -173,8 +173,10 @@ struct SelectArgs {
   int64_t m, n;
   int64_t k;
   SelPlan* plan;
+  SelPlan* next;        // plan of the next selection, reset by this one
+  bool first = false;   // first selection of the context: reset plan as well
   unsigned long long* hist;      // kHistRep x kHistBins counters
-  unsigned long long* counters;  // [0] above threshold, [1] ties
+  unsigned long long* counters;  // [0] above the last bin, [1] in it
   // candidates: 2*cap entries; [0, cap) is split into one segment per block
   // of the full-data passes, [cap, 2*cap) is the shared spill region
   int64_t* cand_idx;
@@ -185,7 +187,7 @@ struct SelectArgs {
   int64_t* s_idx;       // output S list (unordered)
   void* s_val;
   void* s_x;
-  int64_t* tie_idx;     // scratch for ties (cap entries)
+  int64_t* tie_idx;     // scratch (cap entries): the last bin's candidates
   SelCarry* carry;      // persists across iterations
   double* s2part;       // 2 * kSelParts partial sums (pass 0, then compaction)
   hipEvent_t ev_a = nullptr, ev_b = nullptr;  // optional: bracket pass 0
@@ -199,9 +201,9 @@ struct SelectArgs {
   const SelPlan* rplan = nullptr;
   // optional: x - s is written into these working copies of D (ldd x n,
   // row-major; the bf16 copy for FP32 X only) at every entry of the new S:
-  // by the compaction for the entries it takes below the plan's
-  // count_above, by the tie-value pass for the rest (the ties, or every
-  // entry when the threshold scan wrote the list)
+  // by the compaction for the entries above the last bin, by the final step
+  // for those taken from it, or by the tie-value pass for every entry when
+  // the threshold scan wrote the list
   void* dwn = nullptr;      // in the type of X
   uint16_t* dw16 = nullptr;
   int64_t lddw = 0;

@@ -5,12 +5,17 @@
 // The residual R = X - U_L V_L^T is recomputed on the fly from the factors
 // (2r multiply-adds per entry) and never stored.  The k-th largest |R| is
 // found by a most-significant-digit radix select on the IEEE bits of |R|
-// (monotone in |R|): a full pass histograms the top 12 bits; when the
-// entries at or above the bucket holding the k-th key fit in the candidate
-// buffer, a second pass collects them and the remaining digits are resolved
-// over the candidates only; otherwise further full passes histogram the
-// next digits.  Degenerate inputs (more exact ties at the threshold than the
-// candidate buffer holds) fall back to an index-ordered scan.
+// (monotone in |R|).  In the steady state one pass histograms and collects a
+// window of keys around the last threshold, in bins fine enough that the bin
+// holding the k-th key has few entries; the compaction writes everything
+// above that bin to S and lists the bin's entries, and one block takes the
+// rest of S from that list by (|R| descending, index ascending).  In the
+// first iteration, or when the window missed, a pass histograms the top 12
+// bits of every key and a second one collects from the bucket holding the
+// k-th key, with the fine histogram of that bucket (further passes first
+// resolve more digits when the bucket overflows the candidate buffer).
+// Degenerate inputs (more exact ties at the threshold than the candidate
+// buffer holds) fall back to an index-ordered scan.
 //
 // FP32 residuals are evaluated on the matrix cores in aligned 16 x 16 tiles
 // (res_tile); every FP32 consumer (selection passes, tie scan, tie values,
@@ -53,10 +58,50 @@ __device__ __forceinline__ int digit_bits(int pbits, int kbits) {
   return rem < kHistBits ? rem : kHistBits;
 }
 
-template <typename T, int RP>
+// FP64 pass: columns per thread of the wide form (sel_grid chooses it from
+// 1025 columns on).
+template <int RP>
 constexpr int sel_cpt() {
-  if (sizeof(T) == 8) return RP <= 8 ? 4 : (RP <= 16 ? 2 : 1);
-  return RP <= 24 ? 4 : 2;
+  return RP <= 8 ? 4 : (RP <= 16 ? 2 : 1);
+}
+
+template <typename T>
+struct PassKeys {
+  typename KeyBits<T>::key_t klo, kspan, kmin;
+  int shift;
+};
+
+// Bins of the carried window, which starts at a level-0 digit boundary klo two
+// digits below the last threshold: the first 4 digits in 256 bins each, then
+// one bin per digit, the last bin open to the top.  The threshold moves
+// little between iterations, so the k-th key falls in a fine bin; after a
+// larger rise its digit still holds a small part of the keys.  No finer above
+// than that: every block adds its nonzero bins to the global histogram (2
+// bins per digit there: pass 0 of 25 344 x 200 26 against 21 us).
+constexpr unsigned int kWinA = 4;   // digits of the fine zone
+constexpr int kWinABits = 8;        // log2 of its bins per digit
+constexpr unsigned int kWinB0 = kWinA << kWinABits;
+template <typename T>
+__device__ __forceinline__ unsigned int win_bin(typename KeyBits<T>::key_t rel) {
+  constexpr int S0 = KeyBits<T>::value - kHistBits0;
+  const unsigned int d = (unsigned int)(rel >> S0);
+  const unsigned int a = (unsigned int)(rel >> (S0 - kWinABits));
+  const unsigned int c = kWinB0 + (d - kWinA);
+  const unsigned int far = c < (unsigned int)kHistBins - 1u ? c : (unsigned int)kHistBins - 1u;
+  return d < kWinA ? a : far;
+}
+// Keys of bin `bin` relative to klo: [lo, hi].
+template <typename T>
+__device__ __forceinline__ void win_range(unsigned int bin, unsigned long long& lo,
+                                          unsigned long long& hi) {
+  constexpr int S0 = KeyBits<T>::value - kHistBits0;
+  if (bin < kWinB0) {
+    lo = (unsigned long long)bin << (S0 - kWinABits);
+    hi = lo + ((1ull << (S0 - kWinABits)) - 1ull);
+  } else {
+    lo = (unsigned long long)(kWinA + bin - kWinB0) << S0;
+    hi = bin == (unsigned int)kHistBins - 1u ? ~0ull : lo + ((1ull << S0) - 1ull);
+  }
 }
 
 // Candidate output of a collecting pass.  Wave w of block b owns the
@@ -87,15 +132,34 @@ struct SegSink {
   T* ring_v;
   T* ring_x;
   unsigned int flushed;     // wave-uniform: logical positions already stored
+  unsigned int* lh;         // the block's histogram (HM != 0)
+  PassKeys<T> pk;
 };
 
+// Histogram of appended entries, taken where they leave the ring: 64 entries
+// per step fill the wave, where the entries of one row step are few (2 % of
+// the lanes in pass 0 of 10000 x 10000: 166 us with the count in the row loop).
+// HM 0: none, 1: bins of the carried window, 2: the bucket's fine bins.
+template <typename T, int HM>
+__device__ __forceinline__ void seg_count_key(const SegSink<T>& s, T v) {
+  if constexpr (HM != 0) {
+    using K = typename KeyBits<T>::key_t;
+    const K rel = (K)((K)abs_key(v) - s.pk.klo);
+    if constexpr (HM == 1)
+      atomicAdd(&s.lh[win_bin<T>(rel)], 1u);
+    else if (rel < s.pk.kspan)
+      atomicAdd(&s.lh[rel >> s.pk.shift], 1u);
+  }
+}
+
 // Store the ring entry of logical position e (lanes with act).
-template <typename T>
+template <typename T, int HM>
 __device__ __forceinline__ void seg_emit(SegSink<T>& s, bool act, unsigned int e) {
   if (!act) return;
   const unsigned int slot = e & (kSegRing - 1);
   const int64_t i = s.ring_i[slot];
   const T v = s.ring_v[slot], x = s.ring_x[slot];
+  seg_count_key<T, HM>(s, v);
   long long pos;
   if (e < s.cap) {
     pos = s.base + e;
@@ -112,7 +176,7 @@ __device__ __forceinline__ void seg_emit(SegSink<T>& s, bool act, unsigned int e
 
 // Called by every lane of the wave (uniform control flow); lanes with
 // `take` append (idx, r, x).  Positions follow lane order within the wave.
-template <typename T>
+template <typename T, int HM>
 __device__ __forceinline__ void seg_push(SegSink<T>& s, bool take, int64_t idx, T r, T x) {
   const unsigned long long mask = __ballot(take);
   if (mask == 0ull) return;
@@ -136,11 +200,13 @@ __device__ __forceinline__ void seg_push(SegSink<T>& s, bool take, int64_t idx, 
       // atomic whose returned value would hold up the loads in flight)
       const unsigned int slot = e & (kSegRing - 1);
       const long long pos = s.base + e;
+      const T v = s.ring_v[slot];
       s.idx[pos] = s.ring_i[slot];
-      s.val[pos] = s.ring_v[slot];
+      s.val[pos] = v;
       s.xv[pos] = s.ring_x[slot];
+      seg_count_key<T, HM>(s, v);
     } else {
-      seg_emit(s, true, e);
+      seg_emit<T, HM>(s, true, e);
     }
     s.flushed = __builtin_amdgcn_readfirstlane(s.flushed + 64u);
     __builtin_amdgcn_wave_barrier();
@@ -148,11 +214,11 @@ __device__ __forceinline__ void seg_push(SegSink<T>& s, bool take, int64_t idx, 
 }
 
 // End of a collecting pass: store the entries still in the ring.
-template <typename T>
+template <typename T, int HM>
 __device__ __forceinline__ void seg_close(SegSink<T>& s) {
   __builtin_amdgcn_wave_barrier();
   const unsigned int l = threadIdx.x & 63;
-  seg_emit(s, l < s.fill - s.flushed, s.flushed + l);
+  seg_emit<T, HM>(s, l < s.fill - s.flushed, s.flushed + l);
   s.flushed = s.fill;
 }
 
@@ -187,20 +253,15 @@ __device__ __forceinline__ void seg_range(const SelPlan* plan, const unsigned in
 // registers, read from V_L^T with coalesced loads) and reads the U_L row
 // from LDS as a broadcast.  What a pass does with each residual key is set
 // by three switches, resolved outside the row loop:
-//   HIST  histogram (key >> shift) & mask over the keys in [klo, klo + kspan)
+//   HIST  histogram of the keys in [klo, klo + kspan): bins (key - klo) >>
+//         shift, or win_bin in the carried-window pass
 //   TAKE  append every key >= kmin (kmin >= 1, so zeros are never taken)
 //   S2    sum R^2 over all entries
 // Uses: level-0 histogram (HIST over every key, with S2, in pass 0), deeper
-// digits (HIST inside the bucket), collection (TAKE from the bucket low
-// key, or from the threshold key + 1 when ties are resolved by index), and
-// the carried-window pass 0 (HIST + TAKE + S2 over the window).
+// digits (HIST inside the bucket), collection (TAKE from the bucket low key
+// with HIST of the bucket, or TAKE from the threshold key + 1 when ties are
+// resolved by index), and the carried-window pass 0 (HIST + TAKE + S2).
 // ---------------------------------------------------------------------------
-template <typename T>
-struct PassKeys {
-  typename KeyBits<T>::key_t klo, kspan, kmin, mask;
-  int shift;
-};
-
 template <typename T, int RP, int CPT, bool HIST, bool TAKE, bool S2, bool FULL, bool VEC>
 __device__ __forceinline__ void sel_tile(const T* __restrict__ X, int64_t ldx, int64_t n,
                                          int64_t i0, int nr, int64_t j0, const T* us,
@@ -210,7 +271,7 @@ __device__ __forceinline__ void sel_tile(const T* __restrict__ X, int64_t ldx, i
   using K = typename KeyBits<T>::key_t;
   // rows whose X loads are in flight together (fewer when collecting, to
   // leave registers for the append)
-  constexpr int G = TAKE ? 2 : 4;
+  constexpr int G = TAKE && CPT > 1 ? 2 : 4;
   T xa[G][CPT], xb[G][CPT];
   auto load_group = [&](T (&xx)[G][CPT], int gi) {
 #pragma unroll
@@ -253,10 +314,12 @@ __device__ __forceinline__ void sel_tile(const T* __restrict__ X, int64_t ldx, i
         if constexpr (S2) {
           if (ok) s2 += (double)r * (double)r;
         }
-        if constexpr (HIST) {
-          if (ok && (K)(key - pk.klo) < pk.kspan) atomicAdd(&lh[(key >> pk.shift) & pk.mask], 1u);
+        if constexpr (HIST && !TAKE) {
+          if (ok && (K)(key - pk.klo) < pk.kspan) atomicAdd(&lh[(K)(key - pk.klo) >> pk.shift], 1u);
         }
-        if constexpr (TAKE) seg_push(sink, ok && key >= pk.kmin, (i0 + ii) * n + j0 + t, r, xa[a][t]);
+        if constexpr (TAKE)
+          seg_push<T, HIST ? (S2 ? 1 : 2) : 0>(sink, ok && key >= pk.kmin,
+                                               (i0 + ii) * n + j0 + t, r, xa[a][t]);
       }
     }
 #pragma unroll
@@ -276,9 +339,7 @@ __device__ __forceinline__ void sel_tile(const T* __restrict__ X, int64_t ldx, i
 // (all WT tiles issued before the first is used).  The candidates a wave
 // appends lie in one 16 WT-column strip, in band order (local for the later
 // scattered updates of D).  Bands wholly inside the matrix (and a 16-byte
-// aligned X) take a path without bounds checks; in the carried-window pass
-// (HIST and TAKE together, whose key windows coincide) one comparison serves
-// both.
+// aligned X) take a path without bounds checks.
 template <int RP> struct ResStrip {
   // four tiles per wave keep the pass within 128 registers (four waves per
   // SIMD at four blocks per CU)
@@ -335,18 +396,12 @@ __device__ __forceinline__ void sel_band_mfma(const float* __restrict__ X, int64
         if constexpr (S2) {
           if (ok) t2 = fma((double)r, (double)r, t2);
         }
-        if constexpr (HIST && TAKE) {
-          const bool c = ok && key >= pk.kmin;
-          if (c) atomicAdd(&lh[(key >> pk.shift) & pk.mask], 1u);
-          seg_push(sink, c, row * n + col0 + v, r, x[t][v]);
-        } else {
-          if constexpr (HIST) {
-            if (ok && (K)(key - pk.klo) < pk.kspan)
-              atomicAdd(&lh[(key >> pk.shift) & pk.mask], 1u);
-          }
-          if constexpr (TAKE)
-            seg_push(sink, ok && key >= pk.kmin, row * n + col0 + v, r, x[t][v]);
+        if constexpr (HIST && !TAKE) {
+          if (ok && (K)(key - pk.klo) < pk.kspan) atomicAdd(&lh[(key - pk.klo) >> pk.shift], 1u);
         }
+        if constexpr (TAKE)
+          seg_push<float, HIST ? (S2 ? 1 : 2) : 0>(sink, ok && key >= pk.kmin,
+                                                   row * n + col0 + v, r, x[t][v]);
       }
       if constexpr (S2) s2 += t2;
     }
@@ -395,30 +450,29 @@ __device__ __forceinline__ void sel_pass_mfma(const float* __restrict__ X, int64
   }
 }
 
-template <typename T, int RP, bool HIST, bool TAKE, bool S2>
+// CPT: columns per thread and rpt: rows per tile of the FP64 pass.
+template <typename T, int RP, int CPT, bool HIST, bool TAKE, bool S2>
 __device__ __forceinline__ void sel_pass_body(const T* __restrict__ X, int64_t ldx,
                                               const T* __restrict__ UL,
                                               const T* __restrict__ VLt, int64_t ldv,
                                               int64_t m, int64_t n, unsigned int* lh, T* us,
                                               const PassKeys<T>& pk, SegSink<T>& sink,
-                                              bool vec_ok, double& s2) {
+                                              bool vec_ok, int rpt, double& s2) {
   if constexpr (sizeof(T) == 4) {
     sel_pass_mfma<RP, HIST, TAKE, S2>(X, ldx, UL, VLt, ldv, m, n, lh, pk, sink, s2, vec_ok);
   } else {
-  constexpr int CPT = sel_cpt<T, RP>();
   constexpr int TW = 256 * CPT;
   const int tid = threadIdx.x;
   const int64_t ctiles = (n + TW - 1) / TW;
-  const int64_t rtiles = (m + kRowsPerTile - 1) / kRowsPerTile;
+  const int64_t rtiles = (m + rpt - 1) / rpt;
   const int64_t ntiles = ctiles * rtiles;
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int64_t ct = tile % ctiles, rt = tile / ctiles;
     const int64_t j0 = ct * TW + (int64_t)tid * CPT;
-    const int64_t i0 = rt * kRowsPerTile;
-    const int nr = (m - i0) < kRowsPerTile ? (int)(m - i0) : kRowsPerTile;
+    const int64_t i0 = rt * rpt;
+    const int nr = (m - i0) < rpt ? (int)(m - i0) : rpt;
     __syncthreads();
-    for (int e = tid; e < kRowsPerTile * RP; e += 256)
-      us[e] = (e < nr * RP) ? UL[i0 * RP + e] : T(0);
+    for (int e = tid; e < nr * RP; e += 256) us[e] = UL[i0 * RP + e];
     __syncthreads();
     // V_L^T (RP x ldv): lanes read consecutive columns of each row
     T v[CPT][RP];
@@ -450,7 +504,6 @@ __device__ __forceinline__ PassKeys<T> keys_level0() {
   pk.kspan = (K)(K(1) << KB);
   pk.kmin = 1;
   pk.shift = KB - kHistBits0;
-  pk.mask = (K)(kHistBins - 1);
   return pk;
 }
 
@@ -472,18 +525,18 @@ __device__ __forceinline__ PassKeys<T> keys_level0() {
   __shared__ T ring_v[kSelWaves * kSegRing], ring_x[kSelWaves * kSegRing];    \
   SegSink<T> sink{cand_idx, cand_val, cand_x, (long long)seg * seg_cap, seg_cap, 0u, \
                   (unsigned long long*)&plan->ncand, ccap, ring_i + wave * kSegRing, \
-                  ring_v + wave * kSegRing, ring_x + wave * kSegRing, 0u};
+                  ring_v + wave * kSegRing, ring_x + wave * kSegRing, 0u, lh, {}};
 
 // Closing of a collecting pass: publish the wave's segment fill.
-#define GODEC_SEL_SEG_CLOSE                                                   \
-  seg_close(sink);                                                            \
+#define GODEC_SEL_SEG_CLOSE(HM)                                               \
+  seg_close<T, HM>(sink);                                                     \
   if (lane == 0) seg_count[seg] = sink.fill < seg_cap ? sink.fill : seg_cap;
 
 // Pass 0: the carried-window pass (steady state) or the full level-0
 // histogram (first iteration); both also sum R^2.  With r16, the blocks
 // first restore bf16(X) at the previous S's entries of that copy (scattered
 // 2-byte stores that overlap the pass).
-template <typename T, int RP>
+template <typename T, int RP, int CPT>
 __global__ __launch_bounds__(256) void k_sel_pass0(const T* __restrict__ X, int64_t ldx,
                                                    const T* __restrict__ UL,
                                                    const T* __restrict__ VLt, int64_t ldv,
@@ -494,7 +547,7 @@ __global__ __launch_bounds__(256) void k_sel_pass0(const T* __restrict__ X, int6
                                                    T* __restrict__ cand_val,
                                                    T* __restrict__ cand_x,
                                                    unsigned int* __restrict__ seg_count,
-                                                   double* __restrict__ s2part,
+                                                   double* __restrict__ s2part, int rpt,
                                                    uint16_t* __restrict__ r16, int64_t ldd16,
                                                    const int64_t* __restrict__ ridx,
                                                    const float* __restrict__ rx,
@@ -529,8 +582,8 @@ __global__ __launch_bounds__(256) void k_sel_pass0(const T* __restrict__ X, int6
     const bool vec_ok0 = (ldx % 4 == 0) && ((((uintptr_t)X) & 15) == 0);
     PassKeys<T> pk0 = keys_level0<T>();
     double s20 = 0.0;
-    sel_pass_body<T, RP, false, false, true>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk0, sink,
-                                             vec_ok0, s20);
+    sel_pass_body<T, RP, CPT, false, false, true>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk0, sink,
+                                                  vec_ok0, rpt, s20);
     s20 = wave_sum(s20);
     if (lane == 0) red[wave] = s20;
     __syncthreads();
@@ -541,23 +594,22 @@ __global__ __launch_bounds__(256) void k_sel_pass0(const T* __restrict__ X, int6
   PassKeys<T> pk = keys_level0<T>();
   if (carry) {
     // histogram and collect the window [dlo-th level-0 digit, top)
-    const K lo = (K)plan->carry_dlo << (KB - kHistBits0);
-    pk.klo = lo > 0 ? lo : K(1);
-    pk.kspan = (K)((K(1) << KB) - pk.klo);
-    pk.kmin = pk.klo;
+    pk.klo = (K)plan->carry_dlo << (KB - kHistBits0);
+    pk.kmin = pk.klo > 0 ? pk.klo : K(1);
   }
   for (int e = tid; e < kHistBins; e += 256) lh[e] = 0u;
   const bool vec_ok = (ldx % 4 == 0) && ((((uintptr_t)X) & 15) == 0);
+  sink.pk = pk;
   __syncthreads();
   double s2 = 0.0;
   if (carry)
-    sel_pass_body<T, RP, true, true, true>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
-                                           vec_ok, s2);
+    sel_pass_body<T, RP, CPT, true, true, true>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
+                                                vec_ok, rpt, s2);
   else
-    sel_pass_body<T, RP, true, false, true>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
-                                            vec_ok, s2);
+    sel_pass_body<T, RP, CPT, true, false, true>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
+                                                 vec_ok, rpt, s2);
+  if (carry) { GODEC_SEL_SEG_CLOSE(1) }
   __syncthreads();
-  if (carry) { GODEC_SEL_SEG_CLOSE }
   unsigned long long* hrep = hist + (int64_t)(blockIdx.x % kHistRep) * kHistBins;
   for (int e = tid; e < kHistBins; e += 256)
     if (lh[e]) atomicAdd(&hrep[e], (unsigned long long)lh[e]);
@@ -568,21 +620,24 @@ __global__ __launch_bounds__(256) void k_sel_pass0(const T* __restrict__ X, int6
   if (tid == 0) s2part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-// Later passes (first iteration and fall-backs): the level-0 histogram
-// again (after a missed carry), deeper digits, collection from the bucket,
-// or collection above a resolved threshold whose ties overflow the buffer.
-// Advance the plan.  One block.  stage 0 follows a full-data pass (which
-// histogrammed in SEL_HIST or collected in SEL_COLLECT); stage 1 follows a
-// candidate histogram (SEL_REFINE).  In any other combination the preceding
-// kernel did nothing and neither does this one.  The digit holding the
-// k_rem-th largest key is found with a block-wide suffix scan.
+// Bits of the fine histogram of a bucket whose keys share pbits high bits.
+__device__ __forceinline__ int fine_bits(int pbits, int kbits) {
+  const int rem = kbits - pbits;
+  return rem < kHistBits0 ? rem : kHistBits0;
+}
+
+// Advance the plan after a full-data pass (which histogrammed in SEL_HIST, or
+// collected in SEL_COLLECT or SEL_TIES); in any other mode the pass did
+// nothing and neither does this.  The bin holding the k_rem-th largest key is
+// found with a block-wide suffix scan.  At SEL_FINAL, [blo, bhi] are the keys
+// of the last bin: every candidate above it belongs to S, and k_rem of those
+// inside it.
 //
-// sel_plan_core runs either as the kernel k_sel_plan (COH = false) or in
-// the last block to finish the pass or candidate histogram it follows
-// (COH = true): then the histogram, which the pass's blocks added to with
-// device-scope atomics, and the spill counter are read with device-scope
-// loads, and the bins are counted in 32 bits in the pass's own LDS (the
-// host uses this form only when m n < 2^32).
+// Runs either as the kernel k_sel_plan (COH = false) or in the last block to
+// finish the pass it follows (COH = true): then the histogram, which the
+// pass's blocks added to with device-scope atomics, and the spill counter are
+// read with device-scope loads, and the bins are counted in 32 bits in the
+// pass's own LDS (the host uses this form only when m n < 2^32).
 template <bool COH>
 __device__ __forceinline__ unsigned long long hist_load(const unsigned long long* p) {
   if constexpr (COH)
@@ -598,174 +653,199 @@ __device__ __forceinline__ long long ncand_load(const SelPlan* plan) {
     return plan->ncand;
 }
 
-template <typename T, typename HT, bool COH>
+// Result of the bin search (LDS): the bin, the keys above it and in it.
+struct BinHit {
+  unsigned long long cum, cnt, total;
+  int bin;
+};
+
+template <typename T, typename HT, bool COH, int NT>
 __device__ void sel_plan_core(SelPlan* __restrict__ plan, unsigned long long* __restrict__ hist,
-                              int stage, HT* h, unsigned long long* part, int* sel_t) {
+                              HT* h, unsigned long long* part, BinHit* hit) {
   constexpr int KB = KeyBits<T>::value;
-  const int tid = threadIdx.x;
+  constexpr int PER = kHistBins / NT;
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int mode = plan->mode;
-  if (stage == 0 && (mode == SEL_COLLECT || mode == SEL_TIES)) {
+  const int pbits = plan->pbits;
+  if (mode == SEL_TIES || (mode == SEL_COLLECT && pbits == KB)) {
     if (tid == 0) {
       if (ncand_load<COH>(plan) > plan->cap) plan->overflow = 1;
-      if (mode == SEL_TIES) plan->mode = SEL_TSCAN;
-      else plan->mode = (plan->pbits == KB) ? SEL_FINAL : SEL_REFINE;
+      if (mode == SEL_TIES) {
+        plan->mode = SEL_TSCAN;
+      } else {
+        plan->blo = plan->bhi = plan->prefix;
+        plan->mode = SEL_FINAL;
+      }
     }
     return;
   }
-  if (!((stage == 0 && mode == SEL_HIST) || (stage == 1 && mode == SEL_REFINE))) return;
-  const int pbits = plan->pbits;
-  const int dbits = digit_bits(pbits, KB);
-  const int bins = 1 << dbits;
-  const int per = (bins + 255) / 256;
-  // sum the replicas in replica order (and clear them for the next
-  // histogram); every load of a batch is issued before the first add: all
-  // of the thread's bins at once in the kernel, UB bins at a time in the
-  // last block of a pass (whose register budget is the pass's)
-  constexpr int MAXPER = (kHistBins + 255) / 256;
-  constexpr int UB = COH ? 2 : MAXPER;
-  for (int u0 = 0; u0 < MAXPER; u0 += UB) {
-    unsigned long long v[UB][kHistRep];
+  if (mode != SEL_HIST && mode != SEL_COLLECT) return;
+  const bool window = mode == SEL_HIST && pbits == 0 && plan->carry_used == 1;
+  const int dbits = mode == SEL_COLLECT ? fine_bits(pbits, KB) : digit_bits(pbits, KB);
+  const int bins = window ? kHistBins : 1 << dbits;
+  // thread t owns PER bins, top bins first; the replicas are summed (and
+  // cleared for the next histogram) with every load issued first
+  unsigned long long v[PER][kHistRep];
 #pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      const int e = tid + 256 * (u0 + u);
+  for (int u = 0; u < PER; ++u) {
+    const int e = kHistBins - 1 - (u * NT + tid);
 #pragma unroll
-      for (int r = 0; r < kHistRep; ++r)
-        v[u][r] = e < bins ? hist_load<COH>(hist + r * kHistBins + e) : 0ull;
+    for (int r = 0; r < kHistRep; ++r)
+      v[u][r] = e < bins ? hist_load<COH>(hist + r * kHistBins + e) : 0ull;
+  }
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int e = kHistBins - 1 - (u * NT + tid);
+    unsigned long long acc = 0;
+#pragma unroll
+    for (int r = 0; r < kHistRep; ++r) {
+      acc += v[u][r];
+      if (e < bins) hist[r * kHistBins + e] = 0ull;
     }
+    h[e] = (HT)acc;
+  }
+  if (tid == 0) hit->bin = -1;
+  __syncthreads();
+  // inclusive scan over threads, each with PER adjacent bins
+  const int top = kHistBins - 1 - tid * PER;
+  unsigned long long own = 0;
 #pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      const int e = tid + 256 * (u0 + u);
-      if (e < bins) {
-        unsigned long long acc = 0;
+  for (int u = 0; u < PER; ++u) own += h[top - u];
+  unsigned long long inc = own;
 #pragma unroll
-        for (int r = 0; r < kHistRep; ++r) {
-          acc += v[u][r];
-          hist[r * kHistBins + e] = 0ull;
-        }
-        h[e] = (HT)acc;
+  for (int off = 1; off < 64; off <<= 1) {
+    const unsigned long long o = __shfl_up(inc, off, 64);
+    if (lane >= off) inc += o;
+  }
+  if (lane == 63) part[wave] = inc;
+  __syncthreads();
+  unsigned long long base = 0, total = 0;
+  for (int w = 0; w < NW; ++w) {
+    if (w < wave) base += part[w];
+    total += part[w];
+  }
+  inc += base;
+  const unsigned long long k_rem = (unsigned long long)plan->k_rem;
+  if (inc - own < k_rem && inc >= k_rem) {   // one thread at most
+    unsigned long long cum = inc - own;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const unsigned long long c = h[top - u];
+      if (hit->bin < 0 && cum + c >= k_rem) {
+        hit->bin = top - u;
+        hit->cum = cum;
+        hit->cnt = c;
       }
+      cum += c;
     }
   }
+  if (tid == 0) hit->total = total;
   __syncthreads();
-  // thread t owns digits [bins - (t+1)*per, bins - t*per): top digits first
-  unsigned long long s = 0;
-  for (int u = 0; u < per; ++u) {
-    const int d = bins - 1 - (tid * per + u);
-    if (d >= 0) s += h[d];
-  }
-  part[tid] = s;
-  if (tid == 0) *sel_t = -1;
-  __syncthreads();
-  // inclusive scan of part[] (Hillis-Steele)
-  for (int off = 1; off < 256; off <<= 1) {
-    const unsigned long long add = tid >= off ? part[tid - off] : 0ull;
-    __syncthreads();
-    part[tid] += add;
-    __syncthreads();
-  }
-  const long long k_rem = plan->k_rem;
-  const unsigned long long before = tid > 0 ? part[tid - 1] : 0ull;
-  if (before < (unsigned long long)k_rem && part[tid] >= (unsigned long long)k_rem) *sel_t = tid;
-  __syncthreads();
-  if (tid == 0) {
-    int dsel = -1;
-    unsigned long long cum = 0;
-    if (*sel_t >= 0) {
-      cum = *sel_t > 0 ? part[*sel_t - 1] : 0ull;
-      for (int u = 0; u < per; ++u) {
-        const int d = bins - 1 - (*sel_t * per + u);
-        if (d < 0) break;
-        if (cum + h[d] >= (unsigned long long)k_rem) { dsel = d; break; }
-        cum += h[d];
-      }
-    }
-    if (stage == 0 && pbits == 0 && plan->carry_used == 1) {
-      // pass 0 histogrammed and collected only digits >= carry_dlo: accept
-      // when the k-th key lies there and every candidate was kept;
-      // otherwise fall back to the full level-0 histogram in the next pass
-      if (dsel < 0 || ncand_load<COH>(plan) > plan->cap) {
-        plan->carry_used = 0;
-        plan->ncand = 0;
-        plan->slow = 1;
-        plan->mode = SEL_HIST;   // prefix 0, pbits 0, k_rem = k unchanged
-        return;
-      }
-      plan->carry_used = 2;
-      plan->count_above += (long long)cum;
-      plan->k_rem = k_rem - (long long)cum;
-      plan->prefix = (unsigned long long)dsel;
-      plan->pbits = dbits;
-      plan->bucket_count = (long long)h[dsel];
-      plan->mode = (plan->pbits == KB) ? SEL_FINAL : SEL_REFINE;
+  if (tid != 0) return;
+  int dsel = hit->bin;
+  unsigned long long cum = hit->cum, cnt = hit->cnt;
+  if (window) {
+    // the pass histogrammed and collected only digits >= carry_dlo: accept
+    // when the k-th key lies there, every candidate was kept (there is room
+    // for 2 cap of them) and the bin's list has room; otherwise fall back to
+    // the full level-0 histogram in the next pass
+    if (dsel < 0 || ncand_load<COH>(plan) > plan->cap || (long long)cnt > plan->cap) {
+      plan->carry_used = 0;
+      plan->ncand = 0;
+      plan->slow = 1;   // prefix 0, pbits 0, k_rem = k unchanged
       return;
     }
-    if (dsel < 0) {
-      // fewer keys than k_rem in the bucket: only when the remaining keys
-      // are zeros (excluded from the candidates); settle on digit 0
-      dsel = 0;
-      cum = part[255] - h[0];
-    }
-    plan->count_above += (long long)cum;
-    plan->k_rem = k_rem - (long long)cum;
-    plan->prefix = (plan->prefix << dbits) | (unsigned long long)dsel;
-    plan->pbits = pbits + dbits;
-    plan->bucket_count = (long long)h[dsel];
-    int next;
-    if (mode == SEL_HIST) {
-      if (plan->count_above + plan->bucket_count <= plan->cap) {
-        next = SEL_COLLECT;
-        plan->ncand = 0;
-      } else if (plan->pbits == KB) {
-        next = SEL_TIES;
-        plan->ncand = 0;
-        plan->slow = 1;
-      } else {
-        next = SEL_HIST;
-        plan->slow = 1;
-      }
-    } else {
-      next = (plan->pbits == KB) ? SEL_FINAL : SEL_REFINE;
-    }
-    plan->mode = next;
+    const unsigned long long klo = (unsigned long long)plan->carry_dlo << (KB - kHistBits0);
+    unsigned long long lo, hi;
+    win_range<T>((unsigned int)dsel, lo, hi);
+    plan->carry_used = 2;
+    plan->blo = klo + lo;
+    plan->bhi = hi == ~0ull ? hi : klo + hi;
+    plan->count_above = (long long)cum;
+    plan->k_rem = (long long)(k_rem - cum);
+    plan->bucket_count = (long long)cnt;
+    plan->mode = SEL_FINAL;
+    return;
   }
+  if (dsel < 0) {
+    // fewer keys than k_rem: only when the remaining keys are zeros (excluded
+    // from the candidates); settle on bin 0
+    dsel = 0;
+    cnt = h[0];
+    cum = hit->total - cnt;
+  }
+  plan->count_above += (long long)cum;
+  plan->k_rem = (long long)(k_rem - cum);
+  plan->bucket_count = (long long)cnt;
+  if (mode == SEL_COLLECT) {
+    const int sh = KB - pbits - dbits;
+    plan->blo = (((plan->prefix << dbits) | (unsigned long long)dsel) << sh);
+    plan->bhi = plan->blo + ((1ull << sh) - 1ull);
+    if (ncand_load<COH>(plan) > plan->cap) plan->overflow = 1;
+    plan->mode = SEL_FINAL;
+    return;
+  }
+  plan->prefix = (plan->prefix << dbits) | (unsigned long long)dsel;
+  plan->pbits = pbits + dbits;
+  int next = SEL_HIST;
+  if (plan->count_above + plan->bucket_count <= plan->cap) {
+    next = SEL_COLLECT;
+    plan->ncand = 0;
+  } else if (plan->pbits == KB) {
+    next = SEL_TIES;
+    plan->ncand = 0;
+    plan->slow = 1;
+  } else {
+    plan->slow = 1;
+  }
+  plan->mode = next;
 }
 
+// One block.  Bound: latency (the histogram's replicas arrive in one round
+// trip, then a wave scan): 1024 threads and two replicas.  With 256 threads
+// and eight replicas (256 KB through one CU) it took 9-11 us.
+constexpr int kPlanThreads = 1024;
 template <typename T>
-__global__ __launch_bounds__(256) void k_sel_plan(SelPlan* __restrict__ plan,
-                                                  unsigned long long* __restrict__ hist,
-                                                  int stage, const double* __restrict__ s2part,
-                                                  int ns2) {
+__global__ __launch_bounds__(kPlanThreads) void k_sel_plan(SelPlan* __restrict__ plan,
+                                                           unsigned long long* __restrict__ hist,
+                                                           const double* __restrict__ s2part,
+                                                           int ns2) {
   __shared__ unsigned long long h[kHistBins];
-  __shared__ unsigned long long part[256];
-  __shared__ int sel_t;
-  __shared__ double red[8];
+  __shared__ unsigned long long part[kPlanThreads / 64];
+  __shared__ BinHit hit;
+  __shared__ double red[kPlanThreads / 64 + 1];
   if (s2part) {
-    // right after pass 0: its per-block sums of R^2, added in block order
+    // right after pass 0: its per-block sums of R^2, added in a fixed order
     const double s = block_sum_fixed(s2part, ns2, red);
     if (threadIdx.x == 0) plan->sum_r2 = s;
   }
-  sel_plan_core<T, unsigned long long, false>(plan, hist, stage, h, part, &sel_t);
+  sel_plan_core<T, unsigned long long, false, kPlanThreads>(plan, hist, h, part, &hit);
 }
 
-// End of a pass or candidate histogram that plans in its last block: every
-// block waits for its histogram atomics and stores to complete and signals
-// arrival; the last one resets the counter and advances the plan in the
-// LDS the pass no longer needs (h: kHistBins 32-bit bins, part: 256 u64).
+// End of a pass that plans in its last block: every block waits for its
+// histogram atomics and stores to complete and signals arrival; the last one
+// resets the counter and advances the plan in the LDS the pass no longer
+// needs (h: kHistBins 32-bit bins, scratch: 8 u64).
 template <typename T>
 __device__ __forceinline__ void plan_in_last_block(SelPlan* __restrict__ plan,
                                                    unsigned long long* __restrict__ hist,
-                                                   int stage, unsigned int* h,
-                                                   unsigned long long* part, int* flags) {
+                                                   unsigned int* h, unsigned long long* scratch,
+                                                   int* flag, BinHit* hit) {
   stores_done();
   __syncthreads();
-  if (threadIdx.x == 0) flags[0] = arrive(&plan->arrivals) == gridDim.x - 1u;
+  if (threadIdx.x == 0) *flag = arrive(&plan->arrivals) == gridDim.x - 1u;
   __syncthreads();
-  if (!flags[0]) return;
+  if (!*flag) return;
   if (threadIdx.x == 0) publish_u32(&plan->arrivals, 0u);
-  sel_plan_core<T, unsigned int, true>(plan, hist, stage, h, part, flags + 1);
+  sel_plan_core<T, unsigned int, true, 256>(plan, hist, h, scratch, hit);
 }
 
-template <typename T, int RP>
+// Later passes (first iteration and fall-backs): the level-0 histogram again
+// (after a missed window), deeper digits, collection from the bucket with its
+// fine histogram, or collection above a resolved threshold whose ties
+// overflow the buffer.
+template <typename T, int RP, int CPT>
 __global__ __launch_bounds__(256) void k_sel_passN(const T* __restrict__ X, int64_t ldx,
                                                    const T* __restrict__ UL,
                                                    const T* __restrict__ VLt, int64_t ldv,
@@ -775,87 +855,64 @@ __global__ __launch_bounds__(256) void k_sel_passN(const T* __restrict__ X, int6
                                                    int64_t* __restrict__ cand_idx,
                                                    T* __restrict__ cand_val,
                                                    T* __restrict__ cand_x,
-                                                   unsigned int* __restrict__ seg_count,
+                                                   unsigned int* __restrict__ seg_count, int rpt,
                                                    int fuse_plan) {
   const int mode = plan->mode;
   if (mode != SEL_HIST && mode != SEL_COLLECT && mode != SEL_TIES) return;
   GODEC_SEL_SHARED
-  __shared__ int pl_flags[2];
+  __shared__ int pl_flag;
+  __shared__ BinHit hit;
   const unsigned long long prefix = plan->prefix;
   const int pbits = plan->pbits;
-  const int dbits = digit_bits(pbits, KB);
-  const bool do_hist = (mode == SEL_HIST);
+  const bool collect = mode == SEL_COLLECT;
+  const int dbits = collect ? fine_bits(pbits, KB) : digit_bits(pbits, KB);
   PassKeys<T> pk = keys_level0<T>();
   if (pbits > 0) {
     pk.klo = (K)(prefix << (KB - pbits));
     pk.kspan = (K)(K(1) << (KB - pbits));
     pk.shift = KB - pbits - dbits;
-    pk.mask = (K)((K(1) << dbits) - 1);
     pk.kmin = pk.klo > 0 ? pk.klo : K(1);
   }
   if (mode == SEL_TIES) pk.kmin = (K)prefix + 1;   // prefix is the full threshold key
-  if (do_hist)
+  const bool hist_it = mode == SEL_HIST || (collect && dbits > 0);
+  if (hist_it)
     for (int e = tid; e < kHistBins; e += 256) lh[e] = 0u;
   const bool vec_ok = (ldx % 4 == 0) && ((((uintptr_t)X) & 15) == 0);
+  sink.pk = pk;
   __syncthreads();
   double s2 = 0.0;
-  if (do_hist)
-    sel_pass_body<T, RP, true, false, false>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
-                                             vec_ok, s2);
+  if (mode == SEL_HIST)
+    sel_pass_body<T, RP, CPT, true, false, false>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
+                                                  vec_ok, rpt, s2);
+  else if (hist_it)
+    sel_pass_body<T, RP, CPT, true, true, false>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
+                                                 vec_ok, rpt, s2);
   else
-    sel_pass_body<T, RP, false, true, false>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
-                                             vec_ok, s2);
+    sel_pass_body<T, RP, CPT, false, true, false>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
+                                                  vec_ok, rpt, s2);
+  if (collect && hist_it) { GODEC_SEL_SEG_CLOSE(2) }
+  else if (mode != SEL_HIST) { GODEC_SEL_SEG_CLOSE(0) }
   __syncthreads();
-  if (!do_hist) { GODEC_SEL_SEG_CLOSE }
-  if (do_hist) {
+  if (hist_it) {
     const int bins = 1 << dbits;
     unsigned long long* hrep = hist + (int64_t)(blockIdx.x % kHistRep) * kHistBins;
     for (int e = tid; e < bins; e += 256)
       if (lh[e]) atomicAdd(&hrep[e], (unsigned long long)lh[e]);
   }
-  // the plan step in the last block (its LDS: lh for the bins, the index
-  // ring for the scan)
+  // the plan step in the last block (its LDS: lh for the bins, the index ring
+  // for the scan)
   if (fuse_plan)
-    plan_in_last_block<T>(plan, hist, 0, lh, reinterpret_cast<unsigned long long*>(ring_i),
-                          pl_flags);
+    plan_in_last_block<T>(plan, hist, lh, reinterpret_cast<unsigned long long*>(ring_i),
+                          &pl_flag, &hit);
 }
 
-// Histogram of the next digit over the candidates inside the bucket.
-template <typename T>
-__global__ __launch_bounds__(256) void k_cand_hist(SelPlan* __restrict__ plan,
-                                                   const T* __restrict__ cand_val,
-                                                   const unsigned int* __restrict__ seg_count,
-                                                   unsigned long long* __restrict__ hist) {
-  constexpr int KB = KeyBits<T>::value;
-  __shared__ unsigned int lh[kHistBins];
-  if (plan->mode != SEL_REFINE) return;
-  const unsigned long long prefix = plan->prefix;
-  const int pbits = plan->pbits;
-  const int dbits = digit_bits(pbits, KB);
-  for (int e = threadIdx.x; e < (1 << dbits); e += 256) lh[e] = 0u;
-  __syncthreads();
-  const int ntot = seg_total(plan);
-  for (int sg = blockIdx.x; sg < ntot; sg += gridDim.x) {
-    long long base, cnt;
-    seg_range(plan, seg_count, sg, base, cnt);
-    for (long long c = base + threadIdx.x; c < base + cnt; c += 256) {
-      const unsigned long long key = abs_key(cand_val[c]);
-      if ((key >> (KB - pbits)) == prefix)
-        atomicAdd(&lh[(key >> (KB - pbits - dbits)) & ((1ull << dbits) - 1)], 1u);
-    }
-  }
-  __syncthreads();
-  unsigned long long* hrep = hist + (int64_t)(blockIdx.x % kHistRep) * kHistBins;
-  for (int e = threadIdx.x; e < (1 << dbits); e += 256)
-    if (lh[e]) atomicAdd(&hrep[e], (unsigned long long)lh[e]);
-}
-
-// FINAL: write S from the candidates.  Entries above the threshold key go
-// straight to S; entries equal to it go to the tie list.  Wave w of block b
-// takes the candidate segments 4 b + w, 4 b + w + 4 gridDim.x, ...: the
-// waves count their entries, the block reserves its output range with one
+// FINAL: write S from the candidates.  Entries above the last bin go straight
+// to S; the positions of those in it go to the list of k_sel_final.  Wave w of
+// block b takes the candidate segments 4 b + w, 4 b + w + 4 gridDim.x, ...:
+// the waves count their entries, the block reserves its output range with one
 // atomic per list, and each wave then writes its entries in order (ballots
-// only, no block barrier), 256 candidates per step.
+// only, no block barrier), 256 candidates per step with every load of the
+// step issued first.
 template <typename T>
 __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
                                                      const int64_t* __restrict__ cand_idx,
@@ -865,7 +922,7 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
                                                      int64_t* __restrict__ s_idx,
                                                      T* __restrict__ s_val,
                                                      T* __restrict__ s_x,
-                                                     int64_t* __restrict__ tie_idx,
+                                                     int64_t* __restrict__ list,
                                                      unsigned long long* __restrict__ counters,
                                                      double* __restrict__ s2sel,
                                                      T* __restrict__ dwn,
@@ -876,9 +933,8 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
   __shared__ unsigned long long base_a, base_t;
   if (plan->mode != SEL_FINAL) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const unsigned long long tkey = plan->prefix;
-  const unsigned long long kcap = (unsigned long long)(plan->count_above + plan->k_rem);
-  const long long dkeep = plan->count_above;
+  const unsigned long long blo = plan->blo, bhi = plan->bhi;
+  const unsigned long long acap = (unsigned long long)plan->count_above;
   const double rcols = 1.0 / (double)(ncols > 0 ? ncols : 1);
   const unsigned long long tcap = (unsigned long long)plan->cap;
   const unsigned long long below = (1ull << lane) - 1ull;
@@ -890,10 +946,20 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
   for (int sg = w0; sg < ntot; sg += wstride) {
     long long c0, cnt;
     seg_range(plan, seg_count, sg, c0, cnt);
-    for (long long c = c0 + lane; c < c0 + cnt; c += 64) {
-      const unsigned long long key = abs_key(cand_val[c]);
-      na += key > tkey;
-      nt += (key == tkey && tkey > 0);
+    for (long long cb = c0; cb < c0 + cnt; cb += 256) {
+      T v[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        const long long c = cb + 64 * h + lane;
+        v[h] = c < c0 + cnt ? cand_val[c] : T(0);
+      }
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        const long long c = cb + 64 * h + lane;
+        const unsigned long long key = abs_key(v[h]);
+        na += c < c0 + cnt && key > bhi;
+        nt += c < c0 + cnt && key >= blo && key <= bhi;
+      }
     }
   }
   na = wave_sum(na);
@@ -909,51 +975,51 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
   __syncthreads();
   unsigned long long ba = base_a, bt = base_t;
   for (int w = 0; w < wave; ++w) { ba += wa[w]; bt += wt[w]; }
-  // phase 2: each wave writes its segments in order, four loads in flight
+  // phase 2: each wave writes its segments in order
   double s2 = 0.0;
   for (int sg = w0; sg < ntot; sg += wstride) {
     long long c0, cnt;
     seg_range(plan, seg_count, sg, c0, cnt);
     const long long c1 = c0 + cnt;
     for (long long cb = c0; cb < c1; cb += 256) {
-      T v[4];
+      T v[4], xv[4];
+      int64_t id[4];
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
         const long long c = cb + 64 * h + lane;
-        v[h] = c < c1 ? cand_val[c] : T(0);
+        const long long cc = c < c1 ? c : c1 - 1;
+        v[h] = cand_val[cc];
+        id[h] = cand_idx[cc];
+        xv[h] = cand_x[cc];
       }
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
         const long long c = cb + 64 * h + lane;
         const bool valid = c < c1;
         const unsigned long long key = abs_key(v[h]);
-        const bool above = valid && key > tkey;
-        const bool tie = valid && key == tkey && tkey > 0;
-        const unsigned long long ma = __ballot(above), mt = __ballot(tie);
+        const bool above = valid && key > bhi;
+        const bool in = valid && key >= blo && key <= bhi;
+        const unsigned long long ma = __ballot(above), mt = __ballot(in);
         if (above) {
           const unsigned long long pos = ba + __popcll(ma & below);
-          if (pos < kcap) {
-            const int64_t id = cand_idx[c];
-            const T xv = cand_x[c];
-            s_idx[pos] = id;
+          if (pos < acap) {
+            s_idx[pos] = id[h];
             s_val[pos] = v[h];
-            s_x[pos] = xv;
+            s_x[pos] = xv[h];
             s2 += (double)v[h] * (double)v[h];
-            // D = X - S at the entries surely kept (the tie list may
-            // replace positions from count_above on)
-            if ((dwn != nullptr || dw16 != nullptr) && (long long)pos < dkeep) {
+            if (dwn != nullptr || dw16 != nullptr) {   // D = X - S
               int64_t i, j;
-              divmod_nn(id, ncols, rcols, i, j);
-              const T dv = (T)(xv - v[h]);
+              divmod_nn(id[h], ncols, rcols, i, j);
+              const T dv = (T)(xv[h] - v[h]);
               if (dwn) dwn[i * lddw + j] = dv;
               if constexpr (sizeof(T) == 4)
                 if (dw16) dw16[i * lddw + j] = f32_to_bf16(dv);
             }
           }
         }
-        if (tie) {
+        if (in) {
           const unsigned long long pos = bt + __popcll(mt & below);
-          if (pos < tcap) tie_idx[pos] = cand_idx[c];
+          if (pos < tcap) list[pos] = c;
         }
         ba += __popcll(ma);
         bt += __popcll(mt);
@@ -963,124 +1029,258 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
   s2 = wave_sum(s2);
   if (lane == 0) red[wave] = s2;
   __syncthreads();
-  // per-block partial; k_sel_ties adds them in block order
+  // per-block partial; k_sel_final adds them in block order
   if (tid == 0) s2sel[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-// Resolve ties: keep the k_rem smallest linear indices among the entries
-// equal to the threshold key (one block; bitonic sort in LDS when they fit,
-// otherwise repeated minimum extraction by a radix select on the index).
 // The next iteration histograms and collects from kCarryWindow level-0
 // digits below this threshold (1/8 octave for f32 keys, which have 16 digits
 // per octave; 1 octave for f64 keys).
+constexpr int kCarryWindow = 2;
 template <typename T>
 __device__ __forceinline__ void carry_update(SelCarry* carry, unsigned long long tkey) {
   constexpr int KB = KeyBits<T>::value;
-  constexpr int W = sizeof(T) == 4 ? 2 : 2;
-  const int d = (int)(tkey >> (KB - kHistBits0)) - W;
+  const int d = (int)(tkey >> (KB - kHistBits0)) - kCarryWindow;
   carry->dlo = d > 0 ? d : 0;
   carry->valid = 1;
 }
 
+// The state a selection starts from.
 template <typename T>
-__global__ __launch_bounds__(1024) void k_sel_ties(SelPlan* __restrict__ plan,
-                                                   int64_t* __restrict__ s_idx,
-                                                   T* __restrict__ s_val,
-                                                   int64_t* __restrict__ tie_idx,
-                                                   unsigned long long* __restrict__ counters,
-                                                   SelCarry* __restrict__ carry,
-                                                   const double* __restrict__ s2sel, int nsel) {
-  constexpr int KB = KeyBits<T>::value;
-  constexpr int NS = 4096;
-  __shared__ int64_t sk[NS];
-  __shared__ unsigned long long cnt[256];
-  __shared__ unsigned long long sh_pref;
-  __shared__ long long sh_need;
-  __shared__ double red[20];
-  const int tid = threadIdx.x;
-  if (plan->mode != SEL_FINAL) return;
-  // sum of S_t^2 over the entries above the threshold: the compaction's
-  // per-block partials in block order
-  const double sel_above = block_sum_fixed(s2sel, nsel, red);
-  const unsigned long long tkey = plan->prefix;
-  long long nabove = (long long)counters[0];
-  if (nabove > plan->count_above) nabove = plan->count_above;
-  long long nties = (long long)counters[1];
-  if (nties > plan->cap) nties = plan->cap;
-  long long take = (tkey > 0) ? plan->k_rem : 0;
-  if (take > nties) take = nties;
-  const T tval = key_to_val(tkey, (T*)nullptr);
-  if (take == nties) {
-    for (long long e = tid; e < take; e += blockDim.x) {
-      s_idx[nabove + e] = tie_idx[e];
-      s_val[nabove + e] = T(0);   // sign restored below
+__device__ __forceinline__ void plan_reset(SelPlan* plan, unsigned long long* counters,
+                                           long long k, long long cap, int nseg,
+                                           const SelCarry* carry) {
+  plan->prefix = 0; plan->k_rem = k; plan->count_above = 0; plan->bucket_count = 0;
+  plan->ncand = 0; plan->cap = cap; plan->nnz = 0; plan->pbits = 0;
+  plan->kbits = KeyBits<T>::value;
+  plan->mode = (k > 0) ? SEL_HIST : SEL_FINAL; plan->slow = 0; plan->overflow = 0;
+  plan->nseg = nseg;
+  plan->sum_r2 = 0.0; plan->sum_sel2 = 0.0; plan->threshold = 0.0;
+  plan->carry_used = carry->valid ? 1 : 0;
+  plan->carry_dlo = carry->dlo;
+  plan->arrivals = 0u;
+  plan->blo = 1ull;
+  plan->bhi = 0ull;
+  counters[0] = 0; counters[1] = 0;
+}
+
+// What k_sel_final writes entries to.
+template <typename T>
+struct SelOut {
+  int64_t* idx;
+  T* val;
+  T* x;
+  T* dwn;
+  uint16_t* dw16;
+  int64_t lddw, ncols;
+  double rcols;
+  __device__ __forceinline__ void put(long long pos, int64_t id, T v, T xv) const {
+    idx[pos] = id;
+    val[pos] = v;
+    x[pos] = xv;
+    if (dwn != nullptr || dw16 != nullptr) {
+      int64_t i, j;
+      divmod_nn(id, ncols, rcols, i, j);
+      const T dv = (T)(xv - v);
+      if (dwn) dwn[i * lddw + j] = dv;
+      if constexpr (sizeof(T) == 4)
+        if (dw16) dw16[i * lddw + j] = f32_to_bf16(dv);
     }
-  } else if (nties <= NS) {
-    for (int e = tid; e < NS; e += blockDim.x) sk[e] = (e < nties) ? tie_idx[e] : INT64_MAX;
+  }
+};
+
+// Digit of the need-th entry in the order of a 256-bin count (from the top
+// bin down, or from the bottom up), and the entries before it.  One thread.
+__device__ __forceinline__ void digit_at(const unsigned long long* cnt, long long need,
+                                         bool from_top, int& digit, unsigned long long& before) {
+  before = 0;
+  int d = 0;
+  for (; d < 255; ++d) {
+    const unsigned long long c = cnt[from_top ? 255 - d : d];
+    if ((long long)(before + c) >= need) break;
+    before += c;
+  }
+  digit = from_top ? 255 - d : d;
+}
+
+// Last step of a selection, one block: take k_rem of the listed candidates by
+// (|R| descending, linear index ascending), write them to S and X - S into
+// the working copies, close the plan, carry the threshold, and reset the
+// other iteration's plan (which the next selection uses) and the counters.
+// Usually the list holds a few entries (one histogram bin): up to 1024 are
+// ranked by counting; longer lists by a radix select on the key and then, for
+// ties at the threshold that do not all fit, on the index.
+constexpr int kFinalThreads = 1024;
+template <typename T>
+__global__ __launch_bounds__(kFinalThreads) void k_sel_final(
+    SelPlan* __restrict__ plan, SelPlan* __restrict__ next, const int64_t* __restrict__ cand_idx,
+    const T* __restrict__ cand_val, const T* __restrict__ cand_x,
+    const int64_t* __restrict__ list, unsigned long long* __restrict__ counters,
+    SelCarry* __restrict__ carry, const double* __restrict__ s2sel, int nsel, SelOut<T> out,
+    long long k, long long cap, int nseg) {
+  constexpr int NT = kFinalThreads;
+  __shared__ unsigned long long kk[NT];
+  __shared__ int64_t ii[NT];
+  __shared__ double vv[NT];
+  __shared__ double red[NT / 64 + 1];
+  __shared__ unsigned long long cnt[256];
+  __shared__ unsigned long long sh_key, sh_lim, sh_pos, sh_lo, sh_hi;
+  __shared__ long long sh_need;
+  const int tid = threadIdx.x;
+  if (plan->mode == SEL_FINAL) {
+    // sum of S_t^2 over the entries above: the compaction's per-block
+    // partials in block order
+    const double sel_above = block_sum_fixed(s2sel, nsel, red);
+    const long long nabove = plan->count_above;
+    long long nl = (long long)counters[1];
+    if (nl > plan->cap) nl = plan->cap;
+    const long long k_rem = plan->k_rem;
+    const long long take = k_rem < nl ? k_rem : nl;
+    if (tid == 0) sh_key = 0ull;
     __syncthreads();
-    for (int size = 2; size <= NS; size <<= 1)
-      for (int stride = size >> 1; stride > 0; stride >>= 1) {
-        for (int e = tid; e < NS; e += blockDim.x) {
-          const int o = e ^ stride;
-          if (o > e) {
-            const bool up = (e & size) == 0;
-            const int64_t a = sk[e], b = sk[o];
-            if ((a > b) == up) { sk[e] = b; sk[o] = a; }
-          }
+    double s2 = 0.0;
+    if (nl <= NT) {
+      T v = T(0), xv = T(0);
+      int64_t id = 0;
+      unsigned long long key = 0;
+      if (tid < nl) {
+        const long long c = list[tid];
+        v = cand_val[c];
+        xv = cand_x[c];
+        id = cand_idx[c];
+        key = abs_key(v);
+        kk[tid] = key;
+        ii[tid] = id;
+      }
+      vv[tid] = 0.0;
+      __syncthreads();
+      if (tid < nl) {
+        int rank = 0;
+        for (int q = 0; q < (int)nl; ++q)
+          rank += kk[q] > key || (kk[q] == key && ii[q] < id);
+        if (rank < take) {
+          out.put(nabove + rank, id, v, xv);
+          vv[rank] = (double)v * (double)v;
+        }
+        if (rank == k_rem - 1) sh_key = key;
+      }
+      __syncthreads();
+      s2 = block_sum_fixed(vv, NT, red);   // in rank order: the same bits on every run
+    } else {
+      // ---- the threshold key: 8 bits at a time below the bits blo and bhi share ----
+      const unsigned long long blo = plan->blo;
+      const unsigned long long bhi = plan->bhi < (1ull << KeyBits<T>::value)
+                                         ? plan->bhi
+                                         : (1ull << KeyBits<T>::value) - 1ull;
+      int w = 0;
+      while (w < 64 && (blo >> w) != (bhi >> w)) ++w;   // undecided bits
+      unsigned long long pref = w < 64 ? blo >> w : 0ull;
+      long long need = take;
+      unsigned long long neq = (unsigned long long)nl;
+      while (w > 0) {
+        const int step = w < 8 ? w : 8;
+        if (tid < 256) cnt[tid] = 0ull;
+        __syncthreads();
+        for (long long e = tid; e < nl; e += NT) {
+          const unsigned long long key = abs_key(cand_val[list[e]]);
+          if ((key >> w) == pref) atomicAdd(&cnt[(key >> (w - step)) & ((1u << step) - 1u)], 1ull);
         }
         __syncthreads();
-      }
-    for (long long e = tid; e < take; e += blockDim.x) {
-      s_idx[nabove + e] = sk[e];
-      s_val[nabove + e] = T(0);
-    }
-  } else {
-    // radix select of the take-th smallest index (8 bits at a time)
-    if (tid == 0) { sh_pref = 0; sh_need = take; }
-    __syncthreads();
-    for (int shift = 56; shift >= 0; shift -= 8) {
-      if (tid < 256) cnt[tid] = 0;
-      __syncthreads();
-      const unsigned long long pref = sh_pref;
-      for (long long e = tid; e < nties; e += blockDim.x) {
-        const unsigned long long x = (unsigned long long)tie_idx[e];
-        if (shift == 56 || (x >> (shift + 8)) == pref)
-          atomicAdd(&cnt[(x >> shift) & 255], 1ull);
-      }
-      __syncthreads();
-      if (tid == 0) {
-        long long need = sh_need;
-        unsigned long long cum = 0;
-        int d = 0;
-        for (; d < 256; ++d) {
-          if ((long long)(cum + cnt[d]) >= need) break;
-          cum += cnt[d];
+        if (tid == 0) {
+          int d;
+          unsigned long long before;
+          digit_at(cnt, need, true, d, before);
+          sh_need = need - (long long)before;
+          sh_pos = cnt[d];
+          sh_key = (pref << step) | (unsigned long long)d;
         }
-        sh_need = need - (long long)cum;
-        sh_pref = (pref << 8) | (unsigned long long)d;
+        __syncthreads();
+        pref = sh_key;
+        need = sh_need;
+        neq = sh_pos;
+        w -= step;
+        __syncthreads();
       }
+      const unsigned long long tkey = pref;
+      if (tid == 0) {
+        sh_key = k_rem <= nl ? tkey : 0ull;
+        sh_lim = ~0ull;
+      }
+      // ---- the last index taken among the entries equal to it ----
+      if (need < (long long)neq) {
+        unsigned long long ipref = 0;
+        long long ineed = need;
+        for (int shift = 56; shift >= 0; shift -= 8) {
+          if (tid < 256) cnt[tid] = 0ull;
+          __syncthreads();
+          for (long long e = tid; e < nl; e += NT) {
+            const long long c = list[e];
+            const unsigned long long x = (unsigned long long)cand_idx[c];
+            if (abs_key(cand_val[c]) == tkey && (shift == 56 || (x >> (shift + 8)) == ipref))
+              atomicAdd(&cnt[(x >> shift) & 255], 1ull);
+          }
+          __syncthreads();
+          if (tid == 0) {
+            int d;
+            unsigned long long before;
+            digit_at(cnt, ineed, false, d, before);
+            sh_need = ineed - (long long)before;
+            sh_lim = (ipref << 8) | (unsigned long long)d;
+          }
+          __syncthreads();
+          ipref = sh_lim;
+          ineed = sh_need;
+          __syncthreads();
+        }
+      }
+      if (tid == 0) { sh_pos = 0ull; sh_lo = 0ull; sh_hi = 0ull; }
       __syncthreads();
-    }
-    const unsigned long long lim = sh_pref;   // the take-th smallest index
-    __shared__ unsigned long long wpos;
-    if (tid == 0) wpos = 0;
-    __syncthreads();
-    for (long long e = tid; e < nties; e += blockDim.x) {
-      const unsigned long long x = (unsigned long long)tie_idx[e];
-      if (x <= lim) {
-        const unsigned long long p = atomicAdd(&wpos, 1ull);
-        s_idx[nabove + p] = (int64_t)x;
-        s_val[nabove + p] = T(0);
+      // ---- write; the sum of squares in fixed point (two 30-bit halves of
+      // each square relative to the bin's largest), so that it does not
+      // depend on the order of the list ----
+      const unsigned long long lim = sh_lim;
+      const double vmax = (double)key_to_val(bhi, (T*)nullptr);
+      const double vm2 = vmax * vmax;
+      const bool fixed = vm2 > 1e-280 && vm2 < 1e280;
+      int ex = 0;
+      if (fixed) frexp(vm2, &ex);
+      const double up = fixed ? ldexp(1.0, 60 - ex) : 1.0;
+      unsigned long long lo = 0ull, hi = 0ull;
+      for (long long e = tid; e < nl; e += NT) {
+        const long long c = list[e];
+        const T v = cand_val[c];
+        const int64_t id = cand_idx[c];
+        const unsigned long long key = abs_key(v);
+        if (key > tkey || (key == tkey && (unsigned long long)id <= lim)) {
+          const unsigned long long pos = atomicAdd(&sh_pos, 1ull);
+          if ((long long)pos < take) out.put(nabove + (long long)pos, id, v, cand_x[c]);
+          const double q = (double)v * (double)v;
+          if (fixed) {
+            const unsigned long long b = (unsigned long long)(q * up);
+            lo += b & ((1ull << 30) - 1ull);
+            hi += b >> 30;
+          } else {
+            s2 += q;
+          }
+        }
       }
+      atomicAdd(&sh_lo, lo);
+      atomicAdd(&sh_hi, hi);
+      vv[tid] = s2;
+      __syncthreads();
+      s2 = block_sum_fixed(vv, NT, red);
+      if (fixed) s2 = ((double)sh_hi * (double)(1ull << 30) + (double)sh_lo) / up;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      plan->nnz = nabove + take;
+      plan->threshold = (double)key_to_val(sh_key, (T*)nullptr);
+      plan->sum_sel2 = sel_above + s2;
+      carry_update<T>(carry, sh_key);
     }
   }
   __syncthreads();
-  if (tid == 0) {
-    plan->nnz = nabove + take;
-    plan->threshold = (double)tval;
-    plan->sum_sel2 = sel_above + (double)take * (double)tval * (double)tval;
-    carry_update<T>(carry, tkey);
-  }
+  if (tid == 0) plan_reset<T>(next, counters, k, cap, nseg, carry);
 }
 
 // After a TIES collection the candidates hold the entries above the
@@ -1302,9 +1502,11 @@ __global__ __launch_bounds__(256) void k_sel_ties_stream(const T* __restrict__ X
   }
 }
 
-// Restore the sign of tied entries: their stored value is the residual,
-// recomputed here from X and the factors (same arithmetic as selection).
-// FP32: one wavefront per entry, which evaluates the entry's aligned tile.
+// After an index-ordered tie scan: restore the sign of the tied entries, whose
+// stored value is the residual, recomputed here from X and the factors (same
+// arithmetic as the selection), and write X - S into the working copies at
+// every entry.  FP32: one wavefront per entry, which evaluates the entry's
+// aligned tile.
 template <typename T, int RP>
 __global__ __launch_bounds__(256) void k_fix_tie_values(const T* __restrict__ X, int64_t ldx,
                                                         const T* __restrict__ UL,
@@ -1312,17 +1514,13 @@ __global__ __launch_bounds__(256) void k_fix_tie_values(const T* __restrict__ X,
                                                         const T* __restrict__ VLt, int64_t ldv,
                                                         int64_t m, int64_t n,
                                                         const SelPlan* __restrict__ plan,
-                                                        const unsigned long long* __restrict__ counters,
                                                         int64_t* __restrict__ s_idx,
                                                         T* __restrict__ s_val,
                                                         T* __restrict__ s_x,
                                                         T* __restrict__ dwn,
                                                         uint16_t* __restrict__ dw16,
                                                         int64_t lddw) {
-  // the entries the compaction did not write: the ties (from where the tie
-  // list starts), or every entry after a threshold scan (counters[0] = 0)
-  long long start = (long long)counters[0];
-  if (start > plan->count_above) start = plan->count_above;
+  if (plan->mode != SEL_DONE) return;
   const long long nnz = plan->nnz;
   const bool dupd = dwn != nullptr || dw16 != nullptr;
   // D = X - S at entry (i, j) of the working copies
@@ -1336,8 +1534,8 @@ __global__ __launch_bounds__(256) void k_fix_tie_values(const T* __restrict__ X,
     constexpr int KS = ResK<RP>::KS;
     const int lane = threadIdx.x & 63;
     const long long nw = (long long)gridDim.x * (blockDim.x >> 6);
-    for (long long e = start + (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-         e < nnz; e += nw) {
+    for (long long e = (long long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); e < nnz;
+         e += nw) {
       const int64_t idx = s_idx[e];
       const int64_t i = idx / n, j = idx % n;
       if (s_val[e] != 0.f) {   // the whole wavefront reads the same entry
@@ -1360,7 +1558,7 @@ __global__ __launch_bounds__(256) void k_fix_tie_values(const T* __restrict__ X,
     }
     return;
   }
-  for (long long e = start + (long long)blockIdx.x * 256 + threadIdx.x; e < nnz;
+  for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < nnz;
        e += (long long)gridDim.x * 256) {
     const int64_t idx = s_idx[e];
     const int64_t i = idx / n, j = idx % n;
@@ -1379,26 +1577,19 @@ __global__ __launch_bounds__(256) void k_fix_tie_values(const T* __restrict__ X,
   }
 }
 
+// Before the first selection of a context (later ones start from the state
+// that k_sel_final left): the histogram, the plan and the counters, and empty
+// segments, so that consumers see no candidates when no collecting pass runs
+// (k == 0 goes straight to SEL_FINAL).
 template <typename T>
-__global__ void k_sel_reset(SelPlan* plan, unsigned long long* hist,
-                            unsigned long long* counters, unsigned int* seg_count, long long k,
-                            long long cap, int nseg, const SelCarry* carry) {
-  constexpr int KB = KeyBits<T>::value;
+__global__ __launch_bounds__(256) void k_sel_reset(SelPlan* plan, unsigned long long* hist,
+                                                   unsigned long long* counters,
+                                                   unsigned int* seg_count, long long k,
+                                                   long long cap, int nseg,
+                                                   const SelCarry* carry) {
   for (int e = threadIdx.x; e < kHistRep * kHistBins; e += blockDim.x) hist[e] = 0ull;
-  // empty segments, so that consumers see no candidates when no collecting
-  // pass runs (k == 0 goes straight to SEL_FINAL)
   for (int e = threadIdx.x; e < nseg; e += blockDim.x) seg_count[e] = 0u;
-  if (threadIdx.x == 0) {
-    plan->prefix = 0; plan->k_rem = k; plan->count_above = 0; plan->bucket_count = 0;
-    plan->ncand = 0; plan->cap = cap; plan->nnz = 0; plan->pbits = 0; plan->kbits = KB;
-    plan->mode = (k > 0) ? SEL_HIST : SEL_FINAL; plan->slow = 0; plan->overflow = 0;
-    plan->nseg = nseg;
-    plan->sum_r2 = 0.0; plan->sum_sel2 = 0.0; plan->threshold = 0.0;
-    plan->carry_used = carry->valid ? 1 : 0;
-    plan->carry_dlo = carry->dlo;
-    plan->arrivals = 0u;
-    counters[0] = 0; counters[1] = 0;
-  }
+  if (threadIdx.x == 0) plan_reset<T>(plan, counters, k, cap, nseg, carry);
 }
 
 // VLt (rp x ldv) <- VL (ldv x rp), both in the residual type.
@@ -1638,92 +1829,112 @@ static unsigned grid_for(int64_t work, int num_cu, int per_cu) {
   return (unsigned)g;
 }
 
-// Blocks of the full-data passes (one candidate segment each).
+// Shape of the full-data passes: blocks (four candidate segments each), and
+// for FP64 the columns per thread (narrow: 1) and rows per tile.
 // FP32 passes (matrix-core tiles, four blocks per CU fit) take up to four
-// blocks per CU; FP64 passes two.
+// blocks per CU; FP64 passes two, in tiles of 64 rows when there are enough
+// of them for two blocks per CU and down to 4 otherwise (500 x 500, r = 5:
+// one column per thread and 4 rows, 250 blocks, against four columns and 64
+// rows, 8 blocks: 12 against 61 us).
+struct SelShape {
+  int64_t g;
+  bool narrow;
+  int rpt;
+};
 template <typename T>
-static int64_t sel_grid(int rp, int64_t m, int64_t n, int num_cu) {
-  int64_t g = 1;
+static SelShape sel_shape(int rp, int64_t m, int64_t n, int num_cu) {
+  SelShape s{1, false, kRowsPerTile};
   if (sizeof(T) == 4) {
     int64_t cols = 512;
     GODEC_RP_SWITCH(rp, { cols = ResStrip<RP>::COLS; });
-    g = ((n + cols - 1) / cols) * ((m + 15) / 16);
-    g = std::min<int64_t>(g, (int64_t)num_cu * 4);
+    s.g = ((n + cols - 1) / cols) * ((m + 15) / 16);
+    s.g = std::min<int64_t>(s.g, (int64_t)num_cu * 4);
   } else {
-    GODEC_RP_SWITCH(rp, {
-      constexpr int TW = 256 * sel_cpt<T, RP>();
-      g = ((n + TW - 1) / TW) * ((m + kRowsPerTile - 1) / kRowsPerTile);
-    });
-    g = std::min<int64_t>(g, (int64_t)num_cu * 2);
+    s.narrow = n <= 1024;
+    int64_t tw = 256;
+    GODEC_RP_SWITCH(rp, { tw = s.narrow ? 256 : 256 * sel_cpt<RP>(); });
+    const int64_t ct = (n + tw - 1) / tw, want = 2LL * num_cu;
+    while (s.rpt > 4 && ct * ((m + s.rpt - 1) / s.rpt) < want) s.rpt /= 2;
+    s.g = std::min<int64_t>(ct * ((m + s.rpt - 1) / s.rpt), want);
   }
-  return std::max<int64_t>(1, std::min<int64_t>(g, kMaxSeg / kSelWaves));
+  s.g = std::max<int64_t>(1, std::min<int64_t>(s.g, kMaxSeg / kSelWaves));
+  return s;
+}
+
+// The full-data passes: pass 0, then the fall-backs (the level-0 histogram
+// and the collection; between them one pass per deeper digit, needed only
+// when the bucket can overflow the candidate buffer).  The passes after pass 0
+// advance the plan in their last block (32-bit bin counts: m n < 2^32), so a
+// pass with nothing to do costs one launch; otherwise, and after pass 0,
+// k_sel_plan does.
+template <typename T, int RP, int CPT>
+static void sel_passes(const Launch& L, const SelectArgs& a, const SelShape& s, int fallbacks,
+                       bool fuse) {
+  const dim3 g((unsigned)s.g);
+  for (int pass = 0; pass <= fallbacks; ++pass) {
+    if (pass == 0) {
+      if (a.ev_a) (void)hipEventRecord(a.ev_a, L.stream);
+      hipLaunchKernelGGL((k_sel_pass0<T, RP, CPT>), g, dim3(256), 0, L.stream, (const T*)a.X,
+                         a.ldx, (const T*)a.UL, (const T*)a.VLt, a.ldv, a.m, a.n, a.plan, a.hist,
+                         a.cand_idx, (T*)a.cand_val, (T*)a.cand_x, a.seg_count, a.s2part, s.rpt,
+                         sizeof(T) == 4 ? a.r16 : nullptr, a.ldd16, a.ridx, a.rx, a.rplan);
+      if (a.ev_b) (void)hipEventRecord(a.ev_b, L.stream);
+    } else {
+      hipLaunchKernelGGL((k_sel_passN<T, RP, CPT>), g, dim3(256), 0, L.stream, (const T*)a.X,
+                         a.ldx, (const T*)a.UL, (const T*)a.VLt, a.ldv, a.m, a.n, a.plan, a.hist,
+                         a.cand_idx, (T*)a.cand_val, (T*)a.cand_x, a.seg_count, s.rpt,
+                         fuse ? 1 : 0);
+    }
+    if (pass == 0 || !fuse)
+      hipLaunchKernelGGL(k_sel_plan<T>, dim3(1), dim3(kPlanThreads), 0, L.stream, a.plan, a.hist,
+                         pass == 0 ? (const double*)a.s2part : nullptr, (int)s.g);
+  }
 }
 
 template <typename T>
 static void select_t(const Launch& L, int rp, const SelectArgs& a) {
   constexpr int KB = KeyBits<T>::value;
-  const int levels = 1 + (KB - kHistBits0 + kHistBits - 1) / kHistBits;
-  const int64_t g = sel_grid<T>(rp, a.m, a.n, L.num_cu);
-  const int nseg = (int)g * kSelWaves;
-  // the passes after pass 0 advance the plan in their last block (32-bit
-  // bin counts: m n < 2^32), so a pass with nothing to do costs one launch;
-  // otherwise, and after pass 0 and the candidate histograms, k_sel_plan
+  const SelShape s = sel_shape<T>(rp, a.m, a.n, L.num_cu);
+  const int nseg = (int)s.g * kSelWaves;
   const bool fuse = (uint64_t)a.m * (uint64_t)a.n < (1ull << 32);
-  hipLaunchKernelGGL(k_sel_reset<T>, dim3(1), dim3(256), 0, L.stream, a.plan, a.hist,
-                     a.counters, a.seg_count, (long long)a.k, (long long)a.cap, nseg, a.carry);
+  // with room for every entry the first bucket always fits
+  const bool all_fit = a.cap >= a.m * a.n;
+  const int levels = 1 + (KB - kHistBits0 + kHistBits - 1) / kHistBits;
+  if (a.first)
+    hipLaunchKernelGGL(k_sel_reset<T>, dim3(1), dim3(256), 0, L.stream, a.plan, a.hist,
+                       a.counters, a.seg_count, (long long)a.k, (long long)a.cap, nseg, a.carry);
   GODEC_RP_SWITCH(rp, {
-    // pass 0 (carried window or full level 0), one spare pass for the
-    // fall-back level-0 histogram, then one per deeper level and the collection
-    for (int pass = 0; pass <= levels + 1; ++pass) {
-      if (pass == 0) {
-        if (a.ev_a) (void)hipEventRecord(a.ev_a, L.stream);
-        hipLaunchKernelGGL((k_sel_pass0<T, RP>), dim3((unsigned)g), dim3(256), 0, L.stream,
-                           (const T*)a.X, a.ldx, (const T*)a.UL, (const T*)a.VLt, a.ldv, a.m,
-                           a.n, a.plan, a.hist, a.cand_idx, (T*)a.cand_val, (T*)a.cand_x,
-                           a.seg_count, a.s2part, sizeof(T) == 4 ? a.r16 : nullptr, a.ldd16,
-                           a.ridx, a.rx, a.rplan);
-        if (a.ev_b) (void)hipEventRecord(a.ev_b, L.stream);
-      } else {
-        hipLaunchKernelGGL((k_sel_passN<T, RP>), dim3((unsigned)g), dim3(256), 0, L.stream,
-                           (const T*)a.X, a.ldx, (const T*)a.UL, (const T*)a.VLt, a.ldv, a.m,
-                           a.n, a.plan, a.hist, a.cand_idx, (T*)a.cand_val, (T*)a.cand_x,
-                           a.seg_count, fuse ? 1 : 0);
-      }
-      if (pass == 0 || !fuse)
-        hipLaunchKernelGGL(k_sel_plan<T>, dim3(1), dim3(256), 0, L.stream, a.plan, a.hist, 0,
-                           pass == 0 ? (const double*)a.s2part : nullptr, (int)g);
+    const int fallbacks = all_fit ? 2 : levels + 1;
+    if constexpr (sizeof(T) == 4) {
+      sel_passes<T, RP, 1>(L, a, s, fallbacks, fuse);
+    } else {
+      if (s.narrow) sel_passes<T, RP, 1>(L, a, s, fallbacks, fuse);
+      else sel_passes<T, RP, sel_cpt<RP>()>(L, a, s, fallbacks, fuse);
+    }
+    if (!all_fit) {
+      hipLaunchKernelGGL((k_sel_ties_stream<T, RP>), dim3(1), dim3(256), 0, L.stream,
+                         (const T*)a.X, a.ldx, (const T*)a.UL, (const T*)a.VL, (const T*)a.VLt,
+                         a.ldv, a.m, a.n, a.plan, a.cand_idx, (const T*)a.cand_val,
+                         (const T*)a.cand_x, (const unsigned int*)a.seg_count, a.s_idx,
+                         (T*)a.s_val, (T*)a.s_x, a.carry);
+      hipLaunchKernelGGL((k_fix_tie_values<T, RP>), dim3(grid_for(a.k, L.num_cu, 2)), dim3(256),
+                         0, L.stream, (const T*)a.X, a.ldx, (const T*)a.UL, (const T*)a.VL,
+                         (const T*)a.VLt, a.ldv, a.m, a.n, a.plan, a.s_idx, (T*)a.s_val,
+                         (T*)a.s_x, (T*)a.dwn, sizeof(T) == 4 ? a.dw16 : nullptr, a.lddw);
     }
   });
-  const unsigned cg = (unsigned)(g + 1);   // segments are taken round-robin by blocks
-  for (int round = 0; round < levels - 1; ++round) {
-    hipLaunchKernelGGL(k_cand_hist<T>, dim3(cg), dim3(256), 0, L.stream, a.plan,
-                       (const T*)a.cand_val, (const unsigned int*)a.seg_count, a.hist);
-    hipLaunchKernelGGL(k_sel_plan<T>, dim3(1), dim3(256), 0, L.stream, a.plan, a.hist, 1,
-                       (const double*)nullptr, 0);
-  }
-  GODEC_RP_SWITCH(rp, {
-    hipLaunchKernelGGL((k_sel_ties_stream<T, RP>), dim3(1), dim3(256), 0, L.stream,
-                       (const T*)a.X, a.ldx, (const T*)a.UL, (const T*)a.VL, (const T*)a.VLt,
-                       a.ldv, a.m, a.n, a.plan,
-                       a.cand_idx, (const T*)a.cand_val, (const T*)a.cand_x,
-                       (const unsigned int*)a.seg_count, a.s_idx, (T*)a.s_val, (T*)a.s_x,
-                       a.carry);
-  });
+  const unsigned cg = (unsigned)(s.g + 1);   // segments are taken round-robin by blocks
+  uint16_t* dw16 = sizeof(T) == 4 ? a.dw16 : nullptr;
   hipLaunchKernelGGL(k_sel_compact<T>, dim3(cg), dim3(256), 0, L.stream, a.plan, a.cand_idx,
                      (const T*)a.cand_val, (const T*)a.cand_x, (const unsigned int*)a.seg_count,
                      a.s_idx, (T*)a.s_val, (T*)a.s_x, a.tie_idx, a.counters,
-                     a.s2part + kSelParts, (T*)a.dwn, sizeof(T) == 4 ? a.dw16 : nullptr,
-                     a.lddw, a.n);
-  hipLaunchKernelGGL(k_sel_ties<T>, dim3(1), dim3(1024), 0, L.stream, a.plan, a.s_idx,
-                     (T*)a.s_val, a.tie_idx, a.counters, a.carry,
-                     (const double*)(a.s2part + kSelParts), (int)cg);
-  GODEC_RP_SWITCH(rp, {
-    hipLaunchKernelGGL((k_fix_tie_values<T, RP>), dim3(grid_for(a.k, L.num_cu, 2)), dim3(256),
-                       0, L.stream, (const T*)a.X, a.ldx, (const T*)a.UL, (const T*)a.VL,
-                       (const T*)a.VLt, a.ldv, a.m, a.n, a.plan, a.counters, a.s_idx,
-                       (T*)a.s_val, (T*)a.s_x, (T*)a.dwn,
-                       sizeof(T) == 4 ? a.dw16 : nullptr, a.lddw);
-  });
+                     a.s2part + kSelParts, (T*)a.dwn, dw16, a.lddw, a.n);
+  const SelOut<T> out{a.s_idx, (T*)a.s_val, (T*)a.s_x, (T*)a.dwn, dw16, a.lddw, a.n,
+                      1.0 / (double)a.n};
+  hipLaunchKernelGGL(k_sel_final<T>, dim3(1), dim3(kFinalThreads), 0, L.stream, a.plan, a.next,
+                     a.cand_idx, (const T*)a.cand_val, (const T*)a.cand_x, a.tie_idx, a.counters,
+                     a.carry, (const double*)(a.s2part + kSelParts), (int)cg, out,
+                     (long long)a.k, (long long)a.cap, nseg);
 }
 
 void launch_transpose_panel(const Launch& L, bool f64, const void* VL, int64_t rows, int rp,

@@ -122,3 +122,64 @@ def test_l_update_of_narrow_matrices(m, n, r, q, lstep, dt, tol):
         D.ravel()[idx] -= val
     assert gd.info()["rank_eff"] == r
     gd.close()
+
+
+def _mse_identity(X, K, steps):
+    """MSE training with one empty label: the sparse step selects from X
+    itself, so the input sets the ties.  Yields S after each step."""
+    from paper_1309_0302_amd.binding import GoDecMSE
+    tr = GoDecMSE(torch.from_numpy(X).to("cuda:0"), [np.zeros(0, np.int64)], [1], K, seed=1)
+    for _ in range(steps):
+        tr.step(1)
+        idx, val = tr.S()
+        yield idx.cpu().numpy(), val.cpu().numpy(), tr.info()
+    E = tr.residual().cpu().numpy()
+    ref = X.copy()
+    ref.ravel()[idx.cpu().numpy()] = 0
+    assert np.array_equal(E, ref)
+    tr.close()
+
+
+# the last histogram bin: a few entries, over 1024 (radix select of its list),
+# ties that fit and that do not (taken by index), more ties than the candidate
+# buffer holds (index-ordered scan), nothing, everything, more than the nonzeros
+@pytest.mark.parametrize("dt,n,p,K,values", [
+    (np.float32, 300, 512, 50000, "ints"), (np.float64, 300, 256, 30000, "ints"),
+    (np.float32, 2048, 512, 400000, "grid"), (np.float64, 3000, 200, 200001, "grid"),
+    (np.float32, 1025, 77, 3000, "normal"), (np.float64, 1025, 77, 3000, "normal"),
+    (np.float32, 4096, 512, 1000, "signs"), (np.float64, 5000, 256, 70, "signs"),
+    (np.float32, 65, 33, 0, "normal"), (np.float32, 65, 33, 65 * 33, "normal"),
+    (np.float64, 500, 100, 40000, "few"), (np.float32, 1, 1, 1, "normal"),
+    (np.float64, 700, 256, 5000, "wide")])
+def test_selection_lists(dt, n, p, K, values):
+    """S against a sort of the input by (magnitude, index), in the first step
+    (full histogram) and in later ones (carried window); the objective's
+    sums to FP64 rounding of sums of n p terms."""
+    rng = np.random.default_rng(n + p + K)
+    x = rng.standard_normal((n, p))
+    if values == "ints":
+        x = np.round(3 * x)
+    elif values == "grid":
+        x = np.round(x * 512) / 512
+    elif values == "signs":
+        x = np.sign(x)
+    elif values == "few":
+        x = np.where(rng.random((n, p)) < 0.3, x, 0.0)
+    elif values == "wide":
+        x = x * 10.0 ** rng.integers(-30, 30, size=(n, p))
+    X = x.astype(dt)
+    ref = topk_indices(X, K)
+    seen = []
+    for idx, val, info in _mse_identity(X, K, 3):
+        assert np.array_equal(idx, ref)
+        assert np.array_equal(val, X.ravel()[ref])
+        X64 = X.astype(np.float64)
+        thr = np.abs(val).min() if ref.size == K and K > 0 else 0.0
+        assert info["threshold"] == thr
+        rest = np.delete(X64.ravel(), ref)
+        # the objective is the difference of two sums of up to n p squares
+        tol = 1e-15 * np.sqrt(n * p) * 4
+        assert abs(info["rel_err_sq"] - np.sum(rest ** 2) / np.sum(X64 ** 2)) <= tol
+        seen.append(info["rel_err_sq"])
+    for idx, val, info in _mse_identity(X, K, 1):
+        assert info["rel_err_sq"] == seen[0]
