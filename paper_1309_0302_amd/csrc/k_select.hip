@@ -906,13 +906,38 @@ __global__ __launch_bounds__(256) void k_sel_passN(const T* __restrict__ X, int6
                           &pl_flag, &hit);
 }
 
+// Sum of squares that does not depend on the order of its terms: each square
+// relative to a bound of the whole sum in two limbs of 40 bits (what is cut
+// off is 2^-80 of the bound per term), added as integers.  Bounds outside the
+// range of the scale factor leave it to plain FP64 sums.
+struct FixedSum {
+  double up, down;
+  bool on;
+  __device__ explicit FixedSum(double bound) {
+    on = bound > 1e-280 && bound < 1e280;
+    int ex = 0;
+    if (on) frexp(bound, &ex);
+    up = on ? ldexp(1.0, 40 - ex) : 0.0;
+    down = on ? ldexp(1.0, ex - 40) : 0.0;
+  }
+  __device__ void add(double q, unsigned long long& hi, unsigned long long& lo) const {
+    const double s = q * up, f = floor(s);
+    hi += (unsigned long long)f;
+    lo += (unsigned long long)((s - f) * 0x1p40);
+  }
+  __device__ double value(unsigned long long hi, unsigned long long lo) const {
+    return ((double)hi + (double)lo * 0x1p-40) * down;
+  }
+};
+
 // FINAL: write S from the candidates.  Entries above the last bin go straight
 // to S; the positions of those in it go to the list of k_sel_final.  Wave w of
 // block b takes the candidate segments 4 b + w, 4 b + w + 4 gridDim.x, ...:
 // the waves count their entries, the block reserves its output range with one
 // atomic per list, and each wave then writes its entries in order (ballots
 // only, no block barrier), 256 candidates per step with every load of the
-// step issued first.
+// step issued first.  Entries of the spill region lie in the order in which
+// their waves came, so their squares are added in fixed point.
 template <typename T>
 __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
                                                      const int64_t* __restrict__ cand_idx,
@@ -977,10 +1002,13 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
   for (int w = 0; w < wave; ++w) { ba += wa[w]; bt += wt[w]; }
   // phase 2: each wave writes its segments in order
   double s2 = 0.0;
+  const FixedSum fs(plan->sum_r2);
+  unsigned long long fhi = 0ull, flo = 0ull;
   for (int sg = w0; sg < ntot; sg += wstride) {
     long long c0, cnt;
     seg_range(plan, seg_count, sg, c0, cnt);
     const long long c1 = c0 + cnt;
+    const bool spill = fs.on && c0 >= plan->cap;   // wave-uniform
     for (long long cb = c0; cb < c1; cb += 256) {
       T v[4], xv[4];
       int64_t id[4];
@@ -1006,7 +1034,9 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
             s_idx[pos] = id[h];
             s_val[pos] = v[h];
             s_x[pos] = xv[h];
-            s2 += (double)v[h] * (double)v[h];
+            const double sq = (double)v[h] * (double)v[h];
+            if (spill) fs.add(sq, fhi, flo);
+            else s2 += sq;
             if (dwn != nullptr || dw16 != nullptr) {   // D = X - S
               int64_t i, j;
               divmod_nn(id[h], ncols, rcols, i, j);
@@ -1024,6 +1054,14 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
         ba += __popcll(ma);
         bt += __popcll(mt);
       }
+    }
+  }
+  if (__ballot((fhi | flo) != 0ull) != 0ull) {
+    fhi = wave_sum(fhi);
+    flo = wave_sum(flo);
+    if (lane == 0) {
+      atomicAdd(&counters[2], fhi);
+      atomicAdd(&counters[3], flo);
     }
   }
   s2 = wave_sum(s2);
@@ -1061,7 +1099,7 @@ __device__ __forceinline__ void plan_reset(SelPlan* plan, unsigned long long* co
   plan->arrivals = 0u;
   plan->blo = 1ull;
   plan->bhi = 0ull;
-  counters[0] = 0; counters[1] = 0;
+  counters[0] = 0; counters[1] = 0; counters[2] = 0; counters[3] = 0;
 }
 
 // What k_sel_final writes entries to.
@@ -1129,8 +1167,10 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
   const int tid = threadIdx.x;
   if (plan->mode == SEL_FINAL) {
     // sum of S_t^2 over the entries above: the compaction's per-block
-    // partials in block order
-    const double sel_above = block_sum_fixed(s2sel, nsel, red);
+    // partials in block order, and the spill region's
+    const FixedSum fs(plan->sum_r2);
+    const double sel_above =
+        block_sum_fixed(s2sel, nsel, red) + fs.value(counters[2], counters[3]);
     const long long nabove = plan->count_above;
     long long nl = (long long)counters[1];
     if (nl > plan->cap) nl = plan->cap;
@@ -1235,16 +1275,11 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
       }
       if (tid == 0) { sh_pos = 0ull; sh_lo = 0ull; sh_hi = 0ull; }
       __syncthreads();
-      // ---- write; the sum of squares in fixed point (two 30-bit halves of
-      // each square relative to the bin's largest), so that it does not
-      // depend on the order of the list ----
+      // ---- write; the list is in the order in which its blocks came, so the
+      // squares are added in fixed point ----
       const unsigned long long lim = sh_lim;
       const double vmax = (double)key_to_val(bhi, (T*)nullptr);
-      const double vm2 = vmax * vmax;
-      const bool fixed = vm2 > 1e-280 && vm2 < 1e280;
-      int ex = 0;
-      if (fixed) frexp(vm2, &ex);
-      const double up = fixed ? ldexp(1.0, 60 - ex) : 1.0;
+      const FixedSum fl(vmax * vmax * (double)nl);
       unsigned long long lo = 0ull, hi = 0ull;
       for (long long e = tid; e < nl; e += NT) {
         const long long c = list[e];
@@ -1255,13 +1290,8 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
           const unsigned long long pos = atomicAdd(&sh_pos, 1ull);
           if ((long long)pos < take) out.put(nabove + (long long)pos, id, v, cand_x[c]);
           const double q = (double)v * (double)v;
-          if (fixed) {
-            const unsigned long long b = (unsigned long long)(q * up);
-            lo += b & ((1ull << 30) - 1ull);
-            hi += b >> 30;
-          } else {
-            s2 += q;
-          }
+          if (fl.on) fl.add(q, hi, lo);
+          else s2 += q;
         }
       }
       atomicAdd(&sh_lo, lo);
@@ -1269,7 +1299,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
       vv[tid] = s2;
       __syncthreads();
       s2 = block_sum_fixed(vv, NT, red);
-      if (fixed) s2 = ((double)sh_hi * (double)(1ull << 30) + (double)sh_lo) / up;
+      if (fl.on) s2 = fl.value(sh_hi, sh_lo);
     }
     __syncthreads();
     if (tid == 0) {
