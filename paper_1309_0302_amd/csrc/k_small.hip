@@ -18,7 +18,22 @@
 
 namespace godec {
 
-constexpr int kSmallThreads = 384;   // the core: one thread per Jacobi item of a round (r = 20: 300)
+// Work items of one round of the eigen-solver: the 2 x 2 blocks of A on and
+// above the diagonal (rounded up to whole wavefronts), then the (row, pair)
+// items of V.
+template <int RP>
+constexpr int jacobi_blocks() { return (RP / 2) * (RP / 2 + 1) / 2; }
+template <int RP>
+constexpr int jacobi_items() { return (jacobi_blocks<RP>() + 63) / 64 * 64 + RP * (RP / 2); }
+// Threads of the core: one per entry of an RP x RP matrix and per item of a
+// round, up to 704 (RP = 32: two entries for some).
+template <int RP>
+constexpr int core_threads() {
+  int t = RP * RP > jacobi_items<RP>() ? RP * RP : jacobi_items<RP>();
+  t = (t + 63) / 64 * 64;
+  if (t < 128) t = 128;   // at least one wave for each matrix
+  return t < 704 ? t : 704;
+}
 
 // Sum of entry e over nparts partial matrices of `stride` doubles, with
 // independent accumulators so the loads overlap.
@@ -212,24 +227,242 @@ __device__ __forceinline__ void rr_pair(int round, int k, int N, int& a, int& b)
   b = pos(N - 1 - k);
 }
 
-// Two-sided cyclic Jacobi on the symmetric matrix A (LDS, stride LD),
-// accumulating V <- V J.  A is zero outside its leading n x n block and V is
+// The rotations that zero two entries a_pq: c and s, whether each is above
+// rounding level, and whether it is large enough that another sweep is
+// needed.  With
+// d = a_qq - a_pp, h = 2 a_pq, r = hypot(d, h): c^2 = (1 + |d| / r) / 2 and
+// s = sgn(d) h / (2 r c).  The matrix is scaled to a largest entry of about
+// 1, so squares stay in range; blocks below 2^-500 of it are left alone.
+// Step by step for both: each is one chain of dependent FP64 operations, and
+// without branches the two interleave (one after the other: 490 cycles).
+__device__ __forceinline__ void jacobi_rot2(const double (&app)[2], const double (&aqq)[2],
+                                            const double (&apq)[2], double (&c)[2],
+                                            double (&s)[2], bool (&did)[2], bool (&big)[2]) {
+  double d[2], h[2], x[2], y[2], f[2], e[2], c2[2], z[2], g[2];
+#define GODEC_PAIR _Pragma("unroll") for (int u = 0; u < 2; ++u)
+  GODEC_PAIR d[u] = aqq[u] - app[u];
+  GODEC_PAIR h[u] = 2.0 * apq[u];
+  GODEC_PAIR x[u] = h[u] * h[u];
+  GODEC_PAIR x[u] = fma(d[u], d[u], x[u]);
+  GODEC_PAIR y[u] = __builtin_amdgcn_rsq(x[u]);
+  // |a_pq| > tol sqrt(|a_pp a_qq|), compared on squares
+  GODEC_PAIR {
+    const double prod = fabs(app[u] * aqq[u]), apq2 = apq[u] * apq[u];
+    did[u] = apq2 > kJacobiTol * kJacobiTol * prod && fabs(apq[u]) > 0x1p-500;
+    big[u] = did[u] && apq2 > kJacobiQuad * kJacobiQuad * prod;
+  }
+  // y = 1 / sqrt(x): one third-order step from the hardware estimate, whose
+  // relative error of at most 2^-23 becomes about 2^-69 before rounding
+  GODEC_PAIR x[u] = x[u] * y[u];
+  GODEC_PAIR e[u] = fma(-x[u], y[u], 1.0);
+  GODEC_PAIR f[u] = fma(0.375, e[u], 0.5);
+  GODEC_PAIR e[u] = y[u] * e[u];
+  GODEC_PAIR y[u] = fma(e[u], f[u], y[u]);
+  GODEC_PAIR d[u] = 0.5 * fabs(d[u]);
+  GODEC_PAIR c2[u] = fma(d[u], y[u], 0.5);
+  GODEC_PAIR z[u] = __builtin_amdgcn_rsq(c2[u]);
+  GODEC_PAIR g[u] = (aqq[u] - app[u] >= 0.0 ? apq[u] : -apq[u]) * y[u];
+  GODEC_PAIR x[u] = c2[u] * z[u];
+  GODEC_PAIR e[u] = fma(-x[u], z[u], 1.0);
+  GODEC_PAIR f[u] = fma(0.375, e[u], 0.5);
+  GODEC_PAIR e[u] = z[u] * e[u];
+  GODEC_PAIR z[u] = fma(e[u], f[u], z[u]);
+  GODEC_PAIR c[u] = did[u] ? c2[u] * z[u] : 1.0;
+  GODEC_PAIR s[u] = did[u] ? g[u] * z[u] : 0.0;
+#undef GODEC_PAIR
+}
+
+// C = op(A) B for RP x RP matrices in LDS (stride RP + 1), op the transpose
+// with TA_.  2 x 2 outputs per thread: half the LDS reads of one output per
+// thread, which bound the product.  `keep(i, j, v)` stores an entry.
+template <int RP, int NT, bool TA_, typename F>
+__device__ __forceinline__ void small_mm(const double* A, const double* B, F keep) {
+  constexpr int LD = RP + 1;
+  constexpr int W = RP % 2 ? 1 : 2;   // outputs per side
+  constexpr int S = RP / W;
+  for (int e = threadIdx.x; e < S * S; e += NT) {
+    const int i0 = e / S * W, j0 = e % S * W;
+    double c[W][W] = {};
+#pragma unroll
+    for (int l = 0; l < RP; ++l) {
+      double x[W], y[W];
+#pragma unroll
+      for (int u = 0; u < W; ++u) {
+        x[u] = TA_ ? A[l * LD + i0 + u] : A[(i0 + u) * LD + l];
+        y[u] = B[l * LD + j0 + u];
+      }
+#pragma unroll
+      for (int u = 0; u < W; ++u)
+#pragma unroll
+        for (int v = 0; v < W; ++v) c[u][v] = fma(x[u], y[v], c[u][v]);
+    }
+#pragma unroll
+    for (int u = 0; u < W; ++u)
+#pragma unroll
+      for (int v = 0; v < W; ++v) keep(i0 + u, j0 + v, c[u][v]);
+  }
+}
+
+// Two-sided cyclic Jacobi on the symmetric matrix G (LDS, stride RP + 1),
+// accumulating V <- V J.  G is zero outside its leading active block and V is
 // the identity there, so the sweeps run over the full RP x RP at compile-time
 // sizes: a pair that touches the padding has a_pq = 0 and is never rotated.
-// Parallel over disjoint pairs in each round: the rotations of a round are
-// computed first, then one pass applies them, a thread per 2 x 2 block of A
-// (the column rotation of the block's column pair, then the row rotation of
-// its row pair) and a thread per (row, pair) of V.  The rotation itself is
-// one short FP64 chain (reciprocal square roots refined by Newton steps,
-// thresholds compared on squares): the rounds are latency-bound.
-template <int RP>
-__device__ void jacobi_eig(double* A, double* V, int n, double* cs, int* rot) {
+//
+// Bound: latency.  A round is one LDS round trip, the chain of a rotation and
+// one barrier.  The matrix is kept in slots, so that the pairs of every round
+// are the slots (2k, 2k + 1): an item of A reads its 2 x 2 block and the
+// diagonal blocks of its two pairs, computes both rotations itself, and writes
+// its entries to the slots of the next round in the other buffer, where they
+// are moved by the one permutation that steps the round-robin (circle
+// method).  After RP - 1 rounds every index is back in its slot.  Only the
+// blocks on and above the diagonal are kept (RP <= 20: one wave).  The other
+// waves apply the rotations to V one round later, beside the next round of A.
+// The form before (rotations by one wave, handed over through LDS, applied in
+// place; two barriers and twice the LDS trips) took about 1 us per round;
+// core at RP = 20: 68 to 78 -> 43 us, RP = 8: 32 -> 21 us.
+//
+// G holds the eigenvalues on its diagonal afterwards; the eigenvectors are
+// the columns of the returned buffer (V or V1).  A0, A1, V1: scratch of the
+// size of G; cs: 2 RP doubles.
+template <int RP, int NT>
+__device__ __forceinline__ double* jacobi_eig(double* G, double* V, double* A0, double* A1,
+                                              double* V1, double* cs, int* rot) {
+  if constexpr (RP == 1) {
+    return V;
+  } else {
+    constexpr int LD = RP + 1;
+    constexpr int NP = RP / 2;
+    constexpr int NA = jacobi_blocks<RP>();
+    constexpr int NAP = (NA + 63) / 64 * 64;
+    constexpr int NV = RP * NP;
+    constexpr int VT = NT - NAP;               // threads of V
+    constexpr int IPT = (NV + VT - 1) / VT;    // items of V per thread
+    static_assert(RP % 2 == 0 && VT >= 64, "pairs, and a wave for V");
+    const int tid = threadIdx.x;
+    // slot of circle position j, and the slot that slot s moves to
+    auto slot = [](int j) { return j < NP ? 2 * j : 2 * (RP - 1 - j) + 1; };
+    auto step = [&](int s) {
+      const int j = (s & 1) ? RP - 1 - (s >> 1) : s >> 1;
+      return slot(j == 0 ? 0 : (j == 1 ? RP - 1 : j - 1));
+    };
+    // addresses of this thread's item of A, the same in every round
+    int src = 0, low = 0, d1 = 0, d2 = 0, w[4] = {}, diag = -1;
+    if (tid < NA) {
+      int k1 = 0, f = tid;
+      while (f >= NP - k1) { f -= NP - k1; ++k1; }
+      const int k2 = k1 + f;
+      diag = k1 == k2 ? k1 : -1;
+      src = 2 * k1 * LD + 2 * k2;
+      low = k1 == k2 ? src + 1 : src + LD;   // below the diagonal: the entry above it
+      d1 = 2 * k1 * (LD + 1);
+      d2 = 2 * k2 * (LD + 1);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int i = step(2 * k1 + (x >> 1)), j = step(2 * k2 + (x & 1));
+        w[x] = i < j ? i * LD + j : j * LD + i;
+      }
+    }
+    // ... and of V: (row, pair)
+    int vs[IPT], vk[IPT], vw[IPT][2];
+#pragma unroll
+    for (int u = 0; u < IPT; ++u) {
+      const int f = tid - NAP + u * VT, i = f / NP, k = f % NP;
+      vs[u] = f >= 0 && f < NV ? i * LD + 2 * k : -1;
+      vk[u] = 2 * k;
+      vw[u][0] = i * LD + step(2 * k);
+      vw[u][1] = i * LD + step(2 * k + 1);
+    }
+    for (int e = tid; e < RP * RP; e += NT) {
+      const int i = e / RP, j = e % RP;
+      A0[slot(i) * LD + slot(j)] = G[i * LD + j];
+      V1[i * LD + slot(j)] = V[i * LD + j];
+    }
+    if (tid < 2) rot[tid] = 0;
+    __syncthreads();
+    double *Ac = A0, *An = A1, *Vc = V1, *Vn = V, *cw = cs, *cr = cs + RP;
+    auto apply_v = [&](const double* q) {
+#pragma unroll
+      for (int u = 0; u < IPT; ++u) {
+        if (vs[u] < 0) continue;
+        const double x = Vc[vs[u]], y = Vc[vs[u] + 1];
+        const double c = q[vk[u]], s = q[vk[u] + 1];
+        Vn[vw[u][0]] = fma(c, x, -(s * y));
+        Vn[vw[u][1]] = fma(s, x, c * y);
+      }
+    };
+    auto swap = [](double*& x, double*& y) { double* z = x; x = y; y = z; };
+    for (int sweep = 0; sweep < 40; ++sweep) {
+      bool any = false, anybig = false;
+      for (int round = 0; round < RP - 1; ++round) {
+        if (tid < NAP) {
+          if (tid < NA) {
+            // A <- J^T A J on the block (row pair k1) x (column pair k2)
+            const double app[2] = {Ac[d1], Ac[d2]};
+            const double apq[2] = {Ac[d1 + 1], Ac[d2 + 1]};
+            const double aqq[2] = {Ac[d1 + LD + 1], Ac[d2 + LD + 1]};
+            const double a0 = Ac[src], b0 = Ac[src + 1], g0 = Ac[low], e0 = Ac[src + LD + 1];
+            double c[2], s[2];
+            bool did[2], big[2];
+            jacobi_rot2(app, aqq, apq, c, s, did, big);
+            const double a2 = fma(c[1], a0, -(s[1] * b0)), b2 = fma(s[1], a0, c[1] * b0);
+            const double g2 = fma(c[1], g0, -(s[1] * e0)), e2 = fma(s[1], g0, c[1] * e0);
+            An[w[0]] = fma(c[0], a2, -(s[0] * g2));
+            An[w[1]] = fma(c[0], b2, -(s[0] * e2));
+            An[w[2]] = fma(s[0], a2, c[0] * g2);
+            An[w[3]] = fma(s[0], b2, c[0] * e2);
+            if (diag >= 0) {
+              cw[2 * diag] = c[0];
+              cw[2 * diag + 1] = s[0];
+              any |= did[0];
+              anybig |= big[0];
+            }
+          }
+        } else if (sweep + round > 0) {
+          apply_v(cr);
+        }
+        if (round == RP - 2) {
+          if (any) rot[0] = 1;
+          if (anybig) rot[1] = 1;
+        }
+        __syncthreads();
+        swap(Ac, An);
+        swap(cw, cr);
+        if (sweep + round > 0) swap(Vc, Vn);
+      }
+      // converged when nothing was rotated, or by little enough
+      if (rot[0] == 0 || rot[1] == 0) break;
+      __syncthreads();
+      // (the next writes of rot come a barrier later, or from this thread)
+      if (tid < 2) rot[tid] = 0;
+    }
+    if (tid >= NAP) apply_v(cr);
+    __syncthreads();
+    swap(Vc, Vn);
+    for (int e = tid; e < RP * RP; e += NT) {
+      const int i = e / RP, j = e % RP;
+      if (i == j) G[i * LD + i] = Ac[slot(i) * (LD + 1)];
+      Vn[i * LD + j] = Vc[i * LD + slot(j)];
+    }
+    __syncthreads();
+    return Vn;
+  }
+}
+
+// In-place form for the batched core, whose problems keep their rounding: its
+// FP32 results follow the last bits of this solver where small eigenvalues
+// are noise.  One wave per problem (48 items a round at RP = 8, no barrier
+// between waves; with 384 threads per problem 40 us for 32 problems, now
+// 35).  The rotations of a round are computed first, then one pass applies
+// them, a thread per 2 x 2 block of A (the column rotation of the block's
+// column pair, then the row rotation of its row pair) and a thread per (row,
+// pair) of V.
+template <int RP, int NT>
+__device__ __forceinline__ void jacobi_eig_inplace(double* A, double* V, double* cs, int* rot) {
   constexpr int LD = RP + 1;
   constexpr int N = (RP + 1) & ~1;
   constexpr int NP = N / 2;
   constexpr int NBLK = NP * NP;
   __shared__ int pq[2 * NP];
-  (void)n;
   auto pos = [](int i, int round) {
     if (i == 0) return 0;
     int x = i - 1 + round;
@@ -283,7 +516,7 @@ __device__ void jacobi_eig(double* A, double* V, int n, double* cs, int* rot) {
         nbig += __popcll(__ballot(big));
       }
       __syncthreads();
-      for (int e = threadIdx.x; e < NBLK + RP * NP; e += blockDim.x) {
+      for (int e = threadIdx.x; e < NBLK + RP * NP; e += NT) {
         if (e >= NBLK) {
           // V <- V J
           const int f = e - NBLK;
@@ -389,93 +622,59 @@ __device__ void jacobi_svd_values(double* M, int n, double* out, double* cs, int
   __syncthreads();
 }
 
-// ---------------------------------------------------------------------------
-// Core of the low-rank step.  Inputs: Gpart of B' = D Y_q (so B = B' T),
-// st->T, st->R2.  Output: K' = T K in the panel type, such that
-// U_L = B' K' and L = U_L Q2^T.
-// ---------------------------------------------------------------------------
-template <typename TA, int RP>
-__device__ void core_body(const double* __restrict__ Gpart, int nparts, SmallState* st, int p,
-                          double rank_tol, int t_identity, TA* k_panel) {
+// Rank check on R2 (A2^T Y1 = R2^T R2), given in W (LDS, stride RP + 1; may be
+// overwritten): the number of leading singular values that count.  H, fk, sv,
+// cs, rot: scratch.
+template <int RP, int NT>
+__device__ __forceinline__ void core_rank(double* W, double* H, double* fk, double* sv, double* cs,
+                                          int* rot, int n, double rank_tol, int* keep_out) {
   constexpr int LD = RP + 1;
-  __shared__ double G[RP * LD];
-  __shared__ double H[RP * LD];
-  __shared__ double T[RP * LD];
-  __shared__ double V[RP * LD];
-  __shared__ double W[RP * LD];
-  __shared__ double cs[4 * 16 + 4];
-  __shared__ double ev[RP];
-  __shared__ double fk[RP];
-  __shared__ double sv[RP];
-  __shared__ int order[RP];
-  __shared__ int rot[2];
-  __shared__ int sh_keep;
-  __shared__ double red[4];
-  __shared__ double redA[kSmallThreads / 64], redB[kSmallThreads / 64];
+  __shared__ double red[2];
+  __shared__ double redA[NT / 64], redB[NT / 64];
   const int tid = threadIdx.x;
-  const int n = st->r_eff;             // active leading columns
-  for (int e = tid; e < RP * RP; e += blockDim.x) {
-    double s = 0.0;
-    s = sum_parts(Gpart, nparts, RP * RP, e);
-    const int i = e / RP, j = e % RP;
-    G[i * LD + j] = s;
-    T[i * LD + j] = t_identity ? (i == j ? 1.0 : 0.0) : st->T[e];
-    W[i * LD + j] = st->R2[e];
-  }
-  __syncthreads();
-
-  // ---- rank check on R2 (A2^T Y1 = R2^T R2) ----
   // Certificate first: s_min(R2) >= 1/||R2^{-1}||_F and s_max <= ||R2||_F.
   // R2^{-1} (upper triangular, active block) by back substitution, one lane
   // per column in registers, into H; a zero diagonal fails the certificate.
-  if (tid == 0) {
-    int ok = n > 0;
-    for (int i = 0; i < n; ++i)
-      if (!(W[i * LD + i] != 0.0)) ok = 0;
-    red[1] = ok;
-    sh_keep = n;
-  }
-  for (int e = tid; e < RP * RP; e += blockDim.x) {
-    const int i = e / RP, c = e % RP;
-    H[i * LD + c] = (i == c) ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  if (tid < n) fk[tid] = 1.0 / W[tid * LD + tid];
-  __syncthreads();
-  if (red[1] != 0.0 && tid < n) {
-    // column tid of R2^{-1}: each lane substitutes its own column in registers
-    double h[RP];
+  if (tid < 64) {
+    const double dg = tid < n ? W[tid * LD + tid] : 1.0;
+    if (tid < RP) fk[tid] = tid < n ? 1.0 / dg : 0.0;
+    const bool ok = n > 0 && __ballot(!(dg != 0.0)) == 0ull;
+    if (tid == 0) {
+      red[1] = ok ? 1.0 : 0.0;
+      *keep_out = n;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (tid < RP) {
+      double h[RP];
 #pragma unroll
-    for (int i = 0; i < RP; ++i) h[i] = (i == tid) ? 1.0 : 0.0;
+      for (int i = 0; i < RP; ++i) h[i] = (i == tid) ? 1.0 : 0.0;
 #pragma unroll
-    for (int i = RP - 1; i >= 0; --i) {
-      if (i < n) {
-        h[i] *= fk[i];
+      for (int i = RP - 1; i >= 0; --i) {
+        h[i] *= fk[i];   // past n: zero
 #pragma unroll
         for (int l = 0; l < i; ++l) h[l] -= W[l * LD + i] * h[i];
       }
-    }
 #pragma unroll
-    for (int i = 0; i < RP; ++i) H[i * LD + tid] = h[i];
+      for (int i = 0; i < RP; ++i) H[i * LD + tid] = h[i];
+    }
   }
   __syncthreads();
   {
     double fr = 0.0, fi = 0.0;
-    for (int e = tid; e < n * n; e += blockDim.x) {
-      const int i = e / n, c = e % n;
-      if (c >= i) {
+    for (int e = tid; e < RP * RP; e += NT) {
+      const int i = e / RP, c = e % RP;
+      if (c >= i && c < n) {
         fr += W[i * LD + c] * W[i * LD + c];
         fi += H[i * LD + c] * H[i * LD + c];
       }
     }
     fr = wave_sum(fr);
     fi = wave_sum(fi);
-    __syncthreads();
     if ((tid & 63) == 0) { redA[tid >> 6] = fr; redB[tid >> 6] = fi; }
     __syncthreads();
     if (tid == 0) {
       double a = 0, b = 0;
-      for (int w = 0; w < (int)(blockDim.x >> 6); ++w) { a += redA[w]; b += redB[w]; }
+      for (int w = 0; w < NT / 64; ++w) { a += redA[w]; b += redB[w]; }
       const bool ok = red[1] != 0.0 && isfinite(a) && isfinite(b) && (1.0 / b) > rank_tol * a;
       red[0] = ok ? 1.0 : 0.0;
     }
@@ -489,57 +688,80 @@ __device__ void core_body(const double* __restrict__ Gpart, int nparts, SmallSta
       int keep = 0;
       for (int i = 0; i < n; ++i)
         if (smax > 0.0 && sv[i] * sv[i] > rank_tol * smax * smax) ++keep;
-      sh_keep = keep;
+      *keep_out = keep;
     }
     __syncthreads();
   }
+}
 
-  // ---- G_B = T^T G' T on the active block ----
-  for (int e = tid; e < RP * RP; e += blockDim.x) {
-    const int i = e / RP, j = e % RP;
+// ---------------------------------------------------------------------------
+// Core of the low-rank step.  Inputs: Gpart of B' = D Y_q (so B = B' T),
+// st->T, st->R2.  Output: K' = T K in the panel type, such that
+// U_L = B' K' and L = U_L Q2^T.
+// ---------------------------------------------------------------------------
+template <typename TA, int RP, int NT>
+__device__ __forceinline__ void core_body(const double* __restrict__ Gpart, int nparts, SmallState* st, int p,
+                          double rank_tol, int t_identity, TA* k_panel) {
+  constexpr int LD = RP + 1;
+  __shared__ double G[RP * LD];
+  __shared__ double H[RP * LD];
+  __shared__ double T[RP * LD];
+  __shared__ double V[RP * LD];
+  __shared__ double W[RP * LD];
+  __shared__ double V1[RP * LD];
+  __shared__ double cs[4 * 16 + 4];
+  __shared__ double ev[RP];
+  __shared__ double fk[RP];
+  __shared__ double sv[RP];
+  __shared__ int order[RP];
+  __shared__ int rot[2];
+  __shared__ int sh_keep;
+  const int tid = threadIdx.x;
+  const int n = st->r_eff;             // active leading columns
+  for (int e = tid; e < RP * RP; e += NT) {
     double s = 0.0;
-    for (int l = 0; l <= j; ++l) s += G[i * LD + l] * T[l * LD + j];
-    H[i * LD + j] = s;
+    s = sum_parts(Gpart, nparts, RP * RP, e);
+    const int i = e / RP, j = e % RP;
+    G[i * LD + j] = s;
+    T[i * LD + j] = t_identity ? (i == j ? 1.0 : 0.0) : st->T[e];
+    W[i * LD + j] = st->R2[e];
   }
   __syncthreads();
-  for (int e = tid; e < RP * RP; e += blockDim.x) {
-    const int i = e / RP, j = e % RP;
-    double s = 0.0;
-    for (int l = 0; l <= i; ++l) s += T[l * LD + i] * H[l * LD + j];
-    W[i * LD + j] = (i < n && j < n) ? s : 0.0;
-  }
-  __syncthreads();
-  // symmetrise and set V (warm start from the previous iteration if valid)
+
+  core_rank<RP, NT>(W, H, fk, sv, cs, rot, n, rank_tol, &sh_keep);
+
+  // ---- A = M^T G' M on the active block, M = T or, with a warm start from
+  // the previous iteration's eigenvectors, T V ----
   const int warm = st->v_valid;
-  for (int e = tid; e < RP * RP; e += blockDim.x) {
+  for (int e = tid; e < RP * RP; e += NT) {
     const int i = e / RP, j = e % RP;
-    G[i * LD + j] = 0.5 * (W[i * LD + j] + W[j * LD + i]);
     V[i * LD + j] = warm ? st->V[e] : (i == j ? 1.0 : 0.0);
   }
   __syncthreads();
+  const double* M = T;
   if (warm) {
-    // A = V^T G V
-    for (int e = tid; e < RP * RP; e += blockDim.x) {
-      const int i = e / RP, j = e % RP;
-      double s = 0.0;
-      for (int l = 0; l < n; ++l) s += G[i * LD + l] * V[l * LD + j];
-      H[i * LD + j] = s;
-    }
+    small_mm<RP, NT, false>(T, V, [&](int i, int j, double v) { V1[i * LD + j] = v; });
     __syncthreads();
-    for (int e = tid; e < RP * RP; e += blockDim.x) {
-      const int i = e / RP, j = e % RP;
-      double s = 0.0;
-      for (int l = 0; l < n; ++l) s += V[l * LD + i] * H[l * LD + j];
-      W[i * LD + j] = s;
-    }
-    __syncthreads();
-    for (int e = tid; e < RP * RP; e += blockDim.x) {
-      const int i = e / RP, j = e % RP;
-      G[i * LD + j] = 0.5 * (W[i * LD + j] + W[j * LD + i]);
-    }
-    __syncthreads();
+    M = V1;
   }
-  jacobi_eig<RP>(G, V, n, cs, rot);
+  small_mm<RP, NT, false>(G, M, [&](int i, int j, double v) { H[i * LD + j] = v; });
+  __syncthreads();
+  small_mm<RP, NT, true>(M, H, [&](int i, int j, double v) {
+    W[i * LD + j] = (i < n && j < n) ? v : 0.0;
+  });
+  __syncthreads();
+  // symmetrised, and scaled by a power of two to a largest diagonal of about 1
+  double mx = 0.0;
+#pragma unroll
+  for (int i = 0; i < RP; ++i) mx = fmax(mx, fabs(W[i * LD + i]));
+  int sce = 0;
+  if (mx > 0.0 && isfinite(mx)) frexp(mx, &sce);
+  for (int e = tid; e < RP * RP; e += NT) {
+    const int i = e / RP, j = e % RP;
+    G[i * LD + j] = ldexp(0.5 * (W[i * LD + j] + W[j * LD + i]), -sce);
+  }
+  __syncthreads();
+  const double* E = jacobi_eig<RP, NT>(G, V, H, W, V1, cs, rot);
   // sort eigenvalues descending (rank of each by counting; ties by index)
   if (tid < n) {
     const double mine = G[tid * LD + tid];
@@ -549,40 +771,38 @@ __device__ void core_body(const double* __restrict__ Gpart, int nparts, SmallSta
       rank += (o > mine || (o == mine && j < tid)) ? 1 : 0;
     }
     order[rank] = tid;
-    ev[rank] = mine;
+    ev[rank] = ldexp(mine, sce);
   }
   __syncthreads();
   const int keep = sh_keep;
   // K = sum_{i < keep, ev_i > 0} v_i ev_i^{(1-p)/(2p)} v_i^T
   const double ex = (1.0 - (double)p) / (2.0 * (double)p);
-  if (tid < n) {
-    const double lam = ev[tid];
+  if (tid < RP) {
+    const double lam = tid < n ? ev[tid] : 0.0;
     fk[tid] = (tid < keep && lam > 0.0) ? ((p == 1) ? 1.0 : pow(lam, ex)) : 0.0;
+    if (tid >= n) order[tid] = tid;
   }
   __syncthreads();
-  for (int e = tid; e < RP * RP; e += blockDim.x) {
-    const int a = e / RP, b = e % RP;
-    double s = 0.0;
-    if (a < n && b < n) {
-      for (int i = 0; i < keep; ++i) {
-        if (!(ev[i] > 0.0)) continue;
-        s += V[a * LD + order[i]] * fk[i] * V[b * LD + order[i]];
-      }
-    }
-    H[a * LD + b] = s;
-  }
-  __syncthreads();
-  // K' = T K ; store eigenvectors (sorted) for the next warm start
-  int bad = 0;
-  for (int e = tid; e < RP * RP; e += blockDim.x) {
+  // E's columns in descending order, and those columns times fk, transposed
+  for (int e = tid; e < RP * RP; e += NT) {
     const int i = e / RP, j = e % RP;
-    double s = 0.0;
-    for (int l = i; l < RP; ++l) s += T[i * LD + l] * H[l * LD + j];
-    if (!isfinite(s)) bad = 1;
-    st->K[e] = s;
-    k_panel[e] = (TA)s;
-    st->V[e] = (j < n && i < n) ? V[i * LD + order[j]] : (i == j ? 1.0 : 0.0);
+    const double x = E[i * LD + order[j]];
+    G[j * LD + i] = x;
+    W[j * LD + i] = x * fk[j];   // fk is zero where nothing is kept
+    st->V[e] = (j < n && i < n) ? x : (i == j ? 1.0 : 0.0);
   }
+  __syncthreads();
+  small_mm<RP, NT, true>(G, W, [&](int i, int j, double v) {
+    H[i * LD + j] = (i < n && j < n) ? v : 0.0;
+  });
+  __syncthreads();
+  // K' = T K ; the sorted eigenvectors are the next warm start
+  int bad = 0;
+  small_mm<RP, NT, false>(T, H, [&](int i, int j, double v) {
+    if (!isfinite(v)) bad = 1;
+    st->K[i * RP + j] = v;
+    k_panel[i * RP + j] = (TA)v;
+  });
   if (bad) atomicOr(&st->flags, 1);
   if (tid < RP) {
     st->sigma[tid] = (tid < n && ev[tid] > 0.0) ? sqrt(ev[tid]) : 0.0;
@@ -599,11 +819,11 @@ __device__ void core_body(const double* __restrict__ Gpart, int nparts, SmallSta
 }
 
 template <typename TA, int RP>
-__global__ __launch_bounds__(kSmallThreads) void k_core(const double* __restrict__ Gpart,
+__global__ __launch_bounds__(core_threads<RP>()) void k_core(const double* __restrict__ Gpart,
                                                         int nparts, SmallState* st, int p,
                                                         double rank_tol, int t_identity,
                                                         TA* k_panel) {
-  core_body<TA, RP>(Gpart, nparts, st, p, rank_tol, t_identity, k_panel);
+  core_body<TA, RP, core_threads<RP>()>(Gpart, nparts, st, p, rank_tol, t_identity, k_panel);
 }
 
 __global__ void k_small_init(SmallState* st, int r) {
@@ -655,10 +875,10 @@ void launch_core(const Launch& L, bool f64, int rp, const double* Gpart,
                  int t_identity, void* k_panel) {
   GODEC_RP_SWITCH(rp, {
     if (f64)
-      hipLaunchKernelGGL((k_core<double, RP>), dim3(1), dim3(kSmallThreads), 0, L.stream, Gpart,
+      hipLaunchKernelGGL((k_core<double, RP>), dim3(1), dim3(core_threads<RP>()), 0, L.stream, Gpart,
                          nparts, st, p, rank_tol, t_identity, (double*)k_panel);
     else
-      hipLaunchKernelGGL((k_core<float, RP>), dim3(1), dim3(kSmallThreads), 0, L.stream, Gpart,
+      hipLaunchKernelGGL((k_core<float, RP>), dim3(1), dim3(core_threads<RP>()), 0, L.stream, Gpart,
                          nparts, st, p, rank_tol, t_identity, (float*)k_panel);
   });
 }
@@ -740,14 +960,149 @@ __global__ __launch_bounds__(256) void kb_chol(const BProb* __restrict__ probs,
   }
 }
 
+// The same for the batched path (jacobi_eig_inplace).
+template <typename TA, int RP, int NT>
+__device__ __forceinline__ void core_body_inplace(const double* __restrict__ Gpart, int nparts, SmallState* st, int p,
+                          double rank_tol, int t_identity, TA* k_panel) {
+  constexpr int LD = RP + 1;
+  __shared__ double G[RP * LD];
+  __shared__ double H[RP * LD];
+  __shared__ double T[RP * LD];
+  __shared__ double V[RP * LD];
+  __shared__ double W[RP * LD];
+  __shared__ double cs[4 * 16 + 4];
+  __shared__ double ev[RP];
+  __shared__ double fk[RP];
+  __shared__ double sv[RP];
+  __shared__ int order[RP];
+  __shared__ int rot[2];
+  __shared__ int sh_keep;
+  const int tid = threadIdx.x;
+  const int n = st->r_eff;             // active leading columns
+  for (int e = tid; e < RP * RP; e += NT) {
+    double s = 0.0;
+    s = sum_parts(Gpart, nparts, RP * RP, e);
+    const int i = e / RP, j = e % RP;
+    G[i * LD + j] = s;
+    T[i * LD + j] = t_identity ? (i == j ? 1.0 : 0.0) : st->T[e];
+    W[i * LD + j] = st->R2[e];
+  }
+  __syncthreads();
+
+  core_rank<RP, NT>(W, H, fk, sv, cs, rot, n, rank_tol, &sh_keep);
+
+  // ---- G_B = T^T G' T on the active block ----
+  for (int e = tid; e < RP * RP; e += NT) {
+    const int i = e / RP, j = e % RP;
+    double s = 0.0;
+    for (int l = 0; l <= j; ++l) s += G[i * LD + l] * T[l * LD + j];
+    H[i * LD + j] = s;
+  }
+  __syncthreads();
+  for (int e = tid; e < RP * RP; e += NT) {
+    const int i = e / RP, j = e % RP;
+    double s = 0.0;
+    for (int l = 0; l <= i; ++l) s += T[l * LD + i] * H[l * LD + j];
+    W[i * LD + j] = (i < n && j < n) ? s : 0.0;
+  }
+  __syncthreads();
+  // symmetrise and set V (warm start from the previous iteration if valid)
+  const int warm = st->v_valid;
+  for (int e = tid; e < RP * RP; e += NT) {
+    const int i = e / RP, j = e % RP;
+    G[i * LD + j] = 0.5 * (W[i * LD + j] + W[j * LD + i]);
+    V[i * LD + j] = warm ? st->V[e] : (i == j ? 1.0 : 0.0);
+  }
+  __syncthreads();
+  if (warm) {
+    // A = V^T G V
+    for (int e = tid; e < RP * RP; e += NT) {
+      const int i = e / RP, j = e % RP;
+      double s = 0.0;
+      for (int l = 0; l < n; ++l) s += G[i * LD + l] * V[l * LD + j];
+      H[i * LD + j] = s;
+    }
+    __syncthreads();
+    for (int e = tid; e < RP * RP; e += NT) {
+      const int i = e / RP, j = e % RP;
+      double s = 0.0;
+      for (int l = 0; l < n; ++l) s += V[l * LD + i] * H[l * LD + j];
+      W[i * LD + j] = s;
+    }
+    __syncthreads();
+    for (int e = tid; e < RP * RP; e += NT) {
+      const int i = e / RP, j = e % RP;
+      G[i * LD + j] = 0.5 * (W[i * LD + j] + W[j * LD + i]);
+    }
+    __syncthreads();
+  }
+  jacobi_eig_inplace<RP, NT>(G, V, cs, rot);
+  // sort eigenvalues descending (rank of each by counting; ties by index)
+  if (tid < n) {
+    const double mine = G[tid * LD + tid];
+    int rank = 0;
+    for (int j = 0; j < n; ++j) {
+      const double o = G[j * LD + j];
+      rank += (o > mine || (o == mine && j < tid)) ? 1 : 0;
+    }
+    order[rank] = tid;
+    ev[rank] = mine;
+  }
+  __syncthreads();
+  const int keep = sh_keep;
+  // K = sum_{i < keep, ev_i > 0} v_i ev_i^{(1-p)/(2p)} v_i^T
+  const double ex = (1.0 - (double)p) / (2.0 * (double)p);
+  if (tid < n) {
+    const double lam = ev[tid];
+    fk[tid] = (tid < keep && lam > 0.0) ? ((p == 1) ? 1.0 : pow(lam, ex)) : 0.0;
+  }
+  __syncthreads();
+  for (int e = tid; e < RP * RP; e += NT) {
+    const int a = e / RP, b = e % RP;
+    double s = 0.0;
+    if (a < n && b < n) {
+      for (int i = 0; i < keep; ++i) {
+        if (!(ev[i] > 0.0)) continue;
+        s += V[a * LD + order[i]] * fk[i] * V[b * LD + order[i]];
+      }
+    }
+    H[a * LD + b] = s;
+  }
+  __syncthreads();
+  // K' = T K ; store eigenvectors (sorted) for the next warm start
+  int bad = 0;
+  for (int e = tid; e < RP * RP; e += NT) {
+    const int i = e / RP, j = e % RP;
+    double s = 0.0;
+    for (int l = i; l < RP; ++l) s += T[i * LD + l] * H[l * LD + j];
+    if (!isfinite(s)) bad = 1;
+    st->K[e] = s;
+    k_panel[e] = (TA)s;
+    st->V[e] = (j < n && i < n) ? V[i * LD + order[j]] : (i == j ? 1.0 : 0.0);
+  }
+  if (bad) atomicOr(&st->flags, 1);
+  if (tid < RP) {
+    st->sigma[tid] = (tid < n && ev[tid] > 0.0) ? sqrt(ev[tid]) : 0.0;
+    st->sv_c[tid] = 0.0;
+  }
+  if (tid == 0) {
+    st->r_keep = keep;
+    st->v_valid = (keep == n) ? 1 : 0;
+    if (keep < n) {
+      st->r_eff = keep;
+      atomicOr(&st->flags, 2);
+    }
+  }
+}
+
 // Core of the low-rank step per problem: the Gram of B' from the apply
 // pass's partials, then the shared FP64 core (rank certificate, Jacobi
 // eigen-solver, K' = T K into Kp).
-__global__ __launch_bounds__(kSmallThreads) void kb_core(const BProb* __restrict__ probs,
+__global__ __launch_bounds__(64) void kb_core(const BProb* __restrict__ probs,
                                                          const double* __restrict__ gslots,
                                                          int p, int t_identity) {
   const BProb& b = probs[blockIdx.x];
-  core_body<float, RB>(gslots + (int64_t)b.item0 * RB * RB, b.nitems, b.st, p, b.rank_tol,
+  core_body_inplace<float, RB, 64>(gslots + (int64_t)b.item0 * RB * RB, b.nitems, b.st, p, b.rank_tol,
                        t_identity, b.Kp);
 }
 
@@ -771,7 +1126,7 @@ void bl_chol(const Launch& L, const BatchArgs& a, int from_slots, int in, int ou
 }
 
 void bl_core(const Launch& L, const BatchArgs& a, int t_identity) {
-  hipLaunchKernelGGL(kb_core, dim3((unsigned)a.nprob), dim3(kSmallThreads), 0, L.stream, a.probs,
+  hipLaunchKernelGGL(kb_core, dim3((unsigned)a.nprob), dim3(64), 0, L.stream, a.probs,
                      a.gslots, a.p, t_identity);
 }
 

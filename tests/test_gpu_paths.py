@@ -124,6 +124,34 @@ def test_l_update_of_narrow_matrices(m, n, r, q, lstep, dt, tol):
     gd.close()
 
 
+# the r x r eigen-solver: every padded width (one or several waves of items,
+# one or two items per thread), full and padded, cold and warm starts
+@pytest.mark.parametrize("m,n,r,q", [
+    (60, 600, 2, 1), (70, 530, 7, 1), (600, 540, 11, 1), (540, 600, 16, 1), (530, 600, 17, 1),
+    (600, 530, 20, 2), (530, 540, 23, 1), (540, 530, 32, 1), (530, 560, 29, 0)])
+@pytest.mark.parametrize("dt,tol", [(np.float64, 1e-10), (np.float32, 1e-5)])
+def test_core_of_every_width(m, n, r, q, dt, tol):
+    """Three steps against the oracle's update on the library's own S (the
+    bars of the per-step parity tests)."""
+    from oracle import godec_ref as g
+    from oracle.rng_ref import a1_gaussian
+    from paper_1309_0302_amd.binding import GoDec
+    w = wl.tiny(m, n, r, seed=m + n, dtype=dt)
+    gd = GoDec(torch.from_numpy(w.X).to("cuda:0"), r, w.k, q, seed=9)
+    A1 = a1_gaussian(9, n, r)
+    X = w.X.astype(np.float64)
+    D = X.copy()
+    for _ in range(3):
+        gd.step(1)
+        ref = g.brp_power(D, A1, q)
+        assert g.rel_fro(gd.L_dense().cpu().numpy().astype(np.float64), ref.L) <= tol
+        idx, val = (t.cpu().numpy() for t in gd.S())
+        D = X.copy()
+        D.ravel()[idx] -= val
+    assert gd.info()["rank_eff"] == r
+    gd.close()
+
+
 def _mse_identity(X, K, steps):
     """MSE training with one empty label: the sparse step selects from X
     itself, so the input sets the ties.  Yields S after each step."""
