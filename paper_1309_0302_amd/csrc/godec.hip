@@ -78,7 +78,6 @@ struct godec_ctx {
   void *Zt, *Wt;             // 32-row transposed panels for the matrix cores
   float *Wtpart, *Zpart32;   // partial sums of the two MFMA halves
   double* Gpart;
-  GramCtl* gram_ctl;
   SmallState* st;
   SelPlan* plan[2];
   unsigned long long* hist;
@@ -212,8 +211,7 @@ size_t carve(godec_ctx* c, void* base) {
   }
   c->UL = cv.take((size_t)m * rp * ta);
   c->Kp = cv.take((size_t)rp * rp * ta);
-  c->Gpart = (double*)cv.take((size_t)kGramSlots * rp * rp * 8);
-  c->gram_ctl = (GramCtl*)cv.take(sizeof(GramCtl));
+  c->Gpart = (double*)cv.take((size_t)kGramMaxBlocks * rp * rp * 8);
   c->st = (SmallState*)cv.take(sizeof(SmallState));
   c->plan[0] = (SelPlan*)cv.take(sizeof(SelPlan));
   c->plan[1] = (SelPlan*)cv.take(sizeof(SelPlan));
@@ -486,15 +484,15 @@ void gram_pass(godec_ctx* c, DType td, const void* Dsrc, const void* in, bool zt
 // accumulating its R factor into acc (reset when reset != 0).  next_td:
 // type of the matrix-core pass that reads `out` next (its transpose is
 // written to c->Zt), or F64 when none does.
-void chol_qr(godec_ctx* c, const void* in, void* out, double* acc, int reset, DType next_td,
+void chol_qr(godec_ctx* c, void* in, void* out, double* acc, int reset, DType next_td,
              bool from_parts = false) {
   const Launch L = launch_of(c);
-  launch_gram_tree(L, c->f64, c->rp, in, c->ldd, c->Gpart, c->gram_ctl, 1, c->st, acc, reset,
-                   acc == c->st->R2 ? 1 : 0, from_parts ? c->Zpart32 : nullptr,
-                   from_parts ? (int)c->nch_b : 0);
+  const int np = launch_gram_part(L, c->f64, c->rp, in, c->ldd, c->Gpart,
+                                  from_parts ? c->Zpart32 : nullptr,
+                                  from_parts ? (int)c->nch_b : 0);
   const bool zt = !c->f64 && next_td != F64;
-  launch_apply_rinv(L, c->f64, c->rp, in, c->ldd, c->st, out, next_td, zt ? c->Zt : nullptr,
-                    c->ldd);
+  launch_chol_rinv(L, c->f64, c->rp, in, c->ldd, c->Gpart, np, c->st, acc, reset,
+                   acc == c->st->R2 ? 1 : 0, out, next_td, zt ? c->Zt : nullptr, c->ldd);
 }
 
 // A Gram pass and one Cholesky QR step: out = orth(D^T (D in)) via tmp, its
@@ -583,9 +581,8 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
   else
     mfma_apply(c, tdb, Db, in, true, nullptr, (float*)c->Bp);
   // ---- core ----
-  launch_gram_tree(L, c->f64, c->rp, c->Bp, c->m, c->Gpart, c->gram_ctl, 0, c->st, nullptr, 0,
-                   0);
-  launch_core(L, c->f64, c->rp, c->Gpart + (size_t)kGramFinal * c->rp * c->rp, 1, c->st, c->p,
+  const int np = launch_gram_part(L, c->f64, c->rp, c->Bp, c->m, c->Gpart);
+  launch_core(L, c->f64, c->rp, c->Gpart, np, 1, c->st, c->p,
               c->rank_tol, c->q == 0 ? 1 : 0, c->Kp);
   launch_apply_small(L, c->f64, c->rp, c->Bp, c->m, c->Kp, c->UL);
   }
@@ -780,7 +777,6 @@ godec_status godec_init(godec_ctx** out, const void* X_dev, godec_dtype dtype, i
   if (e == hipSuccess) e = hipMemsetAsync(c->plan[0], 0, sizeof(SelPlan), c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->plan[1], 0, sizeof(SelPlan), c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->carry, 0, sizeof(SelCarry), c->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(c->gram_ctl, 0, sizeof(GramCtl), c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->VL, 0, (size_t)c->ldd * c->rp * c->ta, c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->UL, 0, (size_t)c->m * c->rp * c->ta, c->stream);
   if (e != hipSuccess) return cleanup(GODEC_E_DEVICE, hipGetErrorString(e));

@@ -45,7 +45,6 @@ struct godec_grebsmo {
   void *Zt, *Wt;               // transposed panels for the matrix cores (FP32)
   float *Wtpart, *Zpart32;
   double* Gpart;
-  GramCtl* gram_ctl;
   SmallState* st;
   double* part;                // partial triples of the soft pass
   double* stats;               // [0] sum e^2, [1] sum |s|, [2] nnz, [3] ||X||^2
@@ -97,8 +96,7 @@ size_t carve(godec_grebsmo* g, void* base) {
     g->Wtpart = (float*)cv.take((size_t)g->pl.nct_a * 32 * mpad * 4);
     g->Zpart32 = (float*)cv.take((size_t)g->pl.nch_b * ldd * 32 * 4);
   }
-  g->Gpart = (double*)cv.take((size_t)kGramSlots * rp * rp * 8);
-  g->gram_ctl = (GramCtl*)cv.take(sizeof(GramCtl));
+  g->Gpart = (double*)cv.take((size_t)kGramMaxBlocks * rp * rp * 8);
   g->st = (SmallState*)cv.take(sizeof(SmallState));
   g->part = (double*)cv.take((size_t)gb_soft_blocks(g->m, g->n) * 3 * 8);
   g->stats = (double*)cv.take(4 * 8);
@@ -116,6 +114,15 @@ godec_status validate(int64_t m, int64_t n, int32_t r, godec_dtype dtype) {
   return GODEC_OK;
 }
 
+// out = orth(in), one Cholesky QR step; optionally its FP32 transpose too.
+void orth(godec_grebsmo* g, void* in, int64_t rows, void* out, void* t = nullptr,
+          int64_t ldt = 0) {
+  const Launch L = launch_of(g);
+  const int np = launch_gram_part(L, g->f64, g->rp, in, rows, g->Gpart);
+  launch_chol_rinv(L, g->f64, g->rp, in, rows, g->Gpart, np, g->st, nullptr, 0, 0, out,
+                   t ? F32 : F64, t, ldt);
+}
+
 // P0 <- orth(src^T (src P0)), one Cholesky QR step (R factor discarded).
 void gram_orth(godec_grebsmo* g, const void* src) {
   const Launch L = launch_of(g);
@@ -131,8 +138,7 @@ void gram_orth(godec_grebsmo* g, const void* src) {
     mfma_mm_b(L, false, src, ldd, mpad, g->Wt, g->Zpart32, g->pl.rc_b, g->pl.nch_b, g->rp);
     mfma_reduce_z(L, g->Zpart32, g->pl.nch_b, ldd, g->rp, (float*)g->P1);
   }
-  launch_gram_tree(L, g->f64, g->rp, g->P1, ldd, g->Gpart, g->gram_ctl, 1, g->st, nullptr, 0, 0);
-  launch_apply_rinv(L, g->f64, g->rp, g->P1, ldd, g->st, g->P0, F64, nullptr, 0);
+  orth(g, g->P1, ldd, g->P0);
 }
 
 // Greedy step of stage g->stages: append orth((R^T R)^power Omega_s) to V^T.
@@ -174,11 +180,8 @@ void inner_step(godec_grebsmo* g, bool last) {
   g->w_ready = false;
   // U = orth(W): two Cholesky QR rounds; the second also writes U^T for the
   // matrix-core pass
-  launch_gram_tree(L, g->f64, g->rp, g->W, m, g->Gpart, g->gram_ctl, 1, g->st, nullptr, 0, 0);
-  launch_apply_rinv(L, g->f64, g->rp, g->W, m, g->st, g->U, F64, nullptr, 0);
-  launch_gram_tree(L, g->f64, g->rp, g->U, m, g->Gpart, g->gram_ctl, 1, g->st, nullptr, 0, 0);
-  launch_apply_rinv(L, g->f64, g->rp, g->U, m, g->st, g->W, g->f64 ? F64 : F32,
-                    g->f64 ? nullptr : g->Wt, mpad);
+  orth(g, g->W, m, g->U);
+  orth(g, g->U, m, g->W, g->f64 ? nullptr : g->Wt, mpad);
   std::swap(g->U, g->W);
   // V^T = D^T U
   if (g->f64) {
@@ -286,7 +289,6 @@ godec_status godec_grebsmo_init(godec_grebsmo** out, const void* X_dev, godec_dt
   if (e == hipSuccess) e = hipMemsetAsync(g->U, 0, (size_t)mpad * g->rp * g->ta, g->stream);
   if (e == hipSuccess) e = hipMemsetAsync(g->W, 0, (size_t)mpad * g->rp * g->ta, g->stream);
   if (e == hipSuccess && g->Wt) e = hipMemsetAsync(g->Wt, 0, (size_t)32 * mpad * 4, g->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(g->gram_ctl, 0, sizeof(GramCtl), g->stream);
   if (e == hipSuccess) e = hipMemsetAsync(g->stats, 0, 4 * 8, g->stream);
   if (e == hipSuccess) e = hipMemsetAsync(g->nonfinite, 0, 8, g->stream);
   if (e != hipSuccess) return cleanup(GODEC_E_DEVICE, hipGetErrorString(e));

@@ -117,38 +117,25 @@ void launch_apply_t(const Launch& L, DType td, int rp, const void* D,
 void launch_reduce_chunks(const Launch& L, bool f64, int rp,
                           const void* Zpart, int64_t nchunks, int64_t rows,
                           void* Zo);
-// Gram G = P^T P (FP64) of a rows x RP panel in one launch: row blocks
-// write partials, a two-level arrival tree adds them in a fixed order, and
-// the final G lands in Gpart slot kGramFinal.  With `chol` set, the last
-// block then runs the Cholesky step of Cholesky QR (G = R^T R with
-// dependent-column detection) and stores R and 1/diag(R) in st->Rq,
-// st->dinv, and folds R into acc (acc <- R acc, or R when reset_acc),
-// rescaled by a power of two when normalise is set.  ctl must be zero
-// before the first launch; every launch leaves it zero.
-constexpr int kGramRows = 64;        // rows per block
-constexpr int kGramGroup = 16;       // blocks per first-level group
-constexpr int kGramMaxBlocks = 256;
-constexpr int kGramFinal = kGramMaxBlocks + kGramMaxBlocks / kGramGroup;
-constexpr int kGramSlots = kGramFinal + 1;   // partial slots of RP x RP doubles
-constexpr int kGramMaxChunks = 16;   // row-chunk partials k_gram_tree can add up
-struct GramCtl {
-  unsigned int grp[kGramMaxBlocks / kGramGroup];
-  unsigned int top;
-  unsigned int pad[15];
-};
-// Zpart (optional, FP32 only): form P first as the sum of nch (<= 16)
-// row-chunk partials Zpart (nch x rows x 32, chunk-ascending order) and store
-// it, instead of reading it.
-void launch_gram_tree(const Launch& L, bool f64, int rp, const void* P, int64_t rows,
-                      double* Gpart, GramCtl* ctl, int chol, SmallState* st, double* acc,
-                      int reset_acc, int normalise, const float* Zpart = nullptr,
-                      int nch = 0);
-// Out = P R^{-1} with R = st->Rq (upper triangular; zero rows and dinv = 0 on
-// inactive columns), by forward substitution in FP64, rows x RP in the
-// panel type; when Zt is given, also its transpose (32 x ldz, bf16 or f32,
-// rows >= RP zero) for the next matrix-core pass.
-void launch_apply_rinv(const Launch& L, bool f64, int rp, const void* P, int64_t rows,
-                       const SmallState* st, void* Out, DType zt_type, void* Zt, int64_t ldz);
+// Partial Grams P^T P (FP64) of a rows x RP panel, one per block of rows, in
+// the layout that launch_chol_rinv and launch_core (tiled) read; returns
+// their number.  Zpart (optional, FP32 only): form P first as the sum of nch
+// row-chunk partials Zpart (nch x rows x zpart_stride, chunk-ascending order)
+// and store it, instead of reading it.
+constexpr int kGramRows = 128;       // rows per step of a block
+constexpr int kGramMaxBlocks = 128;  // partials: each block that adds them reads all
+constexpr int kGramMaxChunks = 16;   // row-chunk partials that k_gram_part adds up
+int launch_gram_part(const Launch& L, bool f64, int rp, void* P, int64_t rows, double* Gpart,
+                     const float* Zpart = nullptr, int nch = 0);
+// Out = P R^{-1}, R the Cholesky factor of the summed partials (upper
+// triangular, dependent columns detected: zero columns of Out), rows x RP in
+// the panel type, Out != P; when Zt is given, also its transpose (32 x ldz,
+// bf16 or f32, rows >= RP zero) for the next matrix-core pass.  With acc: acc
+// <- R acc, or R when reset_acc, rescaled by a power of two when normalise.
+void launch_chol_rinv(const Launch& L, bool f64, int rp, const void* P, int64_t rows,
+                      const double* Gpart, int nparts, const SmallState* st, double* acc,
+                      int reset_acc, int normalise, void* Out, DType zt_type, void* Zt,
+                      int64_t ldz);
 // Out = P K  (rows x RP), K is RP x RP in the panel type.
 void launch_apply_small(const Launch& L, bool f64, int rp, const void* P,
                         int64_t rows, const void* K, void* Out);
@@ -158,7 +145,7 @@ void launch_copy_panel(const Launch& L, bool f64, int rp, const double* src,
                        const SmallState* st, void* dst);
 // ---- r x r FP64 kernels (k_small.hip) ----
 void launch_core(const Launch& L, bool f64, int rp, const double* Gpart,
-                 int nparts, SmallState* st, int p, double rank_tol,
+                 int nparts, int tiled, SmallState* st, int p, double rank_tol,
                  int t_identity, void* k_panel);
 void launch_small_init(const Launch& L, SmallState* st, int r);
 

@@ -47,7 +47,7 @@ __device__ __forceinline__ void chol_prefetch(CholIn<RP>& in, const SmallState* 
 // overwritten with R (LDS scratch for the broadcast reads of R below).  R and
 // the reciprocal diagonal go to Rq (RP x RP) and dinv; acc may be null.
 template <typename TA, int RP>
-__device__ void wave_chol(double* G, double* Rq, double* dinv, double* acc, int reset_acc,
+__device__ __forceinline__ void wave_chol(double* G, double* Rq, double* dinv, double* acc, int reset_acc,
                           int normalise, const CholIn<RP>& in) {
   const int lane = threadIdx.x & 63;
   const bool col = lane < RP;
@@ -127,7 +127,7 @@ __device__ void wave_chol(double* G, double* Rq, double* dinv, double* acc, int 
 }
 
 template <typename TA, int RP>
-__device__ void wave_chol(double* G, SmallState* st, double* acc, int reset_acc,
+__device__ __forceinline__ void wave_chol(double* G, SmallState* st, double* acc, int reset_acc,
                           int normalise) {
   CholIn<RP> in;
   chol_prefetch<RP>(in, st, acc, reset_acc);

@@ -594,7 +594,7 @@ void launch_gram_form(const Launch& L, const GramForm& g) {
     a.reset = j == 0 ? 1 : 0;
   }
   if (!g.proj)
-    launch_core(L, g.f64, g.rp, g.G[cur], a.np / 16, g.st, g.p, g.rank_tol, g.q == 0 ? 1 : 0, g.Kp);
+    launch_core(L, g.f64, g.rp, g.G[cur], a.np / 16, 0, g.st, g.p, g.rank_tol, g.q == 0 ? 1 : 0, g.Kp);
   const double* K = g.proj ? nullptr : g.st->K;
   GF_RP_SWITCH(g.rp, {
     if (g.f64)

@@ -144,44 +144,6 @@ __global__ __launch_bounds__(256) void k_reduce_chunks(const TA* __restrict__ Zp
   Zo[e] = s;
 }
 
-// Out = P R^{-1} by forward substitution in FP64 (x R = p row by row, R
-// upper triangular in st->Rq, 1/diag in st->dinv, zero on inactive
-// columns); optionally also the transposed panel Zt (32 x ldz) in bf16 or
-// f32 for the next matrix-core pass, rows >= RP zero.
-template <typename TA, int RP, typename TT>
-__global__ __launch_bounds__(256) void k_apply_rinv(const TA* __restrict__ P, int64_t rows,
-                                                    const SmallState* __restrict__ st,
-                                                    TA* __restrict__ Out, TT* __restrict__ Zt,
-                                                    int64_t ldz) {
-  __shared__ double rs[RP * RP];
-  __shared__ double di[RP];
-  for (int e = threadIdx.x; e < RP * RP; e += 256) rs[e] = st->Rq[e];
-  if (threadIdx.x < RP) di[threadIdx.x] = st->dinv[threadIdx.x];
-  __syncthreads();
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= rows) return;
-  double x[RP];
-#pragma unroll
-  for (int j = 0; j < RP; ++j) {
-    double s = (double)P[i * RP + j];
-#pragma unroll
-    for (int l = 0; l < j; ++l) s = fma(-x[l], rs[l * RP + j], s);
-    x[j] = s * di[j];
-  }
-#pragma unroll
-  for (int j = 0; j < RP; ++j) Out[i * RP + j] = (TA)x[j];
-  if (Zt != nullptr) {
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      const float v = j < RP ? (float)x[j] : 0.f;
-      if constexpr (sizeof(TT) == 2)
-        Zt[(int64_t)j * ldz + i] = f32_to_bf16(v);
-      else
-        Zt[(int64_t)j * ldz + i] = (TT)v;
-    }
-  }
-}
-
 // Out = P K with K an RP x RP matrix in the panel type.
 template <typename TA, int RP>
 __global__ __launch_bounds__(256) void k_apply_small(const TA* __restrict__ P,
@@ -295,23 +257,6 @@ void launch_reduce_chunks(const Launch& L, bool f64, int rp, const void* Zpart,
   else
     hipLaunchKernelGGL(k_reduce_chunks<float>, dim3(blocks), dim3(256), 0, L.stream,
                        (const float*)Zpart, nchunks, nel, (float*)Zo);
-}
-
-void launch_apply_rinv(const Launch& L, bool f64, int rp, const void* P, int64_t rows,
-                       const SmallState* st, void* Out, DType zt_type, void* Zt, int64_t ldz) {
-  const unsigned blocks = (unsigned)((rows + 255) / 256);
-  GODEC_RP_SWITCH(rp, {
-    if (f64)
-      hipLaunchKernelGGL((k_apply_rinv<double, RP, double>), dim3(blocks), dim3(256), 0,
-                         L.stream, (const double*)P, rows, st, (double*)Out, (double*)nullptr,
-                         ldz);
-    else if (Zt != nullptr && zt_type == BF16)
-      hipLaunchKernelGGL((k_apply_rinv<float, RP, uint16_t>), dim3(blocks), dim3(256), 0,
-                         L.stream, (const float*)P, rows, st, (float*)Out, (uint16_t*)Zt, ldz);
-    else
-      hipLaunchKernelGGL((k_apply_rinv<float, RP, float>), dim3(blocks), dim3(256), 0,
-                         L.stream, (const float*)P, rows, st, (float*)Out, (float*)Zt, ldz);
-  });
 }
 
 void launch_apply_small(const Launch& L, bool f64, int rp, const void* P,

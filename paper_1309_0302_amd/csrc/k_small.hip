@@ -11,6 +11,8 @@
 // Gram) and keeps the product of the R factors in FP64, rescaled by exact
 // powers of two.  B is handled through K = V diag(s^{(1-p)/p}) V^T from
 // the eigen-decomposition of B^T B, so that U_L = B K and V_L = Q2.
+#include <algorithm>
+
 #include "godec_internal.h"
 #include "k_common.h"
 #include "k_chol.h"
@@ -52,164 +54,306 @@ __device__ __forceinline__ double sum_parts(const double* __restrict__ P, int np
 }
 
 // ---------------------------------------------------------------------------
-// Gram of a panel and the Cholesky step of Cholesky QR (k_chol.h).
+// Cholesky QR of a panel in two launches: k_gram_part writes partial Grams,
+// k_chol_rinv adds them, factors the sum and applies R^{-1} to the rows.
 //
-// Block b sums P[i]^T P[i] over its kGramRows-row slice into partial b (each
-// thread owns a 2 x 2 tile of G; the rows are split over NG thread groups
-// when the tiles do not fill the block).  The last block of each group of
-// kGramGroup blocks adds the group's partials, and the last group leader
-// adds the group sums: a fixed order, so G is the same bits on every run.
-// Every load of a reduction level is issued at once, so a level costs one
-// memory round trip.
+// Bound: latency.  Handing the partials over inside one launch (write-through
+// stores, two levels of arrival counters, the last block factors, a second
+// launch for R^{-1}) took 19 + 5.7 us at 10000 x 20, of which 6 us the tree
+// and 6 us the factorisation in a block that runs its code cold.  The kernel
+// boundary does the hand-over, and every block adds the partials and factors
+// on its own: 5.6 + 15 us; 1503 x 20: 17.3 + 5.7 -> 5.6 + 12.7 us; 25 344 x 4:
+// 9.7 + 3.9 -> 4.0 + 4.6 us.
+//
+// A partial holds the 4 x 4 tiles of G on and above the diagonal (whole
+// matrix when RP < 4), added in a fixed order everywhere: G is the same bits
+// on every run.
 // ---------------------------------------------------------------------------
-// With Zpart (FP32 panels only), the panel is first formed here: row i,
-// column c of P is the sum over h < nch of Zpart[(h rows + i) 32 + c] in
+template <int RP>
+struct GramTile {
+  static constexpr int T4 = (RP + 3) / 4;          // tiles per side
+  static constexpr int RW = 4 * T4;                // padded width
+  static constexpr int NT = T4 * (T4 + 1) / 2;     // tiles on and above the diagonal
+  static constexpr int ENT = RP >= 4 ? NT * 16 : RP * RP;   // doubles of a partial
+};
+
+// Tile t in row-major order of the upper triangle.
+template <int T4>
+__device__ __forceinline__ void gram_tile(int t, int& ta, int& tb) {
+  ta = 0;
+  while (t >= T4 - ta) { t -= T4 - ta; ++ta; }
+  tb = ta + t;
+}
+
+// Block b sums P[i]^T P[i] over its `per` rows (a multiple of kGramRows).
+// Each thread owns a 4 x 4 tile (two 16-byte LDS reads per 16 multiply-adds;
+// with 2 x 2 tiles the LDS reads bounded the loop) over the rows of its
+// group.  With Zpart (FP32 panels only), the panel is first formed here: row
+// i, column c of P is the sum over h < nch of Zpart[(h rows + i) zs + c] in
 // ascending h (the row-chunk partials of a matrix-core Gram pass), and is
 // also stored to P.
-
 template <typename TA, int RP>
-__global__ __launch_bounds__(256) void k_gram_tree(const TA* __restrict__ P, int64_t rows,
+__global__ __launch_bounds__(256) void k_gram_part(TA* __restrict__ P, int64_t rows, int64_t per,
                                                    double* __restrict__ Gpart,
-                                                   GramCtl* __restrict__ ctl, int chol,
-                                                   SmallState* st, double* acc, int reset_acc,
-                                                   int normalise,
                                                    const float* __restrict__ Zpart, int nch) {
-  constexpr int RH = (RP + 1) / 2;    // tiles per side
-  constexpr int RW = 2 * RH;          // padded width
-  constexpr int NT = RH * RH;         // tiles
-  constexpr int NG = 256 / NT;        // row groups
-  constexpr int CH = kGramRows;
-  constexpr int E = RP * RP;
-  __shared__ double ps[CH * RW];
-  __shared__ double red[NG * NT * 4];
-  __shared__ int flag;
+  using GT = GramTile<RP>;
+  constexpr int T4 = GT::T4, RW = GT::RW, NT = GT::NT, CH = kGramRows;
+  constexpr int NG = 256 / NT < CH ? 256 / NT : CH;   // row groups
+  constexpr int RS = NT * 16;
+  constexpr int PER = (CH * T4 + 255) / 256;          // 4-column pieces per thread
+  constexpr size_t kPs = sizeof(TA) * CH * RW, kRed = sizeof(double) * NG * RS;
+  __shared__ __align__(16) char buf[kPs > kRed ? kPs : kRed];
+  TA* ps = reinterpret_cast<TA*>(buf);
+  double* red = reinterpret_cast<double*>(buf);
   const int tid = threadIdx.x;
   const int tile = tid % NT, grp = tid / NT;
   const bool active = grp < NG;
-  const int ta = 2 * (tile / RH), tb = 2 * (tile % RH);
-  // ---- partial of this block's rows ----
-  double a00 = 0.0, a01 = 0.0, a10 = 0.0, a11 = 0.0;
-  const int64_t per = (rows + gridDim.x - 1) / gridDim.x;
+  int ta, tb;
+  gram_tile<T4>(tile, ta, tb);
+  double acc[4][4] = {};
   const int64_t r0 = (int64_t)blockIdx.x * per;
   const int64_t r1 = (r0 + per) < rows ? (r0 + per) : rows;
   for (int64_t i0 = r0; i0 < r1; i0 += CH) {
     const int nr = (r1 - i0) < CH ? (int)(r1 - i0) : CH;
-    __syncthreads();
+    TA x[PER][4];
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) x[j][c] = TA(0);
     if (Zpart != nullptr) {
-      // every entry of the thread and every chunk partial in flight at once;
-      // the partials are added in ascending chunk order
-      constexpr int PER = (CH * RW + 255) / 256;
-      float z[PER];
-      bool ok[PER];
-      int64_t off[PER];
+      // four chunk partials of every piece in flight at once
+      constexpr int HB = 4;
+      const int64_t hstride = rows * RW;   // zpart_stride(RP) == RW
+      for (int h0 = 0; h0 < nch; h0 += HB) {
+        float4 v[HB][PER];
 #pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const int e = tid + 256 * j;
-        const int row = e / RW, c = e % RW;
-        ok[j] = e < CH * RW && row < nr && c < RP;
-        off[j] = ok[j] ? (i0 + row) * zpart_stride(RP) + c : 0;
-        z[j] = 0.f;
+        for (int h = 0; h < HB; ++h)
+#pragma unroll
+          for (int j = 0; j < PER; ++j) {
+            const int q = tid + 256 * j;
+            v[h][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (h0 + h < nch && q < nr * T4)
+              v[h][j] = *reinterpret_cast<const float4*>(Zpart + (h0 + h) * hstride + i0 * RW +
+                                                         4 * (int64_t)q);
+          }
+#pragma unroll
+        for (int h = 0; h < HB; ++h)
+#pragma unroll
+          for (int j = 0; j < PER; ++j) {
+            if (h0 + h >= nch) continue;
+            x[j][0] += v[h][j].x;
+            x[j][1] += v[h][j].y;
+            x[j][2] += v[h][j].z;
+            x[j][3] += v[h][j].w;
+          }
       }
-      const int64_t hstride = rows * zpart_stride(RP);
-      float v[kGramMaxChunks][PER];
-#pragma unroll
-      for (int h = 0; h < kGramMaxChunks; ++h)
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-          v[h][j] = (h < nch && ok[j]) ? Zpart[h * hstride + off[j]] : 0.f;
-#pragma unroll
-      for (int h = 0; h < kGramMaxChunks; ++h)
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-          if (h < nch) z[j] += v[h][j];
 #pragma unroll
       for (int j = 0; j < PER; ++j) {
-        const int e = tid + 256 * j;
-        if (e < CH * RW) {
-          const int row = e / RW, c = e % RW;
-          if (ok[j]) const_cast<TA*>(P)[(i0 + row) * RP + c] = (TA)z[j];
-          ps[e] = ok[j] ? (double)z[j] : 0.0;
+        const int q = tid + 256 * j;
+        if (q >= nr * T4) continue;
+        if constexpr (RW == RP) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) P[i0 * RP + 4 * (int64_t)q + c] = x[j][c];
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            if (c < RP) P[(i0 + q) * RP + c] = x[j][c];
+            else x[j][c] = TA(0);
+          }
         }
       }
     } else {
-      for (int e = tid; e < CH * RW; e += 256) {
-        const int row = e / RW, c = e % RW;
-        ps[e] = (row < nr && c < RP) ? (double)P[(i0 + row) * RP + c] : 0.0;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        const int q = tid + 256 * j;
+        if (q >= nr * T4) continue;
+        if constexpr (RW == RP) {
+          load4(P + i0 * RP + 4 * (int64_t)q, x[j]);
+        } else {
+#pragma unroll
+          for (int c = 0; c < RP; ++c) x[j][c] = P[(i0 + q) * RP + c];
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int q = tid + 256 * j;
+      if (q < CH * T4) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) ps[4 * q + c] = x[j][c];
       }
     }
     __syncthreads();
     if (active) {
       for (int ii = grp; ii < nr; ii += NG) {
-        const double x0 = ps[ii * RW + ta], x1 = ps[ii * RW + ta + 1];
-        const double y0 = ps[ii * RW + tb], y1 = ps[ii * RW + tb + 1];
-        a00 = fma(x0, y0, a00);
-        a01 = fma(x0, y1, a01);
-        a10 = fma(x1, y0, a10);
-        a11 = fma(x1, y1, a11);
+        TA u[4], w[4];
+        load4(ps + ii * RW + 4 * ta, u);
+        load4(ps + ii * RW + 4 * tb, w);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+          for (int d = 0; d < 4; ++d) acc[c][d] = fma((double)u[c], (double)w[d], acc[c][d]);
       }
     }
   }
+  // the groups' tiles, added over the groups: part p of an entry takes the
+  // groups p, p + PARTS, ..., then the parts are added
+  __syncthreads();
   if (active) {
-    double* q = red + (grp * NT + tile) * 4;
-    q[0] = a00; q[1] = a01; q[2] = a10; q[3] = a11;
-  }
-  __syncthreads();
-  for (int e = tid; e < E; e += 256) {
-    const int a = e / RP, b = e % RP;
-    const int t = (a / 2) * RH + b / 2, slot = (a & 1) * 2 + (b & 1);
-    double s = 0.0;
-    for (int q = 0; q < NG; ++q) s += red[(q * NT + t) * 4 + slot];
-    publish(Gpart + (int64_t)blockIdx.x * E + e, s);
-  }
-  // ---- level 1: the last block of the group adds the group's partials ----
-  const int nb = (int)gridDim.x;
-  const int gi = (int)blockIdx.x / kGramGroup;
-  const int g0 = gi * kGramGroup;
-  const int gsz = (nb - g0) < kGramGroup ? (nb - g0) : kGramGroup;
-  stores_done();
-  __syncthreads();
-  if (tid == 0) flag = arrive(&ctl->grp[gi]) == (unsigned int)(gsz - 1);
-  __syncthreads();
-  if (!flag) return;
-  for (int e = tid; e < E; e += 256) {
-    double v[kGramGroup];
 #pragma unroll
-    for (int q = 0; q < kGramGroup; ++q) v[q] = q < gsz ? fetch(Gpart + (int64_t)(g0 + q) * E + e) : 0.0;
-    double s = 0.0;
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int q = 0; q < kGramGroup; ++q) s += v[q];
-    publish(Gpart + (int64_t)(kGramMaxBlocks + gi) * E + e, s);
-  }
-  // ---- level 2: the last group leader adds the group sums ----
-  const int ngr = (nb + kGramGroup - 1) / kGramGroup;
-  stores_done();
-  __syncthreads();
-  if (tid == 0) {
-    publish_u32(&ctl->grp[gi], 0u);
-    flag = arrive(&ctl->top) == (unsigned int)(ngr - 1);
+      for (int d = 0; d < 4; ++d) red[(grp * NT + tile) * 16 + 4 * c + d] = acc[c][d];
   }
   __syncthreads();
-  if (!flag) return;
-  // the Cholesky step's global inputs, in flight during the fetch below
+  constexpr int PARTS = 256 / RS < 1 ? 1 : (256 / RS < NG ? 256 / RS : NG);
+  double* gp = Gpart + (int64_t)blockIdx.x * GT::ENT;
+  auto put = [&](int e, double v) {
+    if constexpr (RP >= 4) {
+      gp[e] = v;
+    } else {
+      if (e / 4 < RP && e % 4 < RP) gp[e / 4 * RP + e % 4] = v;
+    }
+  };
+  if constexpr (PARTS == 1) {
+    for (int e = tid; e < RS; e += 256) {
+      double s = 0.0;
+#pragma unroll
+      for (int g = 0; g < NG; ++g) s += red[g * RS + e];
+      put(e, s);
+    }
+  } else {
+    const int e = tid % RS, p = tid / RS;
+    double s = 0.0;
+    if (p < PARTS) {
+#pragma unroll 8
+      for (int g = p; g < NG; g += PARTS) s += red[g * RS + e];
+    }
+    __syncthreads();
+    if (p < PARTS) red[p * RS + e] = s;
+    __syncthreads();
+    if (tid < RS) {
+      s = 0.0;
+#pragma unroll
+      for (int g = 0; g < PARTS; ++g) s += red[g * RS + tid];
+      put(tid, s);
+    }
+  }
+}
+
+// G (LDS, stride LD) = the sum of nparts partials of k_gram_part, by NT
+// threads (all call it; two barriers): pairs of entries, the partials dealt
+// to NT / pairs groups, eight loads in flight per thread.  scratch: NT pairs.
+template <int RP, int NT, int LD>
+__device__ __forceinline__ void gram_sum(const double* __restrict__ Gpart, int nparts, double* G,
+                                         double* scratch) {
+  using GT = GramTile<RP>;
+  constexpr int VW = GT::ENT % 2 ? 1 : 2;
+  constexpr int Q = GT::ENT / VW;
+  constexpr int SG = NT / Q > 0 ? NT / Q : 1;
+  constexpr int NQ = (Q + NT - 1) / NT;   // pairs per thread (one group only)
+  const int tid = threadIdx.x;
+  auto put = [&](int e, double v) {
+    if constexpr (RP < 4) {
+      G[e / RP * LD + e % RP] = v;
+    } else {
+      int ta, tb;
+      gram_tile<GT::T4>(e / 16, ta, tb);
+      const int i = 4 * ta + e % 16 / 4, j = 4 * tb + e % 4;
+      G[i * LD + j] = v;
+      if (ta != tb) G[j * LD + i] = v;
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < NQ; ++u) {
+    const int q = NQ > 1 ? tid + u * NT : tid % Q, g = NQ > 1 ? 0 : tid / Q;
+    const bool on = NQ > 1 ? q < Q : g < SG;
+    double s[VW] = {};
+    if (on) {
+      const double* p = Gpart + VW * q;
+      constexpr int B = 8;
+      for (int h = g; h < nparts; h += B * SG) {
+        double v[B][VW];
+#pragma unroll
+        for (int k = 0; k < B; ++k)
+#pragma unroll
+          for (int x = 0; x < VW; ++x)
+            v[k][x] = h + k * SG < nparts ? p[(int64_t)(h + k * SG) * GT::ENT + x] : 0.0;
+#pragma unroll
+        for (int k = 0; k < B; ++k)
+#pragma unroll
+          for (int x = 0; x < VW; ++x) s[x] += v[k][x];
+      }
+    }
+    if constexpr (SG == 1) {
+      if (on)
+#pragma unroll
+        for (int x = 0; x < VW; ++x) put(VW * q + x, s[x]);
+    } else {
+      if (on)
+#pragma unroll
+        for (int x = 0; x < VW; ++x) scratch[VW * tid + x] = s[x];
+      __syncthreads();
+      if (tid < Q) {
+#pragma unroll
+        for (int x = 0; x < VW; ++x) {
+          double v = 0.0;
+#pragma unroll 8
+          for (int k = 0; k < SG; ++k) v += scratch[VW * (k * Q + tid) + x];
+          put(VW * tid + x, v);
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// Out = P R^{-1}, one row per thread, with G = R^T R the sum of the partials
+// (k_chol.h; R upper triangular, zero rows and 1/diag = 0 on inactive
+// columns), by forward substitution in FP64; optionally also the transposed
+// panel Zt (32 x ldz) in bf16 or f32 for the next matrix-core pass, rows >= RP
+// zero.  With acc, one more block folds R into it (acc <- R acc, or R with
+// reset_acc), rescaled by a power of two when normalise is set.
+template <typename TA, int RP, typename TT>
+__global__ __launch_bounds__(256) void k_chol_rinv(const TA* __restrict__ P, int64_t rows,
+                                                   const double* __restrict__ Gpart, int nparts,
+                                                   const SmallState* __restrict__ st,
+                                                   double* __restrict__ acc, int reset_acc,
+                                                   int normalise, TA* __restrict__ Out,
+                                                   TT* __restrict__ Zt, int64_t ldz) {
+  __shared__ double Gs[RP * RP], rq[RP * RP], di[RP];
+  __shared__ double scratch[512];
+  const int tid = threadIdx.x;
+  const bool fold = acc != nullptr && blockIdx.x == gridDim.x - 1;
+  const int64_t i = (int64_t)blockIdx.x * 256 + tid;
+  const bool live = !fold && i < rows;
+  // the row and the factorisation's inputs, in flight during the sums
+  TA p[RP];
+#pragma unroll
+  for (int c = 0; c < RP; ++c) p[c] = live ? P[i * RP + c] : TA(0);
   CholIn<RP> cin;
-  if (chol && tid < 64) chol_prefetch<RP>(cin, st, acc, reset_acc);
-  double* Gs = ps;   // E <= 1024 doubles fit in ps
-  for (int e = tid; e < E; e += 256) {
-    double v[kGramMaxBlocks / kGramGroup];
-#pragma unroll
-    for (int q = 0; q < kGramMaxBlocks / kGramGroup; ++q)
-      v[q] = q < ngr ? fetch(Gpart + (int64_t)(kGramMaxBlocks + q) * E + e) : 0.0;
-    double s = 0.0;
-#pragma unroll
-    for (int q = 0; q < kGramMaxBlocks / kGramGroup; ++q) s += v[q];
-    Gs[e] = s;
-    Gpart[(int64_t)kGramFinal * E + e] = s;
-  }
-  if (tid == 0) publish_u32(&ctl->top, 0u);
-  if (!chol) return;
+  if (tid < 64) chol_prefetch<RP>(cin, st, fold ? acc : nullptr, reset_acc);
+  gram_sum<RP, 256, RP>(Gpart, nparts, Gs, scratch);
+  if (tid < 64) wave_chol<TA, RP>(Gs, rq, di, fold ? acc : nullptr, reset_acc, normalise, cin);
   __syncthreads();
-  if (tid >= 64) return;
-  wave_chol<TA, RP>(Gs, st->Rq, st->dinv, acc, reset_acc, normalise, cin);
+  if (!live) return;
+  double y[RP], x[RP];
+#pragma unroll
+  for (int c = 0; c < RP; ++c) y[c] = (double)p[c];
+  row_rinv<RP>(y, rq, di, x);
+#pragma unroll
+  for (int j = 0; j < RP; ++j) Out[i * RP + j] = (TA)x[j];
+  if (Zt != nullptr) {
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+      const float v = j < RP ? (float)x[j] : 0.f;
+      if constexpr (sizeof(TT) == 2)
+        Zt[(int64_t)j * ldz + i] = f32_to_bf16(v);
+      else
+        Zt[(int64_t)j * ldz + i] = (TT)v;
+    }
+  }
 }
 
 // Rotation threshold of the Jacobi sweeps: an off-diagonal entry below
@@ -695,13 +839,15 @@ __device__ __forceinline__ void core_rank(double* W, double* H, double* fk, doub
 }
 
 // ---------------------------------------------------------------------------
-// Core of the low-rank step.  Inputs: Gpart of B' = D Y_q (so B = B' T),
+// Core of the low-rank step.  Inputs: Gpart of B' = D Y_q (so B = B' T; nparts
+// partials, those of k_gram_part or RP x RP matrices),
 // st->T, st->R2.  Output: K' = T K in the panel type, such that
 // U_L = B' K' and L = U_L Q2^T.
 // ---------------------------------------------------------------------------
 template <typename TA, int RP, int NT>
-__device__ __forceinline__ void core_body(const double* __restrict__ Gpart, int nparts, SmallState* st, int p,
-                          double rank_tol, int t_identity, TA* k_panel) {
+__device__ __forceinline__ void core_body(const double* __restrict__ Gpart, int nparts,
+                                          int tiled, SmallState* st, int p, double rank_tol,
+                                          int t_identity, TA* k_panel) {
   constexpr int LD = RP + 1;
   __shared__ double G[RP * LD];
   __shared__ double H[RP * LD];
@@ -718,14 +864,14 @@ __device__ __forceinline__ void core_body(const double* __restrict__ Gpart, int 
   __shared__ int sh_keep;
   const int tid = threadIdx.x;
   const int n = st->r_eff;             // active leading columns
+  __shared__ double scratch[2 * NT];
   for (int e = tid; e < RP * RP; e += NT) {
-    double s = 0.0;
-    s = sum_parts(Gpart, nparts, RP * RP, e);
     const int i = e / RP, j = e % RP;
-    G[i * LD + j] = s;
+    if (!tiled) G[i * LD + j] = sum_parts(Gpart, nparts, RP * RP, e);
     T[i * LD + j] = t_identity ? (i == j ? 1.0 : 0.0) : st->T[e];
     W[i * LD + j] = st->R2[e];
   }
+  if (tiled) gram_sum<RP, NT, LD>(Gpart, nparts, G, scratch);
   __syncthreads();
 
   core_rank<RP, NT>(W, H, fk, sv, cs, rot, n, rank_tol, &sh_keep);
@@ -820,10 +966,11 @@ __device__ __forceinline__ void core_body(const double* __restrict__ Gpart, int 
 
 template <typename TA, int RP>
 __global__ __launch_bounds__(core_threads<RP>()) void k_core(const double* __restrict__ Gpart,
-                                                        int nparts, SmallState* st, int p,
-                                                        double rank_tol, int t_identity,
+                                                        int nparts, int tiled, SmallState* st,
+                                                        int p, double rank_tol, int t_identity,
                                                         TA* k_panel) {
-  core_body<TA, RP, core_threads<RP>()>(Gpart, nparts, st, p, rank_tol, t_identity, k_panel);
+  core_body<TA, RP, core_threads<RP>()>(Gpart, nparts, tiled, st, p, rank_tol, t_identity,
+                                        k_panel);
 }
 
 __global__ void k_small_init(SmallState* st, int r) {
@@ -851,35 +998,53 @@ __global__ void k_small_init(SmallState* st, int r) {
     default: break;                                \
   }
 
-void launch_gram_tree(const Launch& L, bool f64, int rp, const void* P, int64_t rows,
-                      double* Gpart, GramCtl* ctl, int chol, SmallState* st, double* acc,
-                      int reset_acc, int normalise, const float* Zpart, int nch) {
-  int64_t nb = (rows + kGramRows - 1) / kGramRows;
-  if (nb > kGramMaxBlocks) nb = kGramMaxBlocks;
-  if (nb < 1) nb = 1;
+int launch_gram_part(const Launch& L, bool f64, int rp, void* P, int64_t rows, double* Gpart,
+                     const float* Zpart, int nch) {
+  const int64_t steps = std::max<int64_t>(1, (rows + kGramRows - 1) / kGramRows);
+  const int64_t per = (steps + kGramMaxBlocks - 1) / kGramMaxBlocks * kGramRows;
+  const int64_t nb = std::max<int64_t>(1, (rows + per - 1) / per);
   GODEC_RP_SWITCH(rp, {
     if (f64)
-      hipLaunchKernelGGL((k_gram_tree<double, RP>), dim3((unsigned)nb), dim3(256), 0, L.stream,
-                         (const double*)P, rows, Gpart, ctl, chol, st, acc, reset_acc,
-                         normalise, nullptr, 0);
+      hipLaunchKernelGGL((k_gram_part<double, RP>), dim3((unsigned)nb), dim3(256), 0, L.stream,
+                         (double*)P, rows, per, Gpart, nullptr, 0);
     else
-      hipLaunchKernelGGL((k_gram_tree<float, RP>), dim3((unsigned)nb), dim3(256), 0, L.stream,
-                         (const float*)P, rows, Gpart, ctl, chol, st, acc, reset_acc,
-                         normalise, Zpart, nch);
+      hipLaunchKernelGGL((k_gram_part<float, RP>), dim3((unsigned)nb), dim3(256), 0, L.stream,
+                         (float*)P, rows, per, Gpart, Zpart, nch);
+  });
+  return (int)nb;
+}
+
+void launch_chol_rinv(const Launch& L, bool f64, int rp, const void* P, int64_t rows,
+                      const double* Gpart, int nparts, const SmallState* st, double* acc,
+                      int reset_acc, int normalise, void* Out, DType zt_type, void* Zt,
+                      int64_t ldz) {
+  const dim3 g((unsigned)((rows + 255) / 256 + (acc != nullptr ? 1 : 0)));
+  GODEC_RP_SWITCH(rp, {
+    if (f64)
+      hipLaunchKernelGGL((k_chol_rinv<double, RP, double>), g, dim3(256), 0, L.stream,
+                         (const double*)P, rows, Gpart, nparts, st, acc, reset_acc, normalise,
+                         (double*)Out, (double*)nullptr, ldz);
+    else if (Zt != nullptr && zt_type == BF16)
+      hipLaunchKernelGGL((k_chol_rinv<float, RP, uint16_t>), g, dim3(256), 0, L.stream,
+                         (const float*)P, rows, Gpart, nparts, st, acc, reset_acc, normalise,
+                         (float*)Out, (uint16_t*)Zt, ldz);
+    else
+      hipLaunchKernelGGL((k_chol_rinv<float, RP, float>), g, dim3(256), 0, L.stream,
+                         (const float*)P, rows, Gpart, nparts, st, acc, reset_acc, normalise,
+                         (float*)Out, (float*)Zt, ldz);
   });
 }
 
-
 void launch_core(const Launch& L, bool f64, int rp, const double* Gpart,
-                 int nparts, SmallState* st, int p, double rank_tol,
+                 int nparts, int tiled, SmallState* st, int p, double rank_tol,
                  int t_identity, void* k_panel) {
   GODEC_RP_SWITCH(rp, {
     if (f64)
       hipLaunchKernelGGL((k_core<double, RP>), dim3(1), dim3(core_threads<RP>()), 0, L.stream, Gpart,
-                         nparts, st, p, rank_tol, t_identity, (double*)k_panel);
+                         nparts, tiled, st, p, rank_tol, t_identity, (double*)k_panel);
     else
       hipLaunchKernelGGL((k_core<float, RP>), dim3(1), dim3(core_threads<RP>()), 0, L.stream, Gpart,
-                         nparts, st, p, rank_tol, t_identity, (float*)k_panel);
+                         nparts, tiled, st, p, rank_tol, t_identity, (float*)k_panel);
   });
 }
 

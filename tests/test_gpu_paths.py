@@ -152,6 +152,28 @@ def test_core_of_every_width(m, n, r, q, dt, tol):
     gd.close()
 
 
+# partial Grams: rows at the edges of a step and past 128 steps (several steps
+# per block), panels narrower than a tile, with and without chunk partials
+@pytest.mark.parametrize("m,n,r,q", [
+    (1, 600, 1, 1), (127, 640, 2, 1), (129, 16600, 3, 1), (16500, 520, 1, 1), (16385, 513, 2, 0),
+    (2000, 16384, 5, 1)])
+@pytest.mark.parametrize("dt,tol", [(np.float64, 1e-10), (np.float32, 1e-5)])
+def test_panel_row_edges(m, n, r, q, dt, tol):
+    """One step against the oracle's update (the bars of the per-step parity
+    tests) and the orthonormality of V_L."""
+    from oracle import godec_ref as g
+    from oracle.rng_ref import a1_gaussian
+    from paper_1309_0302_amd.binding import GoDec
+    w = wl.tiny(m, n, r, seed=m + n, dtype=dt)
+    gd = GoDec(torch.from_numpy(w.X).to("cuda:0"), r, w.k, q, seed=9)
+    gd.step(1)
+    ref = g.brp_power(w.X.astype(np.float64), a1_gaussian(9, n, r), q)
+    assert g.rel_fro(gd.L_dense().cpu().numpy().astype(np.float64), ref.L) <= tol
+    VL = gd.factors()[1].cpu().numpy().astype(np.float64)
+    assert np.abs(VL.T @ VL - np.eye(r)).max() <= 10 * tol
+    gd.close()
+
+
 def _mse_identity(X, K, steps):
     """MSE training with one empty label: the sparse step selects from X
     itself, so the input sets the ties.  Yields S after each step."""
