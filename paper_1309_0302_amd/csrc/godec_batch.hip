@@ -300,7 +300,11 @@ godec_status autotune(godec_batch* b) {
     HIP_TRY(hipEventSynchronize(e1));
     float ms = 0.f;
     HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-    if (ms < best) {
+    // The times of one split vary by up to 2%, and the split sets the order of
+    // the FP32 sums: a later candidate has to win by more than that, so that
+    // a shape gets the same split, and the same bits, in every process (32
+    // problems of up to 20 000 x 400: 128, 256 and 512 rows within 3%).
+    if (ms < 0.98f * best) {
       best = ms;
       best_rows = rows;
     }
