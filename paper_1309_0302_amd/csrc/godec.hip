@@ -483,16 +483,17 @@ void gram_pass(godec_ctx* c, DType td, const void* Dsrc, const void* in, bool zt
 // Orthonormalise `in` (ldd x RP) into `out` by one Cholesky QR step,
 // accumulating its R factor into acc (reset when reset != 0).  next_td:
 // type of the matrix-core pass that reads `out` next (its transpose is
-// written to c->Zt), or F64 when none does.
+// written to c->Zt), or F64 when none does.  out_t: also out^T (RP x ldd).
 void chol_qr(godec_ctx* c, void* in, void* out, double* acc, int reset, DType next_td,
-             bool from_parts = false) {
+             bool from_parts = false, void* out_t = nullptr) {
   const Launch L = launch_of(c);
   const int np = launch_gram_part(L, c->f64, c->rp, in, c->ldd, c->Gpart,
                                   from_parts ? c->Zpart32 : nullptr,
                                   from_parts ? (int)c->nch_b : 0);
   const bool zt = !c->f64 && next_td != F64;
   launch_chol_rinv(L, c->f64, c->rp, in, c->ldd, c->Gpart, np, c->st, acc, reset,
-                   acc == c->st->R2 ? 1 : 0, out, next_td, zt ? c->Zt : nullptr, c->ldd);
+                   acc == c->st->R2 ? 1 : 0, out, next_td, zt ? c->Zt : nullptr, c->ldd,
+                   out_t);
 }
 
 // A Gram pass and one Cholesky QR step: out = orth(D^T (D in)) via tmp, its
@@ -528,12 +529,6 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
     g.VL = c->VL; g.VLt = c->VLt; g.UL = c->UL; g.ldv = c->ldd;
     launch_gram_form(L, g);
   } else {
-  // ---- subspace chain: Q2 = orth((D^T D)^p A1), R2 tracked ----
-  if (c->warm && c->iters_done > 0)
-    HIP_TRY(hipMemcpyAsync(c->P0, c->VL, (size_t)c->ldd * c->rp * c->ta, hipMemcpyDeviceToDevice,
-                           c->stream));   // Q2 of the last iteration (zero past r_eff)
-  else
-    launch_copy_panel(L, c->f64, c->rp, c->A1, c->n, c->ldd, c->r, c->st, c->P0);
   if (refine && !c->d_native_valid) {
     // D = X - S_{t-1} in FP32 for the refinement passes
     launch_init_d(L, F32, false, c->D, c->ldd, c->X, c->ldx, c->m, c->n, c->mpad);
@@ -547,11 +542,18 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
   auto chain_td = [&](int j) {
     return (mixed && !(refine && j == c->p - 1)) ? BF16 : native;
   };
+  // ---- subspace chain: Q2 = orth((D^T D)^p A1), R2 tracked ----
+  if (c->warm && c->iters_done > 0)
+    HIP_TRY(hipMemcpyAsync(c->P0, c->VL, (size_t)c->ldd * c->rp * c->ta, hipMemcpyDeviceToDevice,
+                           c->stream));   // Q2 of the last iteration (zero past r_eff)
+  else
+    launch_copy_panel(L, c->f64, c->rp, c->A1, c->n, c->ldd, c->r, c->st, c->P0, chain_td(0),
+                      c->f64 ? nullptr : c->Zt);
   const bool low_b = mixed && !refine;
   const DType tdb = low_b ? BF16 : native;
   const void* Db = low_b ? c->D16 : c->D;
   const void* in = c->P0;
-  bool zt = false;
+  bool zt = !c->f64 && !(c->warm && c->iters_done > 0);   // Zt holds P0^T
   for (int j = 0; j < c->p; ++j) {
     const DType td = chain_td(j);
     const bool more = j + 1 < c->p;
@@ -562,7 +564,7 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
   }
   // second Cholesky QR round on Q2 (restores orthonormality to working
   // precision); its R factor joins R2.  Its transpose feeds the B chain.
-  chol_qr(c, c->P0, c->VL, c->st->R2, 0, tdb);
+  chol_qr(c, c->P0, c->VL, c->st->R2, 0, tdb, false, c->VLt);
   if (c->lstep == 1) {
     // projection form: L = D Q2 Q2^T, i.e. U_L = D Q2 and V_L = Q2
     if (c->f64)
@@ -586,7 +588,6 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
               c->rank_tol, c->q == 0 ? 1 : 0, c->Kp);
   launch_apply_small(L, c->f64, c->rp, c->Bp, c->m, c->Kp, c->UL);
   }
-  launch_transpose_panel(L, c->f64, c->VL, c->ldd, c->rp, c->VLt);
   }
   // ---- sparse step ----
   const int prev = c->cur;

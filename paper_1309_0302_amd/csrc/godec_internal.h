@@ -123,26 +123,29 @@ void launch_reduce_chunks(const Launch& L, bool f64, int rp,
 // row-chunk partials Zpart (nch x rows x zpart_stride, chunk-ascending order)
 // and store it, instead of reading it.
 constexpr int kGramRows = 128;       // rows per step of a block
-constexpr int kGramMaxBlocks = 128;  // partials: each block that adds them reads all
+constexpr int kGramMaxBlocks = 128;  // partials at most
 constexpr int kGramMaxChunks = 16;   // row-chunk partials that k_gram_part adds up
 int launch_gram_part(const Launch& L, bool f64, int rp, void* P, int64_t rows, double* Gpart,
                      const float* Zpart = nullptr, int nch = 0);
 // Out = P R^{-1}, R the Cholesky factor of the summed partials (upper
 // triangular, dependent columns detected: zero columns of Out), rows x RP in
 // the panel type, Out != P; when Zt is given, also its transpose (32 x ldz,
-// bf16 or f32, rows >= RP zero) for the next matrix-core pass.  With acc: acc
+// bf16 or f32, rows >= RP zero) for the next matrix-core pass, and Ot = Out^T
+// (RP x ldz, panel type).  With acc: acc
 // <- R acc, or R when reset_acc, rescaled by a power of two when normalise.
 void launch_chol_rinv(const Launch& L, bool f64, int rp, const void* P, int64_t rows,
                       const double* Gpart, int nparts, const SmallState* st, double* acc,
                       int reset_acc, int normalise, void* Out, DType zt_type, void* Zt,
-                      int64_t ldz);
+                      int64_t ldz, void* Ot = nullptr);
 // Out = P K  (rows x RP), K is RP x RP in the panel type.
 void launch_apply_small(const Launch& L, bool f64, int rp, const void* P,
                         int64_t rows, const void* K, void* Out);
-// dst (rows_pad x RP) <- src (rows x r, FP64) with columns >= st->r_eff zeroed.
+// dst (rows_pad x RP) <- src (rows x r, FP64) with columns >= st->r_eff zeroed;
+// FP32 panels optionally also transposed, as launch_chol_rinv's Zt.
 void launch_copy_panel(const Launch& L, bool f64, int rp, const double* src,
                        int64_t rows, int64_t rows_pad, int r,
-                       const SmallState* st, void* dst);
+                       const SmallState* st, void* dst, DType zt_type = F64,
+                       void* Zt = nullptr);
 // ---- r x r FP64 kernels (k_small.hip) ----
 void launch_core(const Launch& L, bool f64, int rp, const double* Gpart,
                  int nparts, int tiled, SmallState* st, int p, double rank_tol,
@@ -196,8 +199,6 @@ struct SelectArgs {
   int64_t lddw = 0;
 };
 void launch_select(const Launch& L, bool f64, int rp, const SelectArgs& a);
-void launch_transpose_panel(const Launch& L, bool f64, const void* VL, int64_t rows, int rp,
-                            void* VLt);
 // R = X - UL VL^T (dense_l = 0) or L = UL VL^T (dense_l = 1).
 void launch_residual(const Launch& L, bool f64, int rp, const void* X,
                      int64_t ldx, const void* UL, const void* VL, int64_t m,

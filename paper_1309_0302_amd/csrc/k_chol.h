@@ -67,17 +67,16 @@ __device__ __forceinline__ void wave_chol(double* G, double* Rq, double* dinv, d
     const double g0k = lane_bcast(g0, k);
     const int actk = __builtin_amdgcn_readlane(act, k) && piv > tau * g0k;
     if (lane == k) act = actk;
-    if (actk) {
-      const double inv = rsqrt_nr(piv);
-      const double rkk = piv * inv;
-      const double rkj = lane > k ? g[k] * inv : (lane == k ? rkk : 0.0);
-      if (lane == k) rdiag = rkk;
-      rcol[k] = rkj;
+    // no branch on actk: the updates of a step fill the latency of the next
+    // step's reciprocal square root
+    const double inv = rsqrt_nr(piv);
+    const double rkk = piv * inv;
+    double rkj = lane > k ? g[k] * inv : (lane == k ? rkk : 0.0);
+    rkj = actk ? rkj : 0.0;
+    rdiag = actk && lane == k ? rkk : rdiag;
+    rcol[k] = rkj;
 #pragma unroll
-      for (int i = k + 1; i < RP; ++i) g[i] -= lane_bcast(rkj, i) * rkj;
-    } else {
-      rcol[k] = 0.0;
-    }
+    for (int i = k + 1; i < RP; ++i) g[i] -= lane_bcast(rkj, i) * rkj;
   }
   if (col) {
 #pragma unroll
@@ -136,16 +135,28 @@ __device__ __forceinline__ void wave_chol(double* G, SmallState* st, double* acc
 
 
 // Row x of P R^{-1}: x R = y by forward substitution (R upper triangular, zero
-// rows and dinv = 0 on inactive columns).
+// rows and dinv = 0 on inactive columns).  Right-looking: the updates of a
+// step are independent, and a row of R is contiguous; the next row is read
+// ahead, and no further one (all of R in registers spills).
 template <int RP>
 __device__ __forceinline__ void row_rinv(const double (&y)[RP], const double* Rq,
                                          const double* dinv, double (&x)[RP]) {
+  double r[2][RP];
+#pragma unroll
+  for (int c = 0; c < RP; ++c) x[c] = y[c];
+#pragma unroll
+  for (int l = 0; l < RP; ++l) r[0][l] = l == 0 ? dinv[0] : Rq[l];
 #pragma unroll
   for (int c = 0; c < RP; ++c) {
-    double s = y[c];
+    if (c + 1 < RP) {
 #pragma unroll
-    for (int l = 0; l < c; ++l) s = fma(-x[l], Rq[l * RP + c], s);
-    x[c] = s * dinv[c];
+      for (int l = c + 1; l < RP; ++l)
+        r[(c + 1) & 1][l] = l == c + 1 ? dinv[l] : Rq[(c + 1) * RP + l];
+    }
+    asm volatile("" ::: "memory");
+    x[c] *= r[c & 1][c];
+#pragma unroll
+    for (int l = c + 1; l < RP; ++l) x[l] = fma(-x[c], r[c & 1][l], x[l]);
   }
 }
 

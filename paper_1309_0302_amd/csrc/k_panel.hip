@@ -167,19 +167,32 @@ __global__ __launch_bounds__(256) void k_apply_small(const TA* __restrict__ P,
 }
 
 // dst (rows_pad x RP, panel type) <- src (rows x r, FP64 row-major), with
-// the columns at or past st->r_eff and all padding set to zero.
-template <typename TA, int RP>
-__global__ __launch_bounds__(256) void k_copy_panel(const double* __restrict__ src,
-                                                    int64_t rows, int64_t rows_pad,
-                                                    int r,
-                                                    const SmallState* __restrict__ st,
-                                                    TA* __restrict__ dst) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= rows_pad * RP) return;
-  const int64_t i = e / RP;
-  const int c = (int)(e % RP);
-  const int reff = st->r_eff;
-  dst[e] = (i < rows && c < r && c < reff) ? (TA)src[i * r + c] : TA(0);
+// the columns at or past st->r_eff and all padding set to zero; optionally
+// also the transposed panel Zt (32 x rows_pad) in bf16 or f32, rows >= RP
+// zero.  One row per thread.
+template <typename TA, int RP, typename TT>
+__global__ __launch_bounds__(64) void k_copy_panel(const double* __restrict__ src,
+                                                   int64_t rows, int64_t rows_pad, int r,
+                                                   const SmallState* __restrict__ st,
+                                                   TA* __restrict__ dst, TT* __restrict__ Zt) {
+  const int64_t i = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  if (i >= rows_pad) return;
+  const int reff = st->r_eff < r ? st->r_eff : r;
+  TA x[RP];
+#pragma unroll
+  for (int c = 0; c < RP; ++c) x[c] = (i < rows && c < reff) ? (TA)src[i * r + c] : TA(0);
+#pragma unroll
+  for (int c = 0; c < RP; ++c) dst[i * RP + c] = x[c];
+  if (Zt != nullptr) {
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+      const float v = j < RP ? (float)x[j] : 0.f;
+      if constexpr (sizeof(TT) == 2)
+        Zt[(int64_t)j * rows_pad + i] = f32_to_bf16(v);
+      else
+        Zt[(int64_t)j * rows_pad + i] = (TT)v;
+    }
+  }
 }
 
 // dst (rows x r, row-major) <- the first r columns of src (rows x RP).
@@ -274,15 +287,18 @@ void launch_apply_small(const Launch& L, bool f64, int rp, const void* P,
 
 void launch_copy_panel(const Launch& L, bool f64, int rp, const double* src,
                        int64_t rows, int64_t rows_pad, int r,
-                       const SmallState* st, void* dst) {
-  const unsigned blocks = (unsigned)((rows_pad * rp + 255) / 256);
+                       const SmallState* st, void* dst, DType zt_type, void* Zt) {
+  const dim3 g((unsigned)((rows_pad + 63) / 64));
   GODEC_RP_SWITCH(rp, {
     if (f64)
-      hipLaunchKernelGGL((k_copy_panel<double, RP>), dim3(blocks), dim3(256), 0,
-                         L.stream, src, rows, rows_pad, r, st, (double*)dst);
+      hipLaunchKernelGGL((k_copy_panel<double, RP, double>), g, dim3(64), 0, L.stream, src, rows,
+                         rows_pad, r, st, (double*)dst, (double*)nullptr);
+    else if (Zt != nullptr && zt_type == BF16)
+      hipLaunchKernelGGL((k_copy_panel<float, RP, uint16_t>), g, dim3(64), 0, L.stream, src,
+                         rows, rows_pad, r, st, (float*)dst, (uint16_t*)Zt);
     else
-      hipLaunchKernelGGL((k_copy_panel<float, RP>), dim3(blocks), dim3(256), 0,
-                         L.stream, src, rows, rows_pad, r, st, (float*)dst);
+      hipLaunchKernelGGL((k_copy_panel<float, RP, float>), g, dim3(64), 0, L.stream, src, rows,
+                         rows_pad, r, st, (float*)dst, (float*)Zt);
   });
 }
 

@@ -1622,16 +1622,6 @@ __global__ __launch_bounds__(256) void k_sel_reset(SelPlan* plan, unsigned long 
   if (threadIdx.x == 0) plan_reset<T>(plan, counters, k, cap, nseg, carry);
 }
 
-// VLt (rp x ldv) <- VL (ldv x rp), both in the residual type.
-template <typename T>
-__global__ __launch_bounds__(256) void k_transpose_panel(const T* __restrict__ VL, int64_t rows,
-                                                         int rp, T* __restrict__ VLt) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= rows * rp) return;
-  const int64_t c = e / rows, j = e % rows;
-  VLt[e] = VL[j * rp + c];
-}
-
 // ---------------------------------------------------------------------------
 // Dense helpers.
 // ---------------------------------------------------------------------------
@@ -1965,17 +1955,6 @@ static void select_t(const Launch& L, int rp, const SelectArgs& a) {
                      a.cand_idx, (const T*)a.cand_val, (const T*)a.cand_x, a.tie_idx, a.counters,
                      a.carry, (const double*)(a.s2part + kSelParts), (int)cg, out,
                      (long long)a.k, (long long)a.cap, nseg);
-}
-
-void launch_transpose_panel(const Launch& L, bool f64, const void* VL, int64_t rows, int rp,
-                            void* VLt) {
-  const unsigned b = (unsigned)((rows * rp + 255) / 256);
-  if (f64)
-    hipLaunchKernelGGL(k_transpose_panel<double>, dim3(b), dim3(256), 0, L.stream,
-                       (const double*)VL, rows, rp, (double*)VLt);
-  else
-    hipLaunchKernelGGL(k_transpose_panel<float>, dim3(b), dim3(256), 0, L.stream,
-                       (const float*)VL, rows, rp, (float*)VLt);
 }
 
 void launch_select(const Launch& L, bool f64, int rp, const SelectArgs& a) {

@@ -62,7 +62,7 @@ __device__ __forceinline__ double sum_parts(const double* __restrict__ P, int np
 // launch for R^{-1}) took 19 + 5.7 us at 10000 x 20, of which 6 us the tree
 // and 6 us the factorisation in a block that runs its code cold.  The kernel
 // boundary does the hand-over, and every block adds the partials and factors
-// on its own: 5.6 + 15 us; 1503 x 20: 17.3 + 5.7 -> 5.6 + 12.7 us; 25 344 x 4:
+// on its own: 5.6 + 10.9 us; 1503 x 20: 17.3 + 5.7 -> 5.6 + 10.0 us; 25 344 x 4:
 // 9.7 + 3.9 -> 4.0 + 4.6 us.
 //
 // A partial holds the 4 x 4 tiles of G on and above the diagonal (whole
@@ -244,7 +244,8 @@ __global__ __launch_bounds__(256) void k_gram_part(TA* __restrict__ P, int64_t r
 
 // G (LDS, stride LD) = the sum of nparts partials of k_gram_part, by NT
 // threads (all call it; two barriers): pairs of entries, the partials dealt
-// to NT / pairs groups, eight loads in flight per thread.  scratch: NT pairs.
+// to NT / pairs groups, up to 20 loads in flight per thread (a load of lines that
+// other XCDs have just written takes about 2000 cycles).  scratch: NT pairs.
 template <int RP, int NT, int LD>
 __device__ __forceinline__ void gram_sum(const double* __restrict__ Gpart, int nparts, double* G,
                                          double* scratch) {
@@ -272,7 +273,7 @@ __device__ __forceinline__ void gram_sum(const double* __restrict__ Gpart, int n
     double s[VW] = {};
     if (on) {
       const double* p = Gpart + VW * q;
-      constexpr int B = 8;
+      constexpr int B = RP >= 12 ? 20 : 10;
       for (int h = g; h < nparts; h += B * SG) {
         double v[B][VW];
 #pragma unroll
@@ -309,49 +310,78 @@ __device__ __forceinline__ void gram_sum(const double* __restrict__ Gpart, int n
   __syncthreads();
 }
 
-// Out = P R^{-1}, one row per thread, with G = R^T R the sum of the partials
-// (k_chol.h; R upper triangular, zero rows and 1/diag = 0 on inactive
-// columns), by forward substitution in FP64; optionally also the transposed
-// panel Zt (32 x ldz) in bf16 or f32 for the next matrix-core pass, rows >= RP
-// zero.  With acc, one more block folds R into it (acc <- R acc, or R with
+// Out = P R^{-1} with G = R^T R the sum of the partials (k_chol.h; R upper
+// triangular, zero rows and 1/diag = 0 on inactive columns), by forward
+// substitution in FP64, one row per thread of waves 1 and 2 (their loads run
+// beside wave 0's factorisation); optionally also the transposed panel Zt (32
+// x ldz) in bf16 or f32 for the next matrix-core pass, rows >= RP zero, and
+// Ot = Out^T (RP x ldz).  With acc, the last block only folds R into it (acc <- R acc, or R with
 // reset_acc), rescaled by a power of two when normalise is set.
+//
+// kRinvRows rows per block: the LDS reads of R bound the substitution, so the
+// rows are spread over many CUs (256 rows on four waves: 6000 of the block's
+// 30000 cycles at RP = 20), each of which adds and factors the same G.
+constexpr int kRinvRows = 128;
+template <int RP>
+constexpr int rinv_threads() { return RP >= 12 ? 512 : 256; }
+
 template <typename TA, int RP, typename TT>
-__global__ __launch_bounds__(256) void k_chol_rinv(const TA* __restrict__ P, int64_t rows,
-                                                   const double* __restrict__ Gpart, int nparts,
-                                                   const SmallState* __restrict__ st,
-                                                   double* __restrict__ acc, int reset_acc,
-                                                   int normalise, TA* __restrict__ Out,
-                                                   TT* __restrict__ Zt, int64_t ldz) {
+__global__ __launch_bounds__(rinv_threads<RP>()) void k_chol_rinv(
+    const TA* __restrict__ P, int64_t rows, const double* __restrict__ Gpart, int nparts,
+    const SmallState* __restrict__ st, double* __restrict__ acc, int reset_acc, int normalise,
+    TA* __restrict__ Out, TT* __restrict__ Zt, int64_t ldz, TA* __restrict__ Ot) {
+  constexpr int NT = rinv_threads<RP>();
   __shared__ double Gs[RP * RP], rq[RP * RP], di[RP];
-  __shared__ double scratch[512];
+  __shared__ double scratch[2 * NT];
   const int tid = threadIdx.x;
-  const bool fold = acc != nullptr && blockIdx.x == gridDim.x - 1;
-  const int64_t i = (int64_t)blockIdx.x * 256 + tid;
-  const bool live = !fold && i < rows;
-  // the row and the factorisation's inputs, in flight during the sums
-  TA p[RP];
-#pragma unroll
-  for (int c = 0; c < RP; ++c) p[c] = live ? P[i * RP + c] : TA(0);
+  const int nrow = (int)gridDim.x - (acc != nullptr ? 1 : 0);   // blocks with rows
+  const bool fold = (int)blockIdx.x == nrow;
+  const int lr = tid - 64;
+  const bool rowlane = !fold && lr >= 0 && lr < kRinvRows;
   CholIn<RP> cin;
   if (tid < 64) chol_prefetch<RP>(cin, st, fold ? acc : nullptr, reset_acc);
-  gram_sum<RP, 256, RP>(Gpart, nparts, Gs, scratch);
+  gram_sum<RP, NT, RP>(Gpart, nparts, Gs, scratch);
+  TA p[RP];
+  auto load_row = [&](int64_t i) {
+    if constexpr (RP % 4 == 0) {
+#pragma unroll
+      for (int c = 0; c < RP; c += 4) {
+        TA v[4];
+        load4(P + i * RP + c, v);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) p[c + d] = v[d];
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < RP; ++c) p[c] = P[i * RP + c];
+    }
+  };
+  int64_t i = (int64_t)blockIdx.x * kRinvRows + lr;
+  if (rowlane && i < rows) load_row(i);
   if (tid < 64) wave_chol<TA, RP>(Gs, rq, di, fold ? acc : nullptr, reset_acc, normalise, cin);
   __syncthreads();
-  if (!live) return;
-  double y[RP], x[RP];
+  if (!rowlane) return;
+  for (; i < rows; i += (int64_t)nrow * kRinvRows) {
+    if (i >= (int64_t)nrow * kRinvRows) load_row(i);
+    double y[RP], x[RP];
 #pragma unroll
-  for (int c = 0; c < RP; ++c) y[c] = (double)p[c];
-  row_rinv<RP>(y, rq, di, x);
+    for (int c = 0; c < RP; ++c) y[c] = (double)p[c];
+    row_rinv<RP>(y, rq, di, x);
 #pragma unroll
-  for (int j = 0; j < RP; ++j) Out[i * RP + j] = (TA)x[j];
-  if (Zt != nullptr) {
+    for (int j = 0; j < RP; ++j) Out[i * RP + j] = (TA)x[j];
+    if (Ot != nullptr) {
 #pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      const float v = j < RP ? (float)x[j] : 0.f;
-      if constexpr (sizeof(TT) == 2)
-        Zt[(int64_t)j * ldz + i] = f32_to_bf16(v);
-      else
-        Zt[(int64_t)j * ldz + i] = (TT)v;
+      for (int j = 0; j < RP; ++j) Ot[(int64_t)j * ldz + i] = (TA)x[j];
+    }
+    if (Zt != nullptr) {
+#pragma unroll
+      for (int j = 0; j < 32; ++j) {
+        const float v = j < RP ? (float)x[j] : 0.f;
+        if constexpr (sizeof(TT) == 2)
+          Zt[(int64_t)j * ldz + i] = f32_to_bf16(v);
+        else
+          Zt[(int64_t)j * ldz + i] = (TT)v;
+      }
     }
   }
 }
@@ -1017,21 +1047,23 @@ int launch_gram_part(const Launch& L, bool f64, int rp, void* P, int64_t rows, d
 void launch_chol_rinv(const Launch& L, bool f64, int rp, const void* P, int64_t rows,
                       const double* Gpart, int nparts, const SmallState* st, double* acc,
                       int reset_acc, int normalise, void* Out, DType zt_type, void* Zt,
-                      int64_t ldz) {
-  const dim3 g((unsigned)((rows + 255) / 256 + (acc != nullptr ? 1 : 0)));
+                      int64_t ldz, void* Ot) {
+  // two blocks per CU at most: longer panels take several rows per thread
+  const int64_t nrow = std::min<int64_t>((rows + kRinvRows - 1) / kRinvRows, 2LL * L.num_cu);
+  const dim3 g((unsigned)(nrow + (acc != nullptr ? 1 : 0)));
   GODEC_RP_SWITCH(rp, {
     if (f64)
-      hipLaunchKernelGGL((k_chol_rinv<double, RP, double>), g, dim3(256), 0, L.stream,
+      hipLaunchKernelGGL((k_chol_rinv<double, RP, double>), g, dim3(rinv_threads<RP>()), 0, L.stream,
                          (const double*)P, rows, Gpart, nparts, st, acc, reset_acc, normalise,
-                         (double*)Out, (double*)nullptr, ldz);
+                         (double*)Out, (double*)nullptr, ldz, (double*)Ot);
     else if (Zt != nullptr && zt_type == BF16)
-      hipLaunchKernelGGL((k_chol_rinv<float, RP, uint16_t>), g, dim3(256), 0, L.stream,
+      hipLaunchKernelGGL((k_chol_rinv<float, RP, uint16_t>), g, dim3(rinv_threads<RP>()), 0, L.stream,
                          (const float*)P, rows, Gpart, nparts, st, acc, reset_acc, normalise,
-                         (float*)Out, (uint16_t*)Zt, ldz);
+                         (float*)Out, (uint16_t*)Zt, ldz, (float*)Ot);
     else
-      hipLaunchKernelGGL((k_chol_rinv<float, RP, float>), g, dim3(256), 0, L.stream,
+      hipLaunchKernelGGL((k_chol_rinv<float, RP, float>), g, dim3(rinv_threads<RP>()), 0, L.stream,
                          (const float*)P, rows, Gpart, nparts, st, acc, reset_acc, normalise,
-                         (float*)Out, (float*)Zt, ldz);
+                         (float*)Out, (float*)Zt, ldz, (float*)Ot);
   });
 }
 
