@@ -23,6 +23,7 @@
 // so all of them see the same bits.  FP64 residuals use the FMA chain resid().
 #include "godec_internal.h"
 #include "k_common.h"
+#include "k_fixedsum.h"
 #include "k_restile.h"
 
 #include <algorithm>
@@ -906,30 +907,6 @@ __global__ __launch_bounds__(256) void k_sel_passN(const T* __restrict__ X, int6
                           &pl_flag, &hit);
 }
 
-// Sum of squares that does not depend on the order of its terms: each square
-// relative to a bound of the whole sum in two limbs of 40 bits (what is cut
-// off is 2^-80 of the bound per term), added as integers.  Bounds outside the
-// range of the scale factor leave it to plain FP64 sums.
-struct FixedSum {
-  double up, down;
-  bool on;
-  __device__ explicit FixedSum(double bound) {
-    on = bound > 1e-280 && bound < 1e280;
-    int ex = 0;
-    if (on) frexp(bound, &ex);
-    up = on ? ldexp(1.0, 40 - ex) : 0.0;
-    down = on ? ldexp(1.0, ex - 40) : 0.0;
-  }
-  __device__ void add(double q, unsigned long long& hi, unsigned long long& lo) const {
-    const double s = q * up, f = floor(s);
-    hi += (unsigned long long)f;
-    lo += (unsigned long long)((s - f) * 0x1p40);
-  }
-  __device__ double value(unsigned long long hi, unsigned long long lo) const {
-    return ((double)hi + (double)lo * 0x1p-40) * down;
-  }
-};
-
 // FINAL: write S from the candidates.  Entries above the last bin go straight
 // to S; the positions of those in it go to the list of k_sel_final.  Wave w of
 // block b takes the candidate segments 4 b + w, 4 b + w + 4 gridDim.x, ...:
@@ -1059,6 +1036,7 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
   if (__ballot((fhi | flo) != 0ull) != 0ull) {
     fhi = wave_sum(fhi);
     flo = wave_sum(flo);
+    FixedSum::carry(fhi, flo);   // counters[3] takes less than 2^40 per wave
     if (lane == 0) {
       atomicAdd(&counters[2], fhi);
       atomicAdd(&counters[3], flo);
@@ -1278,8 +1256,6 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
       // ---- write; the list is in the order in which its blocks came, so the
       // squares are added in fixed point ----
       const unsigned long long lim = sh_lim;
-      const double vmax = (double)key_to_val(bhi, (T*)nullptr);
-      const FixedSum fl(vmax * vmax * (double)nl);
       unsigned long long lo = 0ull, hi = 0ull;
       for (long long e = tid; e < nl; e += NT) {
         const long long c = list[e];
@@ -1290,7 +1266,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
           const unsigned long long pos = atomicAdd(&sh_pos, 1ull);
           if ((long long)pos < take) out.put(nabove + (long long)pos, id, v, cand_x[c]);
           const double q = (double)v * (double)v;
-          if (fl.on) fl.add(q, hi, lo);
+          if (fs.on) fs.add(q, hi, lo);
           else s2 += q;
         }
       }
@@ -1299,7 +1275,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
       vv[tid] = s2;
       __syncthreads();
       s2 = block_sum_fixed(vv, NT, red);
-      if (fl.on) s2 = fl.value(sh_hi, sh_lo);
+      if (fs.on) s2 = fs.value(sh_hi, sh_lo);
     }
     __syncthreads();
     if (tid == 0) {
