@@ -45,7 +45,8 @@ enum DType { F64 = 0, F32 = 1, BF16 = 2 };
 enum SelMode : int {
   SEL_HIST = 0,      // next full-data pass histograms the next digit
   SEL_COLLECT = 1,   // next full-data pass writes candidates >= bucket low
-  SEL_FINAL = 3,     // the candidates hold S: those above [blo, bhi] and part of that bin
+  SEL_REFINE = 2,    // as SEL_FINAL, but the bin is long: the next pass narrows it
+  SEL_FINAL = 3,     // the candidates hold S: those before the last bin and part of it
   SEL_TIES = 4,      // threshold resolved but ties overflow the candidates:
                      // the next full pass collects the entries above it
   SEL_DONE = 5,      // S written by the index-ordered tie scan
@@ -63,6 +64,7 @@ struct SelPlan {
   int pbits;                   // number of resolved key bits
   int kbits;                   // key width (31 for f32, 63 for f64)
   unsigned long long blo, bhi; // at SEL_FINAL: keys of the bin holding the k-th key
+  unsigned long long ilo, ihi; // ... and, where they are ties, its linear indices
   int mode;                    // SelMode
   int slow;                    // a slow exact path was used
   int overflow;                // candidate buffer overflowed

@@ -9,11 +9,11 @@ namespace godec {
 
 // Sum that does not depend on the order of its terms: each term relative to a
 // bound of the whole sum in two limbs of 40 bits (what is cut off is 2^-80 of
-// the bound per term), added as integers.  Every adder carries the low limb
-// into the high one as it goes and once more after adding up lanes, so it
-// hands on less than 2^40: 2^24 adders fit in 64 bits, whatever the number of
-// terms.  Bounds outside the range of the scale factor leave it to plain FP64
-// sums.
+// the bound per term), added as integers.  A low limb holds 2^23 terms: an
+// adder carries it into the high limb at least that often, and once more after
+// adding up lanes, so it hands on less than 2^40 and 2^24 adders fit in 64
+// bits, whatever the number of terms.  Bounds outside the range of the scale
+// factor leave it to plain FP64 sums.
 struct FixedSum {
   double up, down;
   bool on;
@@ -32,7 +32,6 @@ struct FixedSum {
     const double s = q * up, f = floor(s);
     hi += (unsigned long long)f;
     lo += (unsigned long long)((s - f) * 0x1p40);
-    carry(hi, lo);
   }
   __host__ __device__ double value(unsigned long long hi, unsigned long long lo) const {
     return ((double)hi + (double)lo * 0x1p-40) * down;

@@ -9,11 +9,13 @@
 // window of keys around the last threshold, in bins fine enough that the bin
 // holding the k-th key has few entries; the compaction writes everything
 // above that bin to S and lists the bin's entries, and one block takes the
-// rest of S from that list by (|R| descending, index ascending).  In the
-// first iteration, or when the window missed, a pass histograms the top 12
-// bits of every key and a second one collects from the bucket holding the
-// k-th key, with the fine histogram of that bucket (further passes first
-// resolve more digits when the bucket overflows the candidate buffer).
+// rest of S from that list by (|R| descending, index ascending); a long bin
+// (values that lie close together, ties) is first narrowed by further
+// histograms of the candidates.  In the first iteration, or when the window
+// missed, a pass histograms the top 12 bits of every key and a second one
+// collects from the bucket holding the k-th key, with the fine histogram of
+// that bucket (further passes first resolve more digits when the bucket
+// overflows the candidate buffer).
 // Degenerate inputs (more exact ties at the threshold than the candidate
 // buffer holds) fall back to an index-ordered scan.
 //
@@ -627,12 +629,64 @@ __device__ __forceinline__ int fine_bits(int pbits, int kbits) {
   return rem < kHistBits0 ? rem : kHistBits0;
 }
 
+// The digit that a histogram of SEL_REFINE resolves: of the keys in the last
+// bin [blo, bhi] while they differ, then of the indices in [ilo, ihi] (the bin
+// holds ties).  Histogram bins are in selection order, last taken first: keys
+// ascending, indices descending.
+__device__ __forceinline__ int open_bits(unsigned long long lo, unsigned long long hi) {
+  return 64 - __clzll((long long)(lo ^ hi));
+}
+struct RefineDigit {
+  bool by_index;
+  unsigned long long lo, hi, base;
+  int bits, shift;
+  RefineDigit() = default;
+  __device__ explicit RefineDigit(const SelPlan* plan) {
+    by_index = plan->blo == plan->bhi;
+    lo = by_index ? plan->ilo : plan->blo;
+    hi = by_index ? plan->ihi : plan->bhi;
+    const int open = open_bits(lo, hi);
+    base = open < 64 ? (lo >> open) << open : 0ull;
+    bits = open < kHistBits0 ? open : kHistBits0;
+    shift = open - bits;
+  }
+  __device__ unsigned int bin(unsigned long long x) const {
+    const unsigned int d = (unsigned int)((x - base) >> shift);
+    return by_index ? (1u << bits) - 1u - d : d;
+  }
+  // Values of bin b within [lo, hi].
+  __device__ void range(unsigned int b, unsigned long long& l, unsigned long long& h) const {
+    const unsigned long long d = by_index ? (1u << bits) - 1u - b : b;
+    l = base + (d << shift);
+    h = l + ((1ull << shift) - 1ull);
+    l = l > lo ? l : lo;
+    h = h < hi ? h : hi;
+  }
+};
+
+// The last bin (keys [blo, bhi], indices [ilo, ihi]) holds cnt candidates, of
+// which S takes k_rem - cum; the cum ones before them are all taken.  A list
+// up to kLongList long is left to the one block of k_sel_final; a longer one is
+// narrowed first, on all CUs, by the passes that have nothing else to do.
+// A list of 2000 takes k_sel_final 36 us and one of 6600 73, a narrowing pass
+// over 4e5 candidates 14 us (and leaves the final step 6).
+constexpr long long kLongList = 2048;
+__device__ __forceinline__ void set_bin(SelPlan* plan, unsigned long long cum,
+                                        unsigned long long k_rem, unsigned long long cnt) {
+  plan->count_above += (long long)cum;
+  plan->k_rem = (long long)(k_rem - cum);
+  plan->bucket_count = (long long)cnt;
+  const bool open =
+      plan->blo < plan->bhi || (k_rem - cum < cnt && plan->ilo < plan->ihi);
+  plan->mode = (long long)cnt > kLongList && open ? SEL_REFINE : SEL_FINAL;
+}
+
 // Advance the plan after a full-data pass (which histogrammed in SEL_HIST, or
-// collected in SEL_COLLECT or SEL_TIES); in any other mode the pass did
-// nothing and neither does this.  The bin holding the k_rem-th largest key is
-// found with a block-wide suffix scan.  At SEL_FINAL, [blo, bhi] are the keys
-// of the last bin: every candidate above it belongs to S, and k_rem of those
-// inside it.
+// collected in SEL_COLLECT or SEL_TIES) or one over the candidates
+// (SEL_REFINE); in any other mode the pass did nothing and neither does this.
+// The bin holding the k_rem-th largest key is found with a block-wide suffix
+// scan.  At SEL_FINAL every candidate before the last bin ([blo, bhi], [ilo,
+// ihi]) belongs to S, and k_rem of those inside it.
 //
 // Runs either as the kernel k_sel_plan (COH = false) or in the last block to
 // finish the pass it follows (COH = true): then the histogram, which the
@@ -676,14 +730,19 @@ __device__ void sel_plan_core(SelPlan* __restrict__ plan, unsigned long long* __
         plan->mode = SEL_TSCAN;
       } else {
         plan->blo = plan->bhi = plan->prefix;
-        plan->mode = SEL_FINAL;
+        set_bin(plan, 0ull, (unsigned long long)plan->k_rem,
+                (unsigned long long)plan->bucket_count);
       }
     }
     return;
   }
-  if (mode != SEL_HIST && mode != SEL_COLLECT) return;
+  if (mode != SEL_HIST && mode != SEL_COLLECT && mode != SEL_REFINE) return;
+  const bool refine = mode == SEL_REFINE;
+  RefineDigit rd;
+  if (refine) rd = RefineDigit(plan);
   const bool window = mode == SEL_HIST && pbits == 0 && plan->carry_used == 1;
-  const int dbits = mode == SEL_COLLECT ? fine_bits(pbits, KB) : digit_bits(pbits, KB);
+  const int dbits = refine ? rd.bits
+                           : (mode == SEL_COLLECT ? fine_bits(pbits, KB) : digit_bits(pbits, KB));
   const int bins = window ? kHistBins : 1 << dbits;
   // thread t owns PER bins, top bins first; the replicas are summed (and
   // cleared for the next histogram) with every load issued first
@@ -746,6 +805,18 @@ __device__ void sel_plan_core(SelPlan* __restrict__ plan, unsigned long long* __
   if (tid != 0) return;
   int dsel = hit->bin;
   unsigned long long cum = hit->cum, cnt = hit->cnt;
+  if (refine) {
+    if (dsel < 0) {   // fewer than asked for (the rest are zeros): S takes them all
+      plan->mode = SEL_FINAL;
+      return;
+    }
+    unsigned long long lo, hi;
+    rd.range((unsigned int)dsel, lo, hi);
+    if (rd.by_index) { plan->ilo = lo; plan->ihi = hi; }
+    else { plan->blo = lo; plan->bhi = hi; }
+    set_bin(plan, cum, k_rem, cnt);
+    return;
+  }
   if (window) {
     // the pass histogrammed and collected only digits >= carry_dlo: accept
     // when the k-th key lies there, every candidate was kept (there is room
@@ -760,13 +831,11 @@ __device__ void sel_plan_core(SelPlan* __restrict__ plan, unsigned long long* __
     const unsigned long long klo = (unsigned long long)plan->carry_dlo << (KB - kHistBits0);
     unsigned long long lo, hi;
     win_range<T>((unsigned int)dsel, lo, hi);
+    constexpr unsigned long long kTop = (1ull << KB) - 1ull;   // the largest key
     plan->carry_used = 2;
     plan->blo = klo + lo;
-    plan->bhi = hi == ~0ull ? hi : klo + hi;
-    plan->count_above = (long long)cum;
-    plan->k_rem = (long long)(k_rem - cum);
-    plan->bucket_count = (long long)cnt;
-    plan->mode = SEL_FINAL;
+    plan->bhi = hi < kTop - klo ? klo + hi : kTop;
+    set_bin(plan, cum, k_rem, cnt);
     return;
   }
   if (dsel < 0) {
@@ -776,17 +845,17 @@ __device__ void sel_plan_core(SelPlan* __restrict__ plan, unsigned long long* __
     cnt = h[0];
     cum = hit->total - cnt;
   }
+  if (mode == SEL_COLLECT) {
+    const int sh = KB - pbits - dbits;
+    plan->blo = ((plan->prefix << dbits) | (unsigned long long)dsel) << sh;
+    plan->bhi = plan->blo + ((1ull << sh) - 1ull);
+    if (ncand_load<COH>(plan) > plan->cap) plan->overflow = 1;
+    set_bin(plan, cum, k_rem, cnt);
+    return;
+  }
   plan->count_above += (long long)cum;
   plan->k_rem = (long long)(k_rem - cum);
   plan->bucket_count = (long long)cnt;
-  if (mode == SEL_COLLECT) {
-    const int sh = KB - pbits - dbits;
-    plan->blo = (((plan->prefix << dbits) | (unsigned long long)dsel) << sh);
-    plan->bhi = plan->blo + ((1ull << sh) - 1ull);
-    if (ncand_load<COH>(plan) > plan->cap) plan->overflow = 1;
-    plan->mode = SEL_FINAL;
-    return;
-  }
   plan->prefix = (plan->prefix << dbits) | (unsigned long long)dsel;
   plan->pbits = pbits + dbits;
   int next = SEL_HIST;
@@ -842,10 +911,92 @@ __device__ __forceinline__ void plan_in_last_block(SelPlan* __restrict__ plan,
   sel_plan_core<T, unsigned int, true, 256>(plan, hist, h, scratch, hit);
 }
 
+// Add digit d of the lanes with act to cnt (LDS): one atomic for the lanes that
+// share the first one's digit (ordered or equal data give all 64 the same).
+template <typename C>
+__device__ __forceinline__ void count_digit(C* cnt, bool act, unsigned int d) {
+  const unsigned long long m = __ballot(act);
+  if (m == 0ull) return;
+  const int first = __ffsll(m) - 1;
+  const unsigned int d0 = (unsigned int)__builtin_amdgcn_readlane((int)d, first);
+  const unsigned long long same = __ballot(act && d == d0);
+  if ((int)(threadIdx.x & 63) == first) atomicAdd(&cnt[d0], (C)__popcll(same));
+  if (act && d != d0) atomicAdd(&cnt[d], (C)1);
+}
+
+// The last bin.  The index counts only once ties have been narrowed by it.
+struct LastBin {
+  unsigned long long blo, bhi, ilo, ihi;
+  int by_index;   // wave-uniform
+  __device__ LastBin(const SelPlan* plan, unsigned long long itop)
+      : blo(plan->blo), bhi(plan->bhi), ilo(plan->ilo), ihi(plan->ihi) {
+    by_index = __builtin_amdgcn_readfirstlane(ilo > 0ull || ihi < itop ? 1 : 0);
+  }
+  // For N candidates (valid, value): whether they lie before the bin (all
+  // taken) or in it.  id(h) is called only with by_index.
+  template <typename T, int N, typename F>
+  __device__ __forceinline__ void place(const bool (&valid)[N], const T (&v)[N], F id,
+                                        bool (&before)[N], bool (&in)[N]) const {
+#pragma unroll
+    for (int h = 0; h < N; ++h) {
+      const unsigned long long key = abs_key(v[h]);
+      before[h] = valid[h] && key > bhi;
+      in[h] = valid[h] && key >= blo && key <= bhi;
+    }
+    if (by_index) {
+#pragma unroll
+      for (int h = 0; h < N; ++h) {
+        const unsigned long long x = in[h] ? (unsigned long long)id(h) : 0ull;
+        before[h] |= in[h] && x < ilo;
+        in[h] = in[h] && x >= ilo && x <= ihi;
+      }
+    }
+  }
+};
+
+// SEL_REFINE: histogram the next digit of the candidates in the last bin.  The
+// waves take candidate segments as in the compaction.
+template <typename T>
+__device__ __forceinline__ void sel_refine(const SelPlan* __restrict__ plan,
+                                           const int64_t* __restrict__ cand_idx,
+                                           const T* __restrict__ cand_val,
+                                           const unsigned int* __restrict__ seg_count,
+                                           unsigned int* lh) {
+  const int lane = threadIdx.x & 63;
+  const RefineDigit rd(plan);
+  const unsigned long long blo = plan->blo, bhi = plan->bhi;
+  const int ntot = seg_total(plan);
+  for (int sg = kSelWaves * (int)blockIdx.x + (int)(threadIdx.x >> 6); sg < ntot;
+       sg += kSelWaves * (int)gridDim.x) {
+    long long c0, cnt;
+    seg_range(plan, seg_count, sg, c0, cnt);
+    for (long long cb = c0; cb < c0 + cnt; cb += 512) {
+      T v[8];
+#pragma unroll
+      for (int h = 0; h < 8; ++h) {
+        const long long c = cb + 64 * h + lane;
+        v[h] = c < c0 + cnt ? cand_val[c] : T(0);
+      }
+#pragma unroll
+      for (int h = 0; h < 8; ++h) {
+        const long long c = cb + 64 * h + lane;
+        const unsigned long long key = abs_key(v[h]);
+        bool in = c < c0 + cnt && key >= blo && key <= bhi;
+        unsigned long long x = key;
+        if (rd.by_index) {
+          x = in ? (unsigned long long)cand_idx[c] : 0ull;
+          in = in && x >= rd.lo && x <= rd.hi;
+        }
+        count_digit(lh, in, rd.bin(x));
+      }
+    }
+  }
+}
+
 // Later passes (first iteration and fall-backs): the level-0 histogram again
 // (after a missed window), deeper digits, collection from the bucket with its
-// fine histogram, or collection above a resolved threshold whose ties
-// overflow the buffer.
+// fine histogram, collection above a resolved threshold whose ties
+// overflow the buffer, or a histogram of the candidates in a long last bin.
 template <typename T, int RP, int CPT>
 __global__ __launch_bounds__(256) void k_sel_passN(const T* __restrict__ X, int64_t ldx,
                                                    const T* __restrict__ UL,
@@ -859,14 +1010,15 @@ __global__ __launch_bounds__(256) void k_sel_passN(const T* __restrict__ X, int6
                                                    unsigned int* __restrict__ seg_count, int rpt,
                                                    int fuse_plan) {
   const int mode = plan->mode;
-  if (mode != SEL_HIST && mode != SEL_COLLECT && mode != SEL_TIES) return;
+  if (mode != SEL_HIST && mode != SEL_COLLECT && mode != SEL_TIES && mode != SEL_REFINE) return;
   GODEC_SEL_SHARED
   __shared__ int pl_flag;
   __shared__ BinHit hit;
   const unsigned long long prefix = plan->prefix;
   const int pbits = plan->pbits;
-  const bool collect = mode == SEL_COLLECT;
-  const int dbits = collect ? fine_bits(pbits, KB) : digit_bits(pbits, KB);
+  const bool collect = mode == SEL_COLLECT, refine = mode == SEL_REFINE;
+  const int dbits = refine ? RefineDigit(plan).bits
+                           : (collect ? fine_bits(pbits, KB) : digit_bits(pbits, KB));
   PassKeys<T> pk = keys_level0<T>();
   if (pbits > 0) {
     pk.klo = (K)(prefix << (KB - pbits));
@@ -875,14 +1027,16 @@ __global__ __launch_bounds__(256) void k_sel_passN(const T* __restrict__ X, int6
     pk.kmin = pk.klo > 0 ? pk.klo : K(1);
   }
   if (mode == SEL_TIES) pk.kmin = (K)prefix + 1;   // prefix is the full threshold key
-  const bool hist_it = mode == SEL_HIST || (collect && dbits > 0);
+  const bool hist_it = mode == SEL_HIST || refine || (collect && dbits > 0);
   if (hist_it)
     for (int e = tid; e < kHistBins; e += 256) lh[e] = 0u;
   const bool vec_ok = (ldx % 4 == 0) && ((((uintptr_t)X) & 15) == 0);
   sink.pk = pk;
   __syncthreads();
   double s2 = 0.0;
-  if (mode == SEL_HIST)
+  if (refine)
+    sel_refine<T>(plan, cand_idx, cand_val, seg_count, lh);
+  else if (mode == SEL_HIST)
     sel_pass_body<T, RP, CPT, true, false, false>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
                                                   vec_ok, rpt, s2);
   else if (hist_it)
@@ -892,7 +1046,7 @@ __global__ __launch_bounds__(256) void k_sel_passN(const T* __restrict__ X, int6
     sel_pass_body<T, RP, CPT, false, true, false>(X, ldx, UL, VLt, ldv, m, n, lh, us, pk, sink,
                                                   vec_ok, rpt, s2);
   if (collect && hist_it) { GODEC_SEL_SEG_CLOSE(2) }
-  else if (mode != SEL_HIST) { GODEC_SEL_SEG_CLOSE(0) }
+  else if (mode != SEL_HIST && !refine) { GODEC_SEL_SEG_CLOSE(0) }
   __syncthreads();
   if (hist_it) {
     const int bins = 1 << dbits;
@@ -929,13 +1083,14 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
                                                      double* __restrict__ s2sel,
                                                      T* __restrict__ dwn,
                                                      uint16_t* __restrict__ dw16,
-                                                     int64_t lddw, int64_t ncols) {
+                                                     int64_t lddw, int64_t ncols,
+                                                     unsigned long long itop) {
   __shared__ double red[4];
   __shared__ unsigned int wa[4], wt[4];
   __shared__ unsigned long long base_a, base_t;
-  if (plan->mode != SEL_FINAL) return;
+  if (plan->mode != SEL_FINAL && plan->mode != SEL_REFINE) return;   // (no pass left to refine in)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const unsigned long long blo = plan->blo, bhi = plan->bhi;
+  const LastBin bin(plan, itop);
   const unsigned long long acap = (unsigned long long)plan->count_above;
   const double rcols = 1.0 / (double)(ncols > 0 ? ncols : 1);
   const unsigned long long tcap = (unsigned long long)plan->cap;
@@ -955,12 +1110,14 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
         const long long c = cb + 64 * h + lane;
         v[h] = c < c0 + cnt ? cand_val[c] : T(0);
       }
+      bool valid[4], above[4], in[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) valid[h] = cb + 64 * h + lane < c0 + cnt;
+      bin.place(valid, v, [&](int h) { return cand_idx[cb + 64 * h + lane]; }, above, in);
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
-        const long long c = cb + 64 * h + lane;
-        const unsigned long long key = abs_key(v[h]);
-        na += c < c0 + cnt && key > bhi;
-        nt += c < c0 + cnt && key >= blo && key <= bhi;
+        na += above[h];
+        nt += in[h];
       }
     }
   }
@@ -997,15 +1154,15 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
         id[h] = cand_idx[cc];
         xv[h] = cand_x[cc];
       }
+      bool valid[4], above[4], in[4];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) valid[h] = cb + 64 * h + lane < c1;
+      bin.place(valid, v, [&](int h) { return id[h]; }, above, in);
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
         const long long c = cb + 64 * h + lane;
-        const bool valid = c < c1;
-        const unsigned long long key = abs_key(v[h]);
-        const bool above = valid && key > bhi;
-        const bool in = valid && key >= blo && key <= bhi;
-        const unsigned long long ma = __ballot(above), mt = __ballot(in);
-        if (above) {
+        const unsigned long long ma = __ballot(above[h]), mt = __ballot(in[h]);
+        if (above[h]) {
           const unsigned long long pos = ba + __popcll(ma & below);
           if (pos < acap) {
             s_idx[pos] = id[h];
@@ -1024,7 +1181,7 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
             }
           }
         }
-        if (in) {
+        if (in[h]) {
           const unsigned long long pos = bt + __popcll(mt & below);
           if (pos < tcap) list[pos] = c;
         }
@@ -1032,6 +1189,7 @@ __global__ __launch_bounds__(256) void k_sel_compact(SelPlan* __restrict__ plan,
         bt += __popcll(mt);
       }
     }
+    FixedSum::carry(fhi, flo);   // (a segment of the spill region: 16 terms per lane)
   }
   if (__ballot((fhi | flo) != 0ull) != 0ull) {
     fhi = wave_sum(fhi);
@@ -1065,7 +1223,7 @@ __device__ __forceinline__ void carry_update(SelCarry* carry, unsigned long long
 template <typename T>
 __device__ __forceinline__ void plan_reset(SelPlan* plan, unsigned long long* counters,
                                            long long k, long long cap, int nseg,
-                                           const SelCarry* carry) {
+                                           unsigned long long itop, const SelCarry* carry) {
   plan->prefix = 0; plan->k_rem = k; plan->count_above = 0; plan->bucket_count = 0;
   plan->ncand = 0; plan->cap = cap; plan->nnz = 0; plan->pbits = 0;
   plan->kbits = KeyBits<T>::value;
@@ -1077,6 +1235,8 @@ __device__ __forceinline__ void plan_reset(SelPlan* plan, unsigned long long* co
   plan->arrivals = 0u;
   plan->blo = 1ull;
   plan->bhi = 0ull;
+  plan->ilo = 0ull;
+  plan->ihi = itop;
   counters[0] = 0; counters[1] = 0; counters[2] = 0; counters[3] = 0;
 }
 
@@ -1106,17 +1266,67 @@ struct SelOut {
 };
 
 // Digit of the need-th entry in the order of a 256-bin count (from the top
-// bin down, or from the bottom up), and the entries before it.  One thread.
+// bin down, or from the bottom up), and the entries before it.  One wave, four
+// bins per lane, the result on every lane (bin by bin it took up to 10 us).
 __device__ __forceinline__ void digit_at(const unsigned long long* cnt, long long need,
                                          bool from_top, int& digit, unsigned long long& before) {
-  before = 0;
-  int d = 0;
-  for (; d < 255; ++d) {
-    const unsigned long long c = cnt[from_top ? 255 - d : d];
-    if ((long long)(before + c) >= need) break;
-    before += c;
+  const int lane = threadIdx.x & 63;
+  unsigned long long c[4], own = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int d = 4 * lane + u;
+    c[u] = cnt[from_top ? 255 - d : d];
+    own += c[u];
   }
+  unsigned long long inc = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const unsigned long long o = __shfl_up(inc, off, 64);
+    if (lane >= off) inc += o;
+  }
+  const unsigned long long m = __ballot((long long)inc >= need);
+  const int at = m ? __ffsll(m) - 1 : 63;   // (need is at most the total)
+  unsigned long long bef = inc - own;
+  int d = 4 * lane;
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+    if (d == 4 * lane + u && (long long)(bef + c[u]) < need) {
+      bef += c[u];
+      ++d;
+    }
+  before = __shfl(bef, at, 64);
+  d = __shfl(d, at, 64);
   digit = from_top ? 255 - d : d;
+}
+
+// f(valid, c, v, id) for every listed candidate c, its value and its index (the
+// latter two only where asked for), by all threads of a block in step, two
+// entries per thread at a time: a list of kLongList is one trip to memory (with
+// eight, unrolled, the kernel's code grew by half a microsecond of every step).
+template <int NT, bool VAL, bool IDX, typename T, typename F>
+__device__ __forceinline__ void list_each(const int64_t* __restrict__ list, long long nl,
+                                          const T* __restrict__ cand_val,
+                                          const int64_t* __restrict__ cand_idx, F f) {
+  constexpr int B = 2;
+  for (long long e0 = 0; e0 < nl; e0 += B * NT) {
+    long long c[B];
+    T v[B];
+    int64_t id[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const long long e = e0 + b * NT + threadIdx.x;
+      c[b] = list[e < nl ? e : nl - 1];
+    }
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      v[b] = T(0);
+      id[b] = 0;
+      if constexpr (VAL) v[b] = cand_val[c[b]];
+      if constexpr (IDX) id[b] = cand_idx[c[b]];
+    }
+#pragma unroll
+    for (int b = 0; b < B; ++b) f(e0 + b * NT + threadIdx.x < nl, c[b], v[b], id[b]);
+  }
 }
 
 // Last step of a selection, one block: take k_rem of the listed candidates by
@@ -1124,8 +1334,12 @@ __device__ __forceinline__ void digit_at(const unsigned long long* cnt, long lon
 // the working copies, close the plan, carry the threshold, and reset the
 // other iteration's plan (which the next selection uses) and the counters.
 // Usually the list holds a few entries (one histogram bin): up to 1024 are
-// ranked by counting; longer lists by a radix select on the key and then, for
-// ties at the threshold that do not all fit, on the index.
+// ranked by counting; longer lists (up to kLongList entries, or ties) by a
+// radix select on the key and then, for ties at the threshold that do not all
+// fit, on the index (at most itop).
+// Bound there: the lines one CU can have in flight (64-byte lines for 8-byte
+// reads).  MSE step of 100 000 x 512 whole numbers, one entry in ten tied: 0.9
+// ms; with all of the list in this block, one entry in flight per thread, 94.
 constexpr int kFinalThreads = 1024;
 template <typename T>
 __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
@@ -1133,7 +1347,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
     const T* __restrict__ cand_val, const T* __restrict__ cand_x,
     const int64_t* __restrict__ list, unsigned long long* __restrict__ counters,
     SelCarry* __restrict__ carry, const double* __restrict__ s2sel, int nsel, SelOut<T> out,
-    long long k, long long cap, int nseg) {
+    long long k, long long cap, int nseg, unsigned long long itop) {
   constexpr int NT = kFinalThreads;
   __shared__ unsigned long long kk[NT];
   __shared__ int64_t ii[NT];
@@ -1143,7 +1357,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
   __shared__ unsigned long long sh_key, sh_lim, sh_pos, sh_lo, sh_hi;
   __shared__ long long sh_need;
   const int tid = threadIdx.x;
-  if (plan->mode == SEL_FINAL) {
+  if (plan->mode == SEL_FINAL || plan->mode == SEL_REFINE) {
     // sum of S_t^2 over the entries above: the compaction's per-block
     // partials in block order, and the spill region's
     const FixedSum fs(plan->sum_r2);
@@ -1186,31 +1400,32 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
       s2 = block_sum_fixed(vv, NT, red);   // in rank order: the same bits on every run
     } else {
       // ---- the threshold key: 8 bits at a time below the bits blo and bhi share ----
-      const unsigned long long blo = plan->blo;
-      const unsigned long long bhi = plan->bhi < (1ull << KeyBits<T>::value)
-                                         ? plan->bhi
-                                         : (1ull << KeyBits<T>::value) - 1ull;
-      int w = 0;
-      while (w < 64 && (blo >> w) != (bhi >> w)) ++w;   // undecided bits
-      unsigned long long pref = w < 64 ? blo >> w : 0ull;
+      const unsigned long long blo = plan->blo, bhi = plan->bhi;
+      const bool ties = blo == bhi;   // every listed key is the same
+      int w = ties ? 0 : open_bits(blo, bhi);
+      unsigned long long pref = blo >> w;
       long long need = take;
       unsigned long long neq = (unsigned long long)nl;
       while (w > 0) {
         const int step = w < 8 ? w : 8;
         if (tid < 256) cnt[tid] = 0ull;
         __syncthreads();
-        for (long long e = tid; e < nl; e += NT) {
-          const unsigned long long key = abs_key(cand_val[list[e]]);
-          if ((key >> w) == pref) atomicAdd(&cnt[(key >> (w - step)) & ((1u << step) - 1u)], 1ull);
-        }
+        list_each<NT, true, false>(list, nl, cand_val, cand_idx,
+                                   [&](bool valid, long long, T v, int64_t) {
+          const unsigned long long key = abs_key(v);
+          count_digit(cnt, valid && (key >> w) == pref,
+                      (unsigned int)(key >> (w - step)) & ((1u << step) - 1u));
+        });
         __syncthreads();
-        if (tid == 0) {
+        if (tid < 64) {
           int d;
           unsigned long long before;
           digit_at(cnt, need, true, d, before);
-          sh_need = need - (long long)before;
-          sh_pos = cnt[d];
-          sh_key = (pref << step) | (unsigned long long)d;
+          if (tid == 0) {
+            sh_need = need - (long long)before;
+            sh_pos = cnt[d];
+            sh_key = (pref << step) | (unsigned long long)d;
+          }
         }
         __syncthreads();
         pref = sh_key;
@@ -1226,24 +1441,31 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
       }
       // ---- the last index taken among the entries equal to it ----
       if (need < (long long)neq) {
+        int ishift = 0;   // lowest bit of the first digit
+        while ((itop >> ishift) > 255ull) ishift += 8;
         unsigned long long ipref = 0;
         long long ineed = need;
-        for (int shift = 56; shift >= 0; shift -= 8) {
+        for (int shift = ishift; shift >= 0; shift -= 8) {
           if (tid < 256) cnt[tid] = 0ull;
           __syncthreads();
-          for (long long e = tid; e < nl; e += NT) {
-            const long long c = list[e];
-            const unsigned long long x = (unsigned long long)cand_idx[c];
-            if (abs_key(cand_val[c]) == tkey && (shift == 56 || (x >> (shift + 8)) == ipref))
-              atomicAdd(&cnt[(x >> shift) & 255], 1ull);
-          }
+          auto count = [&](bool valid, long long, T v, int64_t id) {
+            const unsigned long long x = (unsigned long long)id;
+            count_digit(cnt,
+                        valid && (ties || abs_key(v) == tkey) &&
+                            (shift == ishift || (x >> (shift + 8)) == ipref),
+                        (unsigned int)(x >> shift) & 255u);
+          };
+          if (ties) list_each<NT, false, true>(list, nl, cand_val, cand_idx, count);
+          else list_each<NT, true, true>(list, nl, cand_val, cand_idx, count);
           __syncthreads();
-          if (tid == 0) {
+          if (tid < 64) {
             int d;
             unsigned long long before;
             digit_at(cnt, ineed, false, d, before);
-            sh_need = ineed - (long long)before;
-            sh_lim = (ipref << 8) | (unsigned long long)d;
+            if (tid == 0) {
+              sh_need = ineed - (long long)before;
+              sh_lim = (ipref << 8) | (unsigned long long)d;
+            }
           }
           __syncthreads();
           ipref = sh_lim;
@@ -1257,19 +1479,26 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
       // squares are added in fixed point ----
       const unsigned long long lim = sh_lim;
       unsigned long long lo = 0ull, hi = 0ull;
-      for (long long e = tid; e < nl; e += NT) {
-        const long long c = list[e];
-        const T v = cand_val[c];
-        const int64_t id = cand_idx[c];
+      list_each<NT, true, true>(list, nl, cand_val, cand_idx,
+                                [&](bool valid, long long c, T v, int64_t id) {
         const unsigned long long key = abs_key(v);
-        if (key > tkey || (key == tkey && (unsigned long long)id <= lim)) {
-          const unsigned long long pos = atomicAdd(&sh_pos, 1ull);
-          if ((long long)pos < take) out.put(nabove + (long long)pos, id, v, cand_x[c]);
-          const double q = (double)v * (double)v;
-          if (fs.on) fs.add(q, hi, lo);
-          else s2 += q;
+        const bool in =
+            valid && (key > tkey || (key == tkey && (unsigned long long)id <= lim));
+        const unsigned long long m = __ballot(in);
+        if (m == 0ull) return;
+        unsigned long long at = 0ull;
+        if ((tid & 63) == 0) at = atomicAdd(&sh_pos, (unsigned long long)__popcll(m));
+        at = __shfl(at, 0, 64) + __popcll(m & ((1ull << (tid & 63)) - 1ull));
+        if (!in) return;
+        if ((long long)at < take) out.put(nabove + (long long)at, id, v, cand_x[c]);
+        const double q = (double)v * (double)v;
+        if (fs.on) {
+          fs.add(q, hi, lo);
+          FixedSum::carry(hi, lo);
+        } else {
+          s2 += q;
         }
-      }
+      });
       atomicAdd(&sh_lo, lo);
       atomicAdd(&sh_hi, hi);
       vv[tid] = s2;
@@ -1286,7 +1515,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_sel_final(
     }
   }
   __syncthreads();
-  if (tid == 0) plan_reset<T>(next, counters, k, cap, nseg, carry);
+  if (tid == 0) plan_reset<T>(next, counters, k, cap, nseg, itop, carry);
 }
 
 // After a TIES collection the candidates hold the entries above the
@@ -1592,10 +1821,11 @@ __global__ __launch_bounds__(256) void k_sel_reset(SelPlan* plan, unsigned long 
                                                    unsigned long long* counters,
                                                    unsigned int* seg_count, long long k,
                                                    long long cap, int nseg,
+                                                   unsigned long long itop,
                                                    const SelCarry* carry) {
   for (int e = threadIdx.x; e < kHistRep * kHistBins; e += blockDim.x) hist[e] = 0ull;
   for (int e = threadIdx.x; e < nseg; e += blockDim.x) seg_count[e] = 0u;
-  if (threadIdx.x == 0) plan_reset<T>(plan, counters, k, cap, nseg, carry);
+  if (threadIdx.x == 0) plan_reset<T>(plan, counters, k, cap, nseg, itop, carry);
 }
 
 // ---------------------------------------------------------------------------
@@ -1892,13 +2122,15 @@ static void select_t(const Launch& L, int rp, const SelectArgs& a) {
   constexpr int KB = KeyBits<T>::value;
   const SelShape s = sel_shape<T>(rp, a.m, a.n, L.num_cu);
   const int nseg = (int)s.g * kSelWaves;
+  const unsigned long long itop = (unsigned long long)(a.m * a.n - 1);   // the last index
   const bool fuse = (uint64_t)a.m * (uint64_t)a.n < (1ull << 32);
   // with room for every entry the first bucket always fits
   const bool all_fit = a.cap >= a.m * a.n;
   const int levels = 1 + (KB - kHistBits0 + kHistBits - 1) / kHistBits;
   if (a.first)
     hipLaunchKernelGGL(k_sel_reset<T>, dim3(1), dim3(256), 0, L.stream, a.plan, a.hist,
-                       a.counters, a.seg_count, (long long)a.k, (long long)a.cap, nseg, a.carry);
+                       a.counters, a.seg_count, (long long)a.k, (long long)a.cap, nseg, itop,
+                       a.carry);
   GODEC_RP_SWITCH(rp, {
     const int fallbacks = all_fit ? 2 : levels + 1;
     if constexpr (sizeof(T) == 4) {
@@ -1924,13 +2156,13 @@ static void select_t(const Launch& L, int rp, const SelectArgs& a) {
   hipLaunchKernelGGL(k_sel_compact<T>, dim3(cg), dim3(256), 0, L.stream, a.plan, a.cand_idx,
                      (const T*)a.cand_val, (const T*)a.cand_x, (const unsigned int*)a.seg_count,
                      a.s_idx, (T*)a.s_val, (T*)a.s_x, a.tie_idx, a.counters,
-                     a.s2part + kSelParts, (T*)a.dwn, dw16, a.lddw, a.n);
+                     a.s2part + kSelParts, (T*)a.dwn, dw16, a.lddw, a.n, itop);
   const SelOut<T> out{a.s_idx, (T*)a.s_val, (T*)a.s_x, (T*)a.dwn, dw16, a.lddw, a.n,
                       1.0 / (double)a.n};
   hipLaunchKernelGGL(k_sel_final<T>, dim3(1), dim3(kFinalThreads), 0, L.stream, a.plan, a.next,
                      a.cand_idx, (const T*)a.cand_val, (const T*)a.cand_x, a.tie_idx, a.counters,
                      a.carry, (const double*)(a.s2part + kSelParts), (int)cg, out,
-                     (long long)a.k, (long long)a.cap, nseg);
+                     (long long)a.k, (long long)a.cap, nseg, itop);
 }
 
 void launch_select(const Launch& L, bool f64, int rp, const SelectArgs& a) {

@@ -31,6 +31,7 @@ static double term(int kind, u64 i) {
 int main(int argc, char** argv) {
   const int kind = atoi(argv[1]);
   const u64 waves = strtoull(argv[2], nullptr, 10), per = strtoull(argv[3], nullptr, 10);
+  const u64 every = strtoull(argv[4], nullptr, 10);   // terms of a lane between carries
   const u64 n = waves * 64 * per;
   // the same sum in 128-bit fixed point, 2^-96 of the bound per unit
   double bound = 0.0;
@@ -48,8 +49,10 @@ int main(int argc, char** argv) {
       for (u64 e = 0; e < per; ++e) {
         const double q = term(kind, (w * per + e) * 64 + l);
         fs.add(q, lhi, llo);
+        if (e % every == every - 1) godec::FixedSum::carry(lhi, llo);
         ref += (unsigned __int128)ldexp(q, 96 - ex);
       }
+      godec::FixedSum::carry(lhi, llo);
       whi += lhi;
       wlo += llo;
     }
@@ -79,11 +82,12 @@ def prog(tmp_path_factory):
 # 6.4e7 terms in one wave and in thousands: the low limbs alone add up to
 # several times 2^64
 @pytest.mark.parametrize("kind", [0, 1, 2, 3])
-@pytest.mark.parametrize("waves,per", [(1, 1000000), (4000, 250), (1, 1), (65000, 1)])
-def test_many_terms(prog, kind, waves, per):
+@pytest.mark.parametrize("waves,per,every", [(1, 1000000, 16), (4000, 250, 1), (1, 1, 1),
+                                             (65000, 1, 1), (1, 1000000, 1 << 23)])
+def test_many_terms(prog, kind, waves, per, every):
     """What each term loses is below 2^-80 of the bound, and the value rounds
     twice."""
-    out = subprocess.run([prog, str(kind), str(waves), str(per)], check=True,
+    out = subprocess.run([prog, str(kind), str(waves), str(per), str(every)], check=True,
                          capture_output=True, text=True).stdout.split()
     got, exact = float(out[0]), float(out[1])
     assert abs(got - exact) <= exact * 2.0 ** -51 + 64 * waves * per * 2.0 ** -80 * exact * 2.01

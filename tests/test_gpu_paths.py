@@ -233,3 +233,62 @@ def test_selection_lists(dt, n, p, K, values):
         seen.append(info["rel_err_sq"])
     for idx, val, info in _mse_identity(X, K, 1):
         assert info["rel_err_sq"] == seen[0]
+
+
+def _close_values(n, p, values, dt, rng):
+    x = rng.standard_normal((n, p))
+    if values == "ints":            # ties
+        return np.round(3 * x).astype(dt)
+    # many different values within 1e-5 of each other, less than a histogram bin
+    return (np.round(8 * x) / 8 * (1 + 1e-5 * rng.random((n, p)))).astype(dt)
+
+
+# a last bin of more than 2048 candidates, narrowed by key or by index: by the
+# two passes there are when the candidates hold every entry, or by more; ties
+# that are cut by the index, and ones that all fit
+@pytest.mark.parametrize("dt,n,p,K,values", [
+    (np.float32, 2048, 512, 400000, "clusters"), (np.float32, 8192, 512, 300000, "clusters"),
+    (np.float64, 3000, 256, 200000, "clusters"), (np.float64, 9000, 256, 150000, "clusters"),
+    (np.float32, 2048, 512, 400000, "ints"), (np.float32, 8192, 512, 300000, "ints"),
+    (np.float64, 3000, 256, 200000, "ints"), (np.float64, 9000, 256, 150000, "ints"),
+    (np.float32, 8192, 512, 0, "ints")])
+def test_long_last_bins(dt, n, p, K, values):
+    """S against a sort by (magnitude, index), its threshold, and the same
+    objective on every run (K = 0: every entry of magnitude 3 or more)."""
+    rng = np.random.default_rng(n + p + K)
+    X = _close_values(n, p, values, dt, rng)
+    K = K or int((np.abs(X) >= 3).sum())
+    ref = topk_indices(X, K)
+    runs = [[info["rel_err_sq"] for idx, val, info in _mse_identity(X, K, 3)
+             if np.array_equal(idx, ref) and np.array_equal(val, X.ravel()[ref])
+             and info["threshold"] == np.abs(val).min()] for _ in range(2)]
+    assert len(runs[0]) == 3 and runs[0] == runs[1]
+
+
+def test_close_values_are_not_slow():
+    """A selection step on values that lie close together stays within five
+    times one on spread values (narrowed on all CUs it is within twice; a list
+    of them in one block was 30 times and more)."""
+    from paper_1309_0302_amd.binding import GoDecMSE
+    n, p, K = 40000, 512, 6000000
+    ms = {}
+    for values in ("normal", "clusters"):
+        g = torch.Generator(device="cuda:0")
+        g.manual_seed(5)
+        x = torch.randn((n, p), generator=g, device="cuda:0")
+        if values == "clusters":
+            x = (x * 2).round() / 2 * (1 + 1e-5 * torch.rand((n, p), generator=g, device="cuda:0"))
+        tr = GoDecMSE(x, [np.zeros(0, np.int64)], [1], K, seed=1)
+        tr.step(2)
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        times = []
+        for _ in range(5):
+            torch.cuda.synchronize()
+            a.record()
+            tr.step(1)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        ms[values] = min(times)
+        tr.close()
+    assert ms["clusters"] <= 5 * ms["normal"], ms
