@@ -254,7 +254,10 @@ __device__ void fold_r(const double* R, double* old, double* acc, int reset, int
 template <typename TA, int RP>
 __global__ __launch_bounds__(512) void kgf_pass(GfPass a) {
   constexpr int E = RP * RP;
-  constexpr int NG = 512 / E;   // row groups of the second round's Gram
+  // row groups of the second round's Gram: at most 32, so that no sum has a
+  // chain of more than 32 (512 partials in a row, at RP = 1, left | |v| - 1 | at
+  // 3e-16 where 1e-16 is reached)
+  constexpr int NG = 512 / E < 32 ? 512 / E : 32;
   extern __shared__ double zs[];   // np x RP
   __shared__ double gs[E], rl[E];
   __shared__ double red[8][16][17];
