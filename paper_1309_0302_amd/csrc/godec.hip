@@ -280,6 +280,17 @@ godec_status validate(int64_t m, int64_t n, int32_t r, int64_t k, int32_t q,
 }
 
 // Whether the L update goes through A = D^T D, and the tiling of that product.
+// A holds u s_1^2 of rounding (s: singular values of D, u: unit roundoff), so
+// that on FP64 data the direction of s_r is off by u (s_1 / s_r)^2 and L by
+// u s_1 / s_r; D and D^T applied to an orthonormal panel leave L at u.  Of
+// exact rank-4 FP64 matrices with s_r / s_1 = 0.1, 1e-2, 1e-3 (500 x 200) L came
+// out at 3e-16, 1.4e-15, 1.5e-14 through A and at 3e-16 each by the panel
+// passes.  FP64 therefore takes this form only where the rank check keeps
+// s_r / s_1 above (r 2^-52)^(1 / 4p), 0.05 for q = 1: the root form with q >= 1
+// and no smaller rank_tol than the default (there 2-9e-16 by both).  At q = 0 the
+// panel path starts from A1 and is off by u s_1 / s_r itself, but by less
+// (1.7e-14 against 5e-14 at 1e-2).  FP32 panels are rounded to 2^-24 by the
+// panel path and not here: 7.5e-8 against 1e-7 at every ratio.
 // The panel has to fit in LDS, and forming A (m n^2 multiply-adds in FP64)
 // has to cost less than the p + q panel passes it shortens.  The candidate
 // arrays of the sparse step, idle during the L update, hold the partial
@@ -289,6 +300,7 @@ void plan_gram_form(godec_ctx* c) {
   const int64_t np = (c->n + kGfTile - 1) / kGfTile * kGfTile;
   if (c->prec != GODEC_PREC_NATIVE || c->n > kGfMaxN || c->rp > 16 || np * c->rp > kGfMaxPanel)
     return;
+  if (c->f64 && (c->lstep == 1 || c->q < 1 || c->rank_tol < c->r * std::ldexp(1.0, -52))) return;
   c->gf_lda = np;
   const double flops = (double)c->m * (double)np * (double)(np + kGfTile);
   if (flops > kGfFlopsPerPass * (c->p + c->q)) return;
@@ -319,6 +331,7 @@ void fill_ctx_params(godec_ctx* c, int64_t m, int64_t n, int32_t r, int64_t k,
   c->kc_a = s.kc_a; c->nct_a = s.nct_a; c->rc_b = s.rc_b; c->nch_b = s.nch_b;
   c->completion = o && (o->support_dev != nullptr || o->support_nnz != 0);
   c->redraw = o && o->redraw_a1;
+  c->lstep = o ? o->lstep : 0;
   plan_gram_form(c);
 }
 
@@ -714,7 +727,6 @@ godec_status godec_init(godec_ctx** out, const void* X_dev, godec_dtype dtype, i
   c->ldx = ldx;
   c->seed = seed;
   c->X = X_dev;
-  c->lstep = opts ? opts->lstep : 0;
   c->warm = opts && opts->warm_start;
   c->stream = opts ? (hipStream_t)opts->stream : nullptr;
   const size_t need = carve(c, nullptr);

@@ -311,3 +311,31 @@ def test_narrow_panel_norms(m, n, r):
         dev.append((V.T @ V - np.eye(r)).astype(np.float64))
         gd.close()
     assert np.sqrt(np.mean(np.square(dev))) <= 4 * 2.0 ** -53
+
+
+# sizes the A = D^T D form takes in the root form; projection form, the rank
+# check off, warm starts (three steps)
+@pytest.mark.parametrize("m,n,r", [(500, 200, 4), (300, 300, 2), (400, 256, 8)])
+@pytest.mark.parametrize("lstep,q,warm,rank_tol,ratio,bar", [
+    (1, 1, 0, 0.0, 1e-3, 16), (1, 2, 0, 0.0, 1e-3, 16), (1, 0, 1, 0.0, 1e-3, 16),
+    (0, 1, 0, 1e-40, 1e-3, 16), (0, 1, 0, 0.0, 0.1, 16)])
+def test_graded_spectrum_fp64(m, n, r, lstep, q, warm, rank_tol, ratio, bar):
+    """L of a matrix of exact rank r whose singular values fall to `ratio` of the
+    largest is the matrix itself.  D and D^T applied to an orthonormal panel
+    keep that to a few roundings (bar: 16 u, u = 2^-53), r.m.s. over six
+    inputs."""
+    from paper_1309_0302_amd.binding import GoDec
+    err = []
+    for seed in range(6):
+        rng = np.random.default_rng(seed)
+        U, V = (np.linalg.qr(rng.standard_normal((k, r)))[0].astype(np.longdouble) for k in (m, n))
+        X = ((U * np.logspace(0, np.log10(ratio), r)) @ V.T).astype(np.float64)
+        gd = GoDec(torch.from_numpy(X).to("cuda:0"), r, 0, q, seed=seed + 1, lstep=lstep,
+                   warm_start=warm, rank_tol=rank_tol)
+        gd.step(3 if warm else 1)
+        UL, VL = (t.cpu().numpy().astype(np.longdouble) for t in gd.factors())
+        # (with the default check an A1 that sees s_r weakly drops it: not L's rounding)
+        if rank_tol > 0 or lstep or gd.info()["rank_eff"] == r:
+            err.append(np.linalg.norm((UL @ VL.T - X).astype(np.float64)) / np.linalg.norm(X))
+        gd.close()
+    assert len(err) >= 2 and np.sqrt(np.mean(np.square(err))) <= bar * 2.0 ** -53
