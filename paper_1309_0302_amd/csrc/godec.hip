@@ -104,7 +104,7 @@ struct godec_ctx {
   bool gram_form = false;
   int64_t gf_lda, gf_rows;
   int gf_split;
-  double *gf_A = nullptr, *gf_Y[2] = {nullptr, nullptr}, *gf_Z = nullptr;
+  double *gf_A = nullptr, *gf_Y[2] = {nullptr, nullptr}, *gf_Z = nullptr, *gf_part = nullptr;
   // state
   int64_t iters_done = 0;
   // BF16_REFINE: the FP32 working copy D is only read by the refinement
@@ -170,6 +170,16 @@ namespace {
 // the general path 30-45 us (25 344 x 200, four passes: 190 us against 94).
 constexpr double kGfFlopsPerPass = 0.75e9;
 
+// Bytes of a fixed support's words, none without one.
+size_t support_words_bytes(const godec_ctx* c) {
+  return c->completion ? align_up(sizeof(SupportWord) * c->m * ((c->n + 63) / 64), 256) : 0;
+}
+// Tiles of A = D^T D on and below the diagonal.
+int64_t gram_tiles(int64_t n) {
+  const int64_t nt = (n + kGfTile - 1) / kGfTile;
+  return nt * (nt + 1) / 2;
+}
+
 // Carve every buffer; returns the total size.  ctx may be a measuring dummy.
 size_t carve(godec_ctx* c, void* base) {
   Carver cv{(char*)base};
@@ -196,11 +206,6 @@ size_t carve(godec_ctx* c, void* base) {
   c->VL = cv.take((size_t)ldd * rp * ta);
   c->VLt = cv.take((size_t)ldd * rp * ta);
   if (c->gram_form) {
-    const size_t panel = (size_t)((c->n + 31) / 32 * 32) * rp * 8;
-    c->gf_A = (double*)cv.take((size_t)c->gf_lda * c->gf_lda * 8);
-    c->gf_Y[0] = (double*)cv.take(panel);
-    c->gf_Y[1] = (double*)cv.take(panel);
-    c->gf_Z = (double*)cv.take(panel);
     c->P0 = c->P1 = c->W = c->Zpart = c->Bp = nullptr;
   } else {
     c->P0 = cv.take((size_t)ldd * rp * ta);
@@ -217,11 +222,38 @@ size_t carve(godec_ctx* c, void* base) {
   c->plan[1] = (SelPlan*)cv.take(sizeof(SelPlan));
   c->hist = (unsigned long long*)cv.take((size_t)kHistReplicas * kHistBins * 8);
   c->counters = (unsigned long long*)cv.take(64);
+  // the selection's scratch: first the candidates and the last bin's list (the
+  // A = D^T D form's buffers lie there too, as a narrow matrix needs them
+  // before the selection runs), then the rest, which a fixed support leaves
+  // unused as well
+  const size_t pool = align_up(cv.off, 256);
   c->cand_idx = (int64_t*)cv.take((size_t)c->cap * 2 * 8);
   c->cand_val = cv.take((size_t)c->cap * 2 * ta);
   c->cand_x = cv.take((size_t)c->cap * 2 * ta);
-  c->seg_count = (unsigned int*)cv.take((size_t)kMaxSeg * 4);
   c->tie_idx = (int64_t*)cv.take((size_t)c->cap * 8);
+  c->seg_count = (unsigned int*)cv.take((size_t)kMaxSeg * 4);
+  const int64_t nwords = (m * c->n + 31) / 32;
+  const int64_t nb = (nwords + 1023) / 1024;
+  c->bitmap = (uint32_t*)cv.take((size_t)nwords * 4);
+  c->wpre = (uint32_t*)cv.take((size_t)nwords * 4);
+  c->bsum = (uint32_t*)cv.take((size_t)nb * 4);
+  c->boff = (unsigned long long*)cv.take((size_t)nb * 8);
+  // a fixed support runs no selection: its words lie in that scratch
+  c->words = nullptr;
+  const size_t words = support_words_bytes(c);
+  if (c->completion) {
+    c->words = base ? (SupportWord*)((char*)base + pool) : nullptr;
+    if (words > cv.off - pool) cv.take(words - (cv.off - pool));
+  }
+  if (c->gram_form) {
+    Carver gv{(char*)base, pool + words};
+    const size_t panel = (size_t)((c->n + 31) / 32 * 32) * rp * 8;
+    c->gf_A = (double*)gv.take((size_t)c->gf_lda * c->gf_lda * 8);
+    c->gf_Y[0] = (double*)gv.take(panel);
+    c->gf_Y[1] = (double*)gv.take(panel);
+    c->gf_Z = (double*)gv.take(panel);
+    c->gf_part = (double*)gv.take((size_t)c->gf_split * gram_tiles(c->n) * kGfTile * kGfTile * 8);
+  }
   c->carry = (SelCarry*)cv.take(sizeof(SelCarry));
   const int64_t kk = std::max<int64_t>(c->k, 1);
   for (int b = 0; b < 2; ++b) {
@@ -229,18 +261,9 @@ size_t carve(godec_ctx* c, void* base) {
     c->s_val[b] = cv.take((size_t)kk * ta);
     c->s_x[b] = cv.take((size_t)kk * ta);
   }
-  const int64_t nwords = (m * c->n + 31) / 32;
-  const int64_t nb = (nwords + 1023) / 1024;
-  c->bitmap = (uint32_t*)cv.take((size_t)nwords * 4);
-  c->wpre = (uint32_t*)cv.take((size_t)nwords * 4);
-  c->bsum = (uint32_t*)cv.take((size_t)nb * 4);
-  c->boff = (unsigned long long*)cv.take((size_t)nb * 8);
   c->norm_x2 = (double*)cv.take(8);
   c->nonfinite = (int*)cv.take(8);
   c->s2part = (double*)cv.take((size_t)std::max(2 * kSelParts, kNormParts) * 8);
-  c->words = c->completion
-                 ? (SupportWord*)cv.take(sizeof(SupportWord) * m * ((c->n + 63) / 64))
-                 : nullptr;
   return align_up(cv.off, 256);
 }
 
@@ -292,9 +315,11 @@ godec_status validate(int64_t m, int64_t n, int32_t r, int64_t k, int32_t q,
 // (1.7e-14 against 5e-14 at 1e-2).  FP32 panels are rounded to 2^-24 by the
 // panel path and not here: 7.5e-8 against 1e-7 at every ratio.
 // The panel has to fit in LDS, and forming A (m n^2 multiply-adds in FP64)
-// has to cost less than the p + q panel passes it shortens.  The candidate
-// arrays of the sparse step, idle during the L update, hold the partial
-// tiles; a matrix too small for one tile there keeps the general path.
+// has to cost less than the p + q panel passes it shortens.  Its buffers lie in
+// the candidate arrays and the list of the sparse step, idle during the L
+// update (behind the words of a fixed support): the workspace is no larger
+// than the panel path's, and a matrix too short for them (40 or 56 bytes per
+// entry: m under about 0.3 n) keeps that path.
 void plan_gram_form(godec_ctx* c) {
   c->gram_form = false;
   const int64_t np = (c->n + kGfTile - 1) / kGfTile * kGfTile;
@@ -304,8 +329,10 @@ void plan_gram_form(godec_ctx* c) {
   c->gf_lda = np;
   const double flops = (double)c->m * (double)np * (double)(np + kGfTile);
   if (flops > kGfFlopsPerPass * (c->p + c->q)) return;
-  const int64_t nt = np / kGfTile, ntile = nt * (nt + 1) / 2;
-  const int64_t fit = c->cap * (16 + 4 * (int64_t)c->ta) / (ntile * kGfTile * kGfTile * 8);
+  const int64_t ntile = gram_tiles(c->n);
+  const int64_t room = c->cap * (24 + 4 * (int64_t)c->ta) - (int64_t)support_words_bytes(c) -
+                       8 * np * (np + 3 * c->rp);   // (all of whole 256-byte lines)
+  const int64_t fit = std::max<int64_t>(room, 0) / (ntile * kGfTile * kGfTile * 8);
   int64_t s = (512 + ntile - 1) / ntile;
   s = std::min<int64_t>(std::min<int64_t>(s, c->mpad / kGfStep), fit);
   if (s < 1) return;
@@ -533,7 +560,7 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
     g.A1 = c->A1;
     g.warm = c->warm && c->iters_done > 0 ? c->VL : nullptr;
     g.ldA = c->gf_lda; g.nsplit = c->gf_split; g.rows_per = c->gf_rows; g.A = c->gf_A;
-    g.part = (double*)c->cand_idx;
+    g.part = c->gf_part;
     for (int h = 0; h < 2; ++h) {
       g.Y[h] = c->gf_Y[h];
       g.G[h] = c->Gpart + (size_t)h * (kGfMaxN / 16) * c->rp * c->rp;

@@ -226,3 +226,28 @@ def test_mse_workspace_size_grows_with_rows():
     a = b.godec_mse_workspace_size(1000, 100, [np.arange(10)], [2], 50, b.GODEC_F32)
     c = b.godec_mse_workspace_size(1000, 100, [np.arange(900)], [2], 50, b.GODEC_F32)
     assert c > a > 1000 * 100 * 4
+
+
+# (m, n, r, k, q, dtype, prec, fixed support, bytes): what these problems needed
+# when the support was kept as run starts and every matrix took the panel
+# passes; the first six fit the 128 MiB of godec_solve_static only just, or are
+# many times wider than tall
+@pytest.mark.parametrize("m,n,r,k,q,dtype,prec,fixed,most", [
+    (4200, 4200, 5, 1000, 1, 1, 0, True, 132203008), (2608, 2567, 9, 22127, 1, 0, 0, True, 133817856),
+    (3201, 3792, 13, 0, 1, 1, 1, True, 133367552), (1477, 11227, 11, 0, 1, 1, 0, True, 132844800),
+    (59, 417, 2, 18, 2, 0, 0, True, 2049536), (55, 511, 2, 12, 2, 0, 0, False, 2246144),
+    (71, 457, 4, 100, 1, 1, 0, False, 2121472), (25344, 200, 2, 395000, 1, 1, 0, False, 121299456),
+    (500, 500, 5, 12500, 2, 0, 0, False, 17750016), (400, 300, 5, 6000, 2, 1, 0, False, 6523392),
+    (55038, 19565, 12, 1, 0, 1, 0, True, 4803859968)])
+def test_workspace_does_not_grow(m, n, r, k, q, dtype, prec, fixed, most):
+    """Support words and the narrow form's buffers lie in the sparse step's
+    scratch, so a workspace that was large enough stays so."""
+    lib = b.load()
+    o = b.godec_opts()
+    lib.godec_opts_default(ctypes.byref(o))
+    o.prec = prec
+    if fixed:
+        o.support_dev, o.support_nnz = 256, k   # (host arithmetic: not read)
+    need = ctypes.c_size_t()
+    assert lib.godec_workspace_size(m, n, r, k, q, dtype, ctypes.byref(o), ctypes.byref(need)) == 0
+    assert 0 < need.value <= most

@@ -339,3 +339,39 @@ def test_graded_spectrum_fp64(m, n, r, lstep, q, warm, rank_tol, ratio, bar):
             err.append(np.linalg.norm((UL @ VL.T - X).astype(np.float64)) / np.linalg.norm(X))
         gd.close()
     assert len(err) >= 2 and np.sqrt(np.mean(np.square(err))) <= bar * 2.0 ** -53
+
+
+# the narrow form's buffers in the sparse step's scratch: beside a fixed
+# support's words, no selection (its counts lie behind them), the shortest
+# matrices that hold them and the first ones that do not, the widest
+@pytest.mark.parametrize("m,n,r,kind", [
+    (120, 400, 4, "sparse"), (160, 400, 4, "sparse"), (130, 512, 8, "sparse"),
+    (320, 512, 8, "sparse"), (300, 400, 4, "none"), (300, 400, 4, "support"),
+    (180, 400, 4, "support"), (2000, 64, 16, "support")])
+@pytest.mark.parametrize("dt,tol", [(np.float64, 1e-10), (np.float32, 1e-5)])
+def test_narrow_buffers_share_the_scratch(m, n, r, kind, dt, tol):
+    """Three steps against the oracle's update on the library's own S (the bars
+    of the per-step parity tests)."""
+    from oracle import godec_ref as g
+    from oracle.rng_ref import a1_gaussian
+    from paper_1309_0302_amd.binding import GoDec
+    w = wl.tiny(m, n, r, seed=m + n, dtype=dt)
+    k, sup = (0 if kind == "none" else w.k), None
+    if kind == "support":
+        sup = np.sort(np.random.default_rng(m).permutation(m * n)[:k]).astype(np.int64)
+    gd = GoDec(torch.from_numpy(w.X).to("cuda:0"), r, k, 1, seed=9,
+               support=None if sup is None else torch.from_numpy(sup).to("cuda:0"))
+    A1 = a1_gaussian(9, n, r)
+    X = w.X.astype(np.float64)
+    D = X.copy()
+    for _ in range(3):
+        gd.step(1)
+        assert g.rel_fro(gd.L_dense().cpu().numpy().astype(np.float64),
+                         g.brp_power(D, A1, 1).L) <= tol
+        idx, val = (t.cpu().numpy() for t in gd.S())
+        R = gd.residual().cpu().numpy()
+        assert np.array_equal(idx, topk_indices(R, k) if sup is None else sup)
+        assert np.array_equal(val, R.ravel()[idx])
+        D = X.copy()
+        D.ravel()[idx] -= val
+    gd.close()
