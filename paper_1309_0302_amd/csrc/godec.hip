@@ -439,11 +439,12 @@ void draw_many(uint64_t seed0, int count, int64_t n, int32_t r, double* out) {
 Launch launch_of(const godec_ctx* c) { return Launch{c->stream, c->num_cu}; }
 
 // Kernel classes timed by godec_profile.
-enum ProfClass { PC_APPLY = 0, PC_APPLY_T, PC_APPLY_BF16, PC_APPLY_T_BF16, PC_SEL_PASS,
-                 PC_COUNT };
+enum ProfClass { PC_APPLY = 0, PC_APPLY_T, PC_APPLY_BF16, PC_APPLY_T_BF16, PC_GRAM, PC_SEL_PASS,
+                 PC_FIXED_PASS, PC_COUNT };
 const char* kProfNames[PC_COUNT] = {"mm_a(D*Z)", "mm_b(W^T*D)", "mm_a_bf16(D*Z)",
-                                    "mm_b_bf16(W^T*D)", "select_pass(hist)"};
-const double kProfElemBytes[PC_COUNT] = {0, 0, 2, 2, 0};   // 0: element size of X
+                                    "mm_b_bf16(W^T*D)", "gram(D^T*D)", "select_pass(hist)",
+                                    "fixed_support_pass"};
+const double kProfElemBytes[PC_COUNT] = {0, 0, 2, 2, 0, 0, 0};   // 0: element size of X
 
 hipEvent_t prof_event(godec_ctx* c) {
   if (c->pool_used == c->pool.size()) {
@@ -567,6 +568,9 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
     }
     g.Zq = c->gf_Z; g.st = c->st; g.Kp = c->Kp;
     g.VL = c->VL; g.VLt = c->VLt; g.UL = c->UL; g.ldv = c->ldd;
+    ProfScope pg(c, PC_GRAM, true), pu(c, PC_APPLY, true);
+    g.ev_gram[0] = pg.a; g.ev_gram[1] = pg.b;
+    g.ev_ul[0] = pu.a; g.ev_ul[1] = pu.b;
     launch_gram_form(L, g);
   } else {
   if (refine && !c->d_native_valid) {
@@ -607,9 +611,10 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
   chol_qr(c, c->P0, c->VL, c->st->R2, 0, tdb, false, c->VLt);
   if (c->lstep == 1) {
     // projection form: L = D Q2 Q2^T, i.e. U_L = D Q2 and V_L = Q2
-    if (c->f64)
+    if (c->f64) {
+      ProfScope ps(c, PC_APPLY);
       launch_apply(L, tdb, c->rp, Db, c->ldd, c->m, c->VL, c->UL);
-    else
+    } else
       mfma_apply(c, tdb, Db, c->VL, true, nullptr, (float*)c->UL);
   } else {
   // ---- B chain: (D^T D)^q Q2 = Y_q T, then B' = D Y_q ----
@@ -618,9 +623,10 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
     gram_chol(c, tdb, Db, in, true, c->P1, c->P0, c->st->T, j == 0, tdb);
     in = c->P0;
   }
-  if (c->f64)
+  if (c->f64) {
+    ProfScope ps(c, PC_APPLY);
     launch_apply(L, tdb, c->rp, Db, c->ldd, c->m, in, c->Bp);
-  else
+  } else
     mfma_apply(c, tdb, Db, in, true, nullptr, (float*)c->Bp);
   // ---- core ----
   const int np = launch_gram_part(L, c->f64, c->rp, c->Bp, c->m, c->Gpart);
@@ -652,7 +658,7 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
     a.rx = (const float*)c->s_x[prev];
     a.rplan = c->plan[prev];
   }
-  if (c->prof) {
+  if (c->prof && !c->completion) {
     a.ev_a = prof_event(c);
     a.ev_b = prof_event(c);
     if (a.ev_a && a.ev_b) c->recs.push_back({PC_SEL_PASS, a.ev_a, a.ev_b});
@@ -674,13 +680,15 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
   a.dwn = upd_native ? c->D : nullptr;
   a.dw16 = mixed ? (uint16_t*)c->D16 : nullptr;
   a.lddw = c->ldd;
-  if (c->completion)
+  if (c->completion) {
+    ProfScope ps(c, PC_FIXED_PASS);
     launch_fixed_support(L, c->f64, c->rp, c->X, c->ldx, c->UL, c->VLt, c->ldd, c->m, c->n,
                          c->words, c->support_nnz, c->s_val[nxt],
                          mixed ? c->s_x[nxt] : nullptr, a.dwn, a.dw16, c->ldd, c->plan[nxt],
                          (double*)c->hist);
-  else
+  } else {
     launch_select(L, c->f64, c->rp, a);
+  }
   c->cur = nxt;
   c->iters_done += 1;
   HIP_TRY(hipGetLastError());

@@ -470,6 +470,8 @@ struct GramForm {
   SmallState* st;
   void *Kp, *VL, *VLt, *UL;
   int64_t ldv;
+  hipEvent_t ev_gram[2] = {nullptr, nullptr};  // optional: start and end of the two
+  hipEvent_t ev_ul[2] = {nullptr, nullptr};    // kernels that read D
 };
 void launch_gram_form(const Launch& L, const GramForm& g);
 

@@ -20,6 +20,8 @@
 // latency and not by data.  Here a pass is one launch of n / 16 blocks: every
 // thread repeats the r x r work (a few hundred FP64 operations) instead of
 // waiting for one block that does it.
+#include <hip/hip_ext.h>
+
 #include "godec_internal.h"
 #include "k_chol.h"
 #include "k_common.h"
@@ -553,11 +555,11 @@ void launch_gram_form(const Launch& L, const GramForm& g) {
   const int ntile = nt * (nt + 1) / 2;
   const dim3 gg((unsigned)ntile, (unsigned)g.nsplit);
   if (g.f64)
-    hipLaunchKernelGGL(kgf_gram<double>, gg, dim3(256), 0, L.stream, (const double*)g.D, g.ldd,
-                       g.mpad, g.rows_per, g.part);
+    hipExtLaunchKernelGGL(kgf_gram<double>, gg, dim3(256), 0, L.stream, g.ev_gram[0],
+                          g.ev_gram[1], 0, (const double*)g.D, g.ldd, g.mpad, g.rows_per, g.part);
   else
-    hipLaunchKernelGGL(kgf_gram<float>, gg, dim3(256), 0, L.stream, (const float*)g.D, g.ldd,
-                       g.mpad, g.rows_per, g.part);
+    hipExtLaunchKernelGGL(kgf_gram<float>, gg, dim3(256), 0, L.stream, g.ev_gram[0],
+                          g.ev_gram[1], 0, (const float*)g.D, g.ldd, g.mpad, g.rows_per, g.part);
   hipLaunchKernelGGL(kgf_sum, dim3((unsigned)ntile, kGfTile * kGfTile / 256), dim3(256), 0,
                      L.stream, (const double*)g.part, ntile, g.nsplit, g.ldA, g.A);
   GfPass a{};
@@ -601,13 +603,14 @@ void launch_gram_form(const Launch& L, const GramForm& g) {
   const double* K = g.proj ? nullptr : g.st->K;
   GF_RP_SWITCH(g.rp, {
     if (g.f64)
-      hipLaunchKernelGGL((kgf_ul_f64<RP>), dim3((unsigned)((g.m + 15) / 16)), dim3(512),
-                         sizeof(double) * a.np * RP, L.stream, (const double*)g.D, g.ldd, g.m,
-                         a.np, (const double*)g.Zq, K, (double*)g.UL);
+      hipExtLaunchKernelGGL((kgf_ul_f64<RP>), dim3((unsigned)((g.m + 15) / 16)), dim3(512),
+                            sizeof(double) * a.np * RP, L.stream, g.ev_ul[0], g.ev_ul[1], 0,
+                            (const double*)g.D, g.ldd, g.m, a.np, (const double*)g.Zq, K,
+                            (double*)g.UL);
     else
-      hipLaunchKernelGGL((kgf_ul_f32<RP>), dim3((unsigned)((g.m + 63) / 64)), dim3(256), 0,
-                         L.stream, (const float*)g.D, g.ldd, g.m, a.np, (const double*)g.Zq, K,
-                         (float*)g.UL);
+      hipExtLaunchKernelGGL((kgf_ul_f32<RP>), dim3((unsigned)((g.m + 63) / 64)), dim3(256), 0,
+                            L.stream, g.ev_ul[0], g.ev_ul[1], 0, (const float*)g.D, g.ldd, g.m,
+                            a.np, (const double*)g.Zq, K, (float*)g.UL);
   });
 }
 

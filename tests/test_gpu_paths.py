@@ -375,3 +375,29 @@ def test_narrow_buffers_share_the_scratch(m, n, r, kind, dt, tol):
         D = X.copy()
         D.ravel()[idx] -= val
     gd.close()
+
+
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+@pytest.mark.parametrize("m,n,lstep,support,names", [
+    (900, 200, 0, False, {"gram(D^T*D)": 1, "mm_a(D*Z)": 1, "select_pass(hist)": 1}),
+    (900, 200, 0, True, {"gram(D^T*D)": 1, "mm_a(D*Z)": 1, "fixed_support_pass": 1}),
+    (300, 600, 0, False, {"mm_a(D*Z)": 5, "mm_b(W^T*D)": 4, "select_pass(hist)": 1}),
+    (300, 600, 1, True, {"mm_a(D*Z)": 4, "mm_b(W^T*D)": 3, "fixed_support_pass": 1})])
+def test_timing_covers_the_streaming_kernels(m, n, lstep, support, names, dt):
+    """godec_profile reports every kernel that streams D or X, with its launches
+    (per iteration at q = 1: the passes of the general chain; one Gram and U_L
+    in the narrow form), a time and the operand's bytes."""
+    from paper_1309_0302_amd.binding import GoDec
+    w = wl.tiny(m, n, 4, seed=3, dtype=dt)
+    sup = torch.arange(0, m * n, 7, device="cuda:0") if support else None
+    gd = GoDec(torch.from_numpy(w.X).to("cuda:0"), 4, sup.numel() if support else w.k, 1, seed=9,
+               lstep=lstep, support=sup)
+    gd.step(1)
+    gd.profile(True)
+    gd.step(3)
+    stats = {s["name"]: s for s in gd.profile_read()}
+    gd.profile(False)
+    assert {k: s["launches"] for k, s in stats.items()} == {k: 3 * v for k, v in names.items()}
+    for s in stats.values():
+        assert 0 < s["total_ms"] < 1000 and s["bytes_per_launch"] == m * n * np.dtype(dt).itemsize
+    gd.close()
