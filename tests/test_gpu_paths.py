@@ -401,3 +401,37 @@ def test_timing_covers_the_streaming_kernels(m, n, lstep, support, names, dt):
     for s in stats.values():
         assert 0 < s["total_ms"] < 1000 and s["bytes_per_launch"] == m * n * np.dtype(dt).itemsize
     gd.close()
+
+
+# exactly rank-deficient X on the panel path (n > 512): inactive columns in the
+# Cholesky QR launches, r_eff below the padded width in later cores
+@pytest.mark.parametrize("r,true", [(6, 3), (20, 7), (24, 1)])
+@pytest.mark.parametrize("lstep,warm,q", [(0, 0, 1), (0, 1, 1), (1, 0, 1), (1, 1, 0), (0, 0, 2)])
+@pytest.mark.parametrize("dt,tol", [(np.float64, 1e-10), (np.float32, 1e-5)])
+def test_rank_drop_on_the_panel_path(r, true, lstep, warm, q, dt, tol):
+    """L is X and the oracle's L after each of three steps; the root form's check
+    leaves the true rank; V_L has that many orthonormal columns and zeros (the
+    bars of the per-step parity tests).  In the projection form at q = 0 one
+    Cholesky QR step decides, on a Gram as ill-conditioned as A1's part in X's
+    row space: a direction of rounding noise may stay, orthonormal to the rest."""
+    from oracle import godec_ref as g
+    from oracle.rng_ref import a1_gaussian
+    from paper_1309_0302_amd.binding import GoDec
+    m, n = 650, 600
+    rng = np.random.default_rng(100 * r + true)
+    X = (rng.standard_normal((m, true)) @ rng.standard_normal((true, n))).astype(dt)
+    X64 = X.astype(np.float64)
+    gd = GoDec(torch.from_numpy(X).to("cuda:0"), r, 0, q, seed=9, lstep=lstep, warm_start=warm)
+    A1 = a1_gaussian(9, n, r)
+    for _ in range(3):
+        gd.step(1)
+        ref = g.brp_projection(X64, A1, q) if lstep else g.brp_power(X64, A1[:, :r], q)
+        L = gd.L_dense().cpu().numpy().astype(np.float64)
+        assert g.rel_fro(L, ref.L) <= tol and g.rel_fro(L, X64) <= tol
+        V = gd.factors()[1].cpu().numpy().astype(np.float64)
+        on = np.abs(V).max(axis=0) > 0
+        assert on.sum() == true if q > 0 else true <= on.sum() <= r
+        assert np.abs(V[:, on].T @ V[:, on] - np.eye(on.sum())).max() <= 10 * tol
+    info = gd.info()
+    assert info["rank_eff"] == (r if lstep else true) and bool(info["flags"] & 2) == (not lstep)
+    gd.close()
