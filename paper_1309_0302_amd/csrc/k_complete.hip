@@ -40,9 +40,9 @@ __global__ __launch_bounds__(256) void kc_check(const int64_t* __restrict__ supp
 
 // The list as the pass reads it: for every row i and 64-column word w of it
 // the word's membership bits and the list position of its first entry.  One
-// thread per word: a lower bound in the ascending list, then the run itself.
-// Any list keeps the reads in bounds; what an invalid one leaves here is not
-// used.
+// thread per word: a lower bound in the ascending list, then the run itself, at
+// most 64 entries.  Any list keeps the reads in bounds and the runs short (one
+// of equal entries too); what an invalid one leaves here is not used.
 __global__ __launch_bounds__(256) void kc_runs(const int64_t* __restrict__ support, int64_t nnz,
                                                int64_t m, int64_t n, int64_t nw,
                                                SupportWord* __restrict__ words) {
@@ -60,7 +60,8 @@ __global__ __launch_bounds__(256) void kc_runs(const int64_t* __restrict__ suppo
   SupportWord o;
   o.start = lo;
   o.bits = 0ull;
-  for (int64_t e = lo; e < nnz; ++e) {
+  const int64_t last = lo + 64 < nnz ? lo + 64 : nnz;
+  for (int64_t e = lo; e < last; ++e) {
     const int64_t id = support[e];
     if (id < key || id >= end) break;
     o.bits |= 1ull << (id - key);

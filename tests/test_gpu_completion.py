@@ -158,3 +158,33 @@ def test_completion_with_other_l_updates(lstep, warm):
     print(f"\n[completion] lstep={lstep} warm={warm}: L vs truth {eL:.2e}", flush=True)
     assert eL <= 1e-10
     gd.close()
+
+
+@pytest.mark.parametrize("kind", ["equal", "last twice", "descending", "negative", "past the end"])
+def test_bad_supports_are_refused_at_once(kind):
+    """A list that is not strictly ascending within the matrix is GODEC_E_INVAL,
+    whatever it holds, in the time a good one takes (a list of equal entries is
+    one long run of the first word; the good list here is set up in
+    milliseconds)."""
+    import time
+    from paper_1309_0302_amd.binding import GoDec, GodecError
+    m, n, k = 5000, 4000, 10000000
+    X = torch.randn((m, n), device="cuda:0")
+    good = torch.arange(0, 2 * k, 2, device="cuda:0")
+    GoDec(X, 2, k, 1, support=good).close()
+    bad = good.clone()
+    if kind == "equal":
+        bad.zero_()
+    elif kind == "last twice":
+        bad[-1] = bad[-2]
+    elif kind == "descending":
+        bad = good.flip(0).contiguous()
+    elif kind == "negative":
+        bad[0] = -1
+    else:
+        bad[-1] = m * n
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    with pytest.raises(GodecError) as ei:
+        GoDec(X, 2, k, 1, support=bad)
+    assert ei.value.status == 1 and time.perf_counter() - t < 1.0
