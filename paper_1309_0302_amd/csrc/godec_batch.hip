@@ -301,9 +301,10 @@ godec_status autotune(godec_batch* b) {
     float ms = 0.f;
     HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
     // The times of one split vary by up to 2%, and the split sets the order of
-    // the FP32 sums: a later candidate has to win by more than that, so that
-    // a shape gets the same split, and the same bits, in every process (32
-    // problems of up to 20 000 x 400: 128, 256 and 512 rows within 3%).
+    // the FP32 sums.  A later candidate has to win by more than that, which
+    // makes it rare, not impossible, that a shape gets another split, and other
+    // last bits, in another process (32 problems of up to 20 000 x 400: 128,
+    // 256 and 512 rows within 3%).  Within a process the choice is kept.
     if (ms < 0.98f * best) {
       best = ms;
       best_rows = rows;

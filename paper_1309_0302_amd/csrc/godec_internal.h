@@ -195,7 +195,8 @@ struct SelectArgs {
   // row-major; the bf16 copy for FP32 X only) at every entry of the new S:
   // by the compaction for the entries above the last bin, by the final step
   // for those taken from it, or by the tie-value pass for every entry when
-  // the threshold scan wrote the list
+  // the threshold scan wrote the list.  dwn may be X itself (with ldx = lddw):
+  // no kernel that writes it reads X at another entry
   void* dwn = nullptr;      // in the type of X
   uint16_t* dw16 = nullptr;
   int64_t lddw = 0;

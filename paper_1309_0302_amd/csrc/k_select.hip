@@ -1740,10 +1740,11 @@ __global__ __launch_bounds__(256) void k_sel_ties_stream(const T* __restrict__ X
 // After an index-ordered tie scan: restore the sign of the tied entries, whose
 // stored value is the residual, recomputed here from X and the factors (same
 // arithmetic as the selection), and write X - S into the working copies at
-// every entry.  FP32: one wavefront per entry, which evaluates the entry's
-// aligned tile.
+// every entry (dwn may be X itself: no restrict on either; an entry is read and
+// written by the same thread).  FP32: one wavefront per entry, which evaluates
+// the entry's aligned tile.
 template <typename T, int RP>
-__global__ __launch_bounds__(256) void k_fix_tie_values(const T* __restrict__ X, int64_t ldx,
+__global__ __launch_bounds__(256) void k_fix_tie_values(const T* X, int64_t ldx,
                                                         const T* __restrict__ UL,
                                                         const T* __restrict__ VL,
                                                         const T* __restrict__ VLt, int64_t ldv,
@@ -1752,7 +1753,7 @@ __global__ __launch_bounds__(256) void k_fix_tie_values(const T* __restrict__ X,
                                                         int64_t* __restrict__ s_idx,
                                                         T* __restrict__ s_val,
                                                         T* __restrict__ s_x,
-                                                        T* __restrict__ dwn,
+                                                        T* dwn,
                                                         uint16_t* __restrict__ dw16,
                                                         int64_t lddw) {
   if (plan->mode != SEL_DONE) return;
