@@ -45,6 +45,7 @@ struct godec_batch {
   double rank_tol = 0.0;
   hipStream_t stream = nullptr;
   int num_cu = 256;
+  std::mutex sort_mu;          // held by godec_batch_get_S (its scratch is shared)
   std::vector<HostProb> hp;
   std::vector<BProb> tab;      // host copy of the device table
   std::vector<BItem> items;    // host copy of the work items (source of async copies)
@@ -517,6 +518,8 @@ godec_status godec_batch_get_S(godec_batch* b, int32_t i, int64_t* idx_dev, void
     // Bound: the scattered list reads and writes.  On the device a list of
     // 1.5e5 entries takes about 50 us; copied to the host, sorted there and
     // copied back it took 4 ms.
+    // Several threads may fetch lists at once: one sort at a time, to its end.
+    std::lock_guard<std::mutex> lk(b->sort_mu);
     const HostProb& h = b->hp[i];
     const int64_t nwords = ceil_div(h.m * h.n, 32), nb = ceil_div(nwords, 1024);
     Carver cv{(char*)b->tab[i].tie_idx};

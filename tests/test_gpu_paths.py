@@ -435,3 +435,31 @@ def test_rank_drop_on_the_panel_path(r, true, lstep, warm, q, dt, tol):
     info = gd.info()
     assert info["rank_eff"] == (r if lstep else true) and bool(info["flags"] & 2) == (not lstep)
     gd.close()
+
+
+def test_batch_lists_from_two_threads():
+    """The same problem's S fetched by two threads at once: each gets the whole
+    sorted list (the index sort has one scratch per problem)."""
+    import threading
+    from paper_1309_0302_amd.binding import GoDecBatch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(3)
+    X = torch.randn((4000, 300), generator=g, device="cuda:0")
+    b = GoDecBatch([(X, 2, 100000, 3), (X * 2, 2, 60000, 4)], 1)
+    b.step(2)
+    ref = [tuple(t.clone() for t in b.S(i)) for i in (0, 1)]
+    wrong = []
+
+    def fetch(i):
+        for _ in range(200):
+            idx, val = b.S(i)
+            if not (torch.equal(idx, ref[i][0]) and torch.equal(val, ref[i][1])):
+                wrong.append(i)
+
+    th = [threading.Thread(target=fetch, args=(i,)) for i in (0, 0, 1, 0)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    assert not wrong
+    b.close()
