@@ -547,39 +547,40 @@ void gram_chol(godec_ctx* c, DType td, const void* Dsrc, const void* in, bool zt
   chol_qr(c, tmp, out, acc, reset, next_td, parts);
 }
 
-godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
+// L update of a narrow matrix through A = D^T D (k_gramform.hip).
+void l_update_narrow(godec_ctx* c) {
+  GramForm g;
+  g.f64 = c->f64; g.rp = c->rp; g.r = c->r; g.p = c->p; g.q = c->q;
+  g.proj = c->lstep == 1; g.rank_tol = c->rank_tol;
+  g.m = c->m; g.n = c->n; g.mpad = c->mpad; g.ldd = c->ldd; g.D = c->D;
+  g.A1 = c->A1;
+  g.warm = c->warm && c->iters_done > 0 ? c->VL : nullptr;
+  g.ldA = c->gf_lda; g.nsplit = c->gf_split; g.rows_per = c->gf_rows; g.A = c->gf_A;
+  g.part = c->gf_part;
+  for (int h = 0; h < 2; ++h) {
+    g.Y[h] = c->gf_Y[h];
+    g.G[h] = c->Gpart + (size_t)h * (kGfMaxN / 16) * c->rp * c->rp;
+  }
+  g.Zq = c->gf_Z; g.st = c->st; g.Kp = c->Kp;
+  g.VL = c->VL; g.VLt = c->VLt; g.UL = c->UL; g.ldv = c->ldd;
+  ProfScope pg(c, PC_GRAM, true), pu(c, PC_APPLY, true);
+  g.ev_gram[0] = pg.a; g.ev_gram[1] = pg.b;
+  g.ev_ul[0] = pu.a; g.ev_ul[1] = pu.b;
+  launch_gram_form(launch_of(c), g);
+}
+
+// L update by panel passes over D; refine: an FP32 iteration of the BF16 form.
+godec_status l_update_panels(godec_ctx* c, bool refine) {
   const Launch L = launch_of(c);
   const DType native = c->f64 ? F64 : F32;
   const bool mixed = c->prec == GODEC_PREC_BF16_REFINE;
-  const bool refine = mixed && total > 0 && t >= total - c->refine_iters;
-  const int64_t kk = std::max<int64_t>(c->k, 1);
-  if (c->gram_form) {
-    GramForm g;
-    g.f64 = c->f64; g.rp = c->rp; g.r = c->r; g.p = c->p; g.q = c->q;
-    g.proj = c->lstep == 1; g.rank_tol = c->rank_tol;
-    g.m = c->m; g.n = c->n; g.mpad = c->mpad; g.ldd = c->ldd; g.D = c->D;
-    g.A1 = c->A1;
-    g.warm = c->warm && c->iters_done > 0 ? c->VL : nullptr;
-    g.ldA = c->gf_lda; g.nsplit = c->gf_split; g.rows_per = c->gf_rows; g.A = c->gf_A;
-    g.part = c->gf_part;
-    for (int h = 0; h < 2; ++h) {
-      g.Y[h] = c->gf_Y[h];
-      g.G[h] = c->Gpart + (size_t)h * (kGfMaxN / 16) * c->rp * c->rp;
-    }
-    g.Zq = c->gf_Z; g.st = c->st; g.Kp = c->Kp;
-    g.VL = c->VL; g.VLt = c->VLt; g.UL = c->UL; g.ldv = c->ldd;
-    ProfScope pg(c, PC_GRAM, true), pu(c, PC_APPLY, true);
-    g.ev_gram[0] = pg.a; g.ev_gram[1] = pg.b;
-    g.ev_ul[0] = pu.a; g.ev_ul[1] = pu.b;
-    launch_gram_form(L, g);
-  } else {
   if (refine && !c->d_native_valid) {
     // D = X - S_{t-1} in FP32 for the refinement passes
     launch_init_d(L, F32, false, c->D, c->ldd, c->X, c->ldx, c->m, c->n, c->mpad);
     if (c->iters_done > 0)
       launch_update_d(L, F32, c->D, c->ldd, c->n,
                       c->completion ? c->support : c->s_idx[c->cur], c->s_val[c->cur],
-                      c->s_x[c->cur], c->plan[c->cur], kk);
+                      c->s_x[c->cur], c->plan[c->cur], std::max<int64_t>(c->k, 1));
     c->d_native_valid = true;
   }
   // type of chain pass j (the refinement redoes the last one in FP32)
@@ -614,9 +615,11 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
     if (c->f64) {
       ProfScope ps(c, PC_APPLY);
       launch_apply(L, tdb, c->rp, Db, c->ldd, c->m, c->VL, c->UL);
-    } else
+    } else {
       mfma_apply(c, tdb, Db, c->VL, true, nullptr, (float*)c->UL);
-  } else {
+    }
+    return GODEC_OK;
+  }
   // ---- B chain: (D^T D)^q Q2 = Y_q T, then B' = D Y_q ----
   in = c->VL;
   for (int j = 0; j < c->q; ++j) {
@@ -626,14 +629,28 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
   if (c->f64) {
     ProfScope ps(c, PC_APPLY);
     launch_apply(L, tdb, c->rp, Db, c->ldd, c->m, in, c->Bp);
-  } else
+  } else {
     mfma_apply(c, tdb, Db, in, true, nullptr, (float*)c->Bp);
+  }
   // ---- core ----
   const int np = launch_gram_part(L, c->f64, c->rp, c->Bp, c->m, c->Gpart);
   launch_core(L, c->f64, c->rp, c->Gpart, np, 1, c->st, c->p,
               c->rank_tol, c->q == 0 ? 1 : 0, c->Kp);
   launch_apply_small(L, c->f64, c->rp, c->Bp, c->m, c->Kp, c->UL);
-  }
+  return GODEC_OK;
+}
+
+godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
+  const Launch L = launch_of(c);
+  const DType native = c->f64 ? F64 : F32;
+  const bool mixed = c->prec == GODEC_PREC_BF16_REFINE;
+  const bool refine = mixed && total > 0 && t >= total - c->refine_iters;
+  const int64_t kk = std::max<int64_t>(c->k, 1);
+  if (c->gram_form) {
+    l_update_narrow(c);
+  } else {
+    const godec_status st = l_update_panels(c, refine);
+    if (st != GODEC_OK) return st;
   }
   // ---- sparse step ----
   const int prev = c->cur;
@@ -641,7 +658,8 @@ godec_status run_iteration(godec_ctx* c, int64_t t, int64_t total) {
   SelectArgs a;
   a.X = c->X; a.ldx = c->ldx; a.UL = c->UL; a.VL = c->VL; a.m = c->m; a.n = c->n; a.k = c->k;
   a.VLt = c->VLt; a.ldv = c->ldd;
-  a.plan = c->plan[nxt]; a.next = c->plan[prev]; a.first = c->iters_done == 0; a.hist = c->hist; a.counters = c->counters;
+  a.plan = c->plan[nxt]; a.next = c->plan[prev]; a.first = c->iters_done == 0;
+  a.hist = c->hist; a.counters = c->counters;
   a.cand_idx = c->cand_idx; a.cand_val = c->cand_val; a.cand_x = c->cand_x; a.cap = c->cap;
   a.seg_count = c->seg_count;
   a.s_idx = c->s_idx[nxt]; a.s_val = c->s_val[nxt]; a.s_x = c->s_x[nxt];

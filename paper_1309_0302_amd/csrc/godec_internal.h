@@ -133,8 +133,8 @@ int launch_gram_part(const Launch& L, bool f64, int rp, void* P, int64_t rows, d
 // triangular, dependent columns detected: zero columns of Out), rows x RP in
 // the panel type, Out != P; when Zt is given, also its transpose (32 x ldz,
 // bf16 or f32, rows >= RP zero) for the next matrix-core pass, and Ot = Out^T
-// (RP x ldz, panel type).  With acc: acc
-// <- R acc, or R when reset_acc, rescaled by a power of two when normalise.
+// (RP x ldz, panel type).  With acc: acc <- R acc, or R when reset_acc, rescaled
+// by a power of two when normalise.
 void launch_chol_rinv(const Launch& L, bool f64, int rp, const void* P, int64_t rows,
                       const double* Gpart, int nparts, const SmallState* st, double* acc,
                       int reset_acc, int normalise, void* Out, DType zt_type, void* Zt,

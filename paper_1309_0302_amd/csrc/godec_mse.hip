@@ -251,7 +251,8 @@ void run_iteration(godec_mse* m, const char* a1_base) {
   SelectArgs s;
   s.X = m->E; s.ldx = m->lde; s.UL = m->UL0; s.VL = m->VL0; s.VLt = m->VLt0; s.ldv = m->pp;
   s.m = m->n; s.n = m->p; s.k = m->K;
-  s.plan = m->plan[nxt]; s.next = m->plan[m->cur]; s.first = m->iters_done == 0; s.hist = m->hist; s.counters = m->counters;
+  s.plan = m->plan[nxt]; s.next = m->plan[m->cur]; s.first = m->iters_done == 0;
+  s.hist = m->hist; s.counters = m->counters;
   s.cand_idx = m->cand_idx; s.cand_val = m->cand_val; s.cand_x = m->cand_x; s.cap = m->cap;
   s.seg_count = m->seg_count;
   s.s_idx = m->s_idx[nxt]; s.s_val = m->s_val[nxt]; s.s_x = m->s_x[nxt];

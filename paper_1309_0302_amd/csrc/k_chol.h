@@ -47,8 +47,8 @@ __device__ __forceinline__ void chol_prefetch(CholIn<RP>& in, const SmallState* 
 // overwritten with R (LDS scratch for the broadcast reads of R below).  R and
 // the reciprocal diagonal go to Rq (RP x RP) and dinv; acc may be null.
 template <typename TA, int RP>
-__device__ __forceinline__ void wave_chol(double* G, double* Rq, double* dinv, double* acc, int reset_acc,
-                          int normalise, const CholIn<RP>& in) {
+__device__ __forceinline__ void wave_chol(double* G, double* Rq, double* dinv, double* acc,
+                                          int reset_acc, int normalise, const CholIn<RP>& in) {
   const int lane = threadIdx.x & 63;
   const bool col = lane < RP;
   const int reff = in.reff;
@@ -127,12 +127,11 @@ __device__ __forceinline__ void wave_chol(double* G, double* Rq, double* dinv, d
 
 template <typename TA, int RP>
 __device__ __forceinline__ void wave_chol(double* G, SmallState* st, double* acc, int reset_acc,
-                          int normalise) {
+                                          int normalise) {
   CholIn<RP> in;
   chol_prefetch<RP>(in, st, acc, reset_acc);
   wave_chol<TA, RP>(G, st->Rq, st->dinv, acc, reset_acc, normalise, in);
 }
-
 
 // Row x of P R^{-1}: x R = y by forward substitution (R upper triangular, zero
 // rows and dinv = 0 on inactive columns).  Right-looking: the updates of a

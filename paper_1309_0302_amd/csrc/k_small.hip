@@ -315,8 +315,8 @@ __device__ __forceinline__ void gram_sum(const double* __restrict__ Gpart, int n
 // substitution in FP64, one row per thread of waves 1 and 2 (their loads run
 // beside wave 0's factorisation); optionally also the transposed panel Zt (32
 // x ldz) in bf16 or f32 for the next matrix-core pass, rows >= RP zero, and
-// Ot = Out^T (RP x ldz).  With acc, the last block only folds R into it (acc <- R acc, or R with
-// reset_acc), rescaled by a power of two when normalise is set.
+// Ot = Out^T (RP x ldz).  With acc, the last block only folds R into it (acc <-
+// R acc, or R with reset_acc), rescaled by a power of two when normalise is set.
 //
 // kRinvRows rows per block: the LDS reads of R bound the substitution, so the
 // rows are spread over many CUs (256 rows on four waves: 6000 of the block's
@@ -1159,8 +1159,9 @@ __global__ __launch_bounds__(256) void kb_chol(const BProb* __restrict__ probs,
 
 // The same for the batched path (jacobi_eig_inplace).
 template <typename TA, int RP, int NT>
-__device__ __forceinline__ void core_body_inplace(const double* __restrict__ Gpart, int nparts, SmallState* st, int p,
-                          double rank_tol, int t_identity, TA* k_panel) {
+__device__ __forceinline__ void core_body_inplace(const double* __restrict__ Gpart, int nparts,
+                                                  SmallState* st, int p, double rank_tol,
+                                                  int t_identity, TA* k_panel) {
   constexpr int LD = RP + 1;
   __shared__ double G[RP * LD];
   __shared__ double H[RP * LD];
@@ -1177,10 +1178,8 @@ __device__ __forceinline__ void core_body_inplace(const double* __restrict__ Gpa
   const int tid = threadIdx.x;
   const int n = st->r_eff;             // active leading columns
   for (int e = tid; e < RP * RP; e += NT) {
-    double s = 0.0;
-    s = sum_parts(Gpart, nparts, RP * RP, e);
     const int i = e / RP, j = e % RP;
-    G[i * LD + j] = s;
+    G[i * LD + j] = sum_parts(Gpart, nparts, RP * RP, e);
     T[i * LD + j] = t_identity ? (i == j ? 1.0 : 0.0) : st->T[e];
     W[i * LD + j] = st->R2[e];
   }
@@ -1296,11 +1295,11 @@ __device__ __forceinline__ void core_body_inplace(const double* __restrict__ Gpa
 // pass's partials, then the shared FP64 core (rank certificate, Jacobi
 // eigen-solver, K' = T K into Kp).
 __global__ __launch_bounds__(64) void kb_core(const BProb* __restrict__ probs,
-                                                         const double* __restrict__ gslots,
-                                                         int p, int t_identity) {
+                                              const double* __restrict__ gslots, int p,
+                                              int t_identity) {
   const BProb& b = probs[blockIdx.x];
-  core_body_inplace<float, RB, 64>(gslots + (int64_t)b.item0 * RB * RB, b.nitems, b.st, p, b.rank_tol,
-                       t_identity, b.Kp);
+  core_body_inplace<float, RB, 64>(gslots + (int64_t)b.item0 * RB * RB, b.nitems, b.st, p,
+                                   b.rank_tol, t_identity, b.Kp);
 }
 
 __global__ void kb_small_init(const BProb* __restrict__ probs) {
