@@ -205,7 +205,9 @@ size_t carve(godec_ctx* c, void* base) {
                   : nullptr;
   c->VL = cv.take((size_t)ldd * rp * ta);
   c->VLt = cv.take((size_t)ldd * rp * ta);
-  if (c->gram_form) {
+  // (an FP64 matrix has them in either form: the form depends on options, which
+  // a layer's workspace is sized without)
+  if (c->gram_form && !c->f64) {
     c->P0 = c->P1 = c->W = c->Zpart = c->Bp = nullptr;
   } else {
     c->P0 = cv.take((size_t)ldd * rp * ta);

@@ -251,3 +251,23 @@ def test_workspace_does_not_grow(m, n, r, k, q, dtype, prec, fixed, most):
     need = ctypes.c_size_t()
     assert lib.godec_workspace_size(m, n, r, k, q, dtype, ctypes.byref(o), ctypes.byref(need)) == 0
     assert 0 < need.value <= most
+
+
+@pytest.mark.parametrize("m,n,r,q", [(500, 200, 4, 1), (600, 96, 3, 1), (400, 512, 8, 2),
+                                     (300, 300, 2, 0), (700, 600, 5, 1)])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_workspace_does_not_depend_on_the_form(m, n, r, q, dtype):
+    """The L update's form follows lstep and rank_tol on FP64; the size does not
+    (a layer's workspace is sized without options)."""
+    lib = b.load()
+    seen = set()
+    for lstep in (0, 1):
+        for tol in (0.0, 1e-40, 1e-3):
+            o = b.godec_opts()
+            lib.godec_opts_default(ctypes.byref(o))
+            o.lstep, o.rank_tol = lstep, tol
+            need = ctypes.c_size_t()
+            assert lib.godec_workspace_size(m, n, r, m * n // 20, q, dtype, ctypes.byref(o),
+                                            ctypes.byref(need)) == 0
+            seen.add(need.value)
+    assert len(seen) == 1

@@ -463,3 +463,20 @@ def test_batch_lists_from_two_threads():
         t.join()
     assert not wrong
     b.close()
+
+
+def test_fp64_layer_with_a_smaller_rank_tol():
+    """The rank check's tolerance may choose the form of an FP64 layer's L update;
+    L, S and dX agree with the default's to the oracle bars (1e-10)."""
+    from paper_1309_0302_amd.binding import GoDecLayer
+    w = wl.tiny(520, 96, 3, seed=4, dtype=np.float64)
+    X = torch.from_numpy(w.X[None]).to("cuda:0")
+    G = torch.randn(X.shape, generator=torch.Generator("cuda:0").manual_seed(1), device="cuda:0",
+                    dtype=torch.float64)
+    out = []
+    for tol in (0.0, 1e-40):
+        layer = GoDecLayer(3, w.k, 1, 3, seed=5, rank_tol=tol)
+        L, S = layer.forward(X)
+        out.append((L.clone(), S.clone(), layer.backward(G, G).clone()))
+    for a, c in zip(*out):
+        assert (a - c).norm() <= 1e-10 * a.norm()
